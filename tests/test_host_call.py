@@ -1,0 +1,55 @@
+"""The native forward callables of the binding against its Python marshaller: the same results however the arguments
+are passed, and the marshaller's own errors for calls that do not fit."""
+import pytest
+
+torch = pytest.importorskip("torch")
+from paper_2512_20861_amd import binding as B  # noqa: E402
+
+
+def test_malformed_calls_raise_what_the_marshaller_raises():
+    B.lib()
+    x = torch.zeros(4, 8)
+    for fn, args in ((B.monarch_forward, (x, x, x, x, 4, 8)), (B.lowrank_forward, (x, x, x, x)), (B.blast_forward, (x, x, x, x, x, 2, 8)),
+                     (B.dense_reference_forward, (x, x, x)), (B.monarch_rect_forward, (x, x, x, x, 2, 2, 2)), (B.blast_group_forward, (x, x, x, x, 2, 8, 2))):
+        with pytest.raises(Exception) as got:
+            fn(*args)
+        with pytest.raises(Exception) as want:
+            fn.marshal(*args)
+        assert (type(got.value), str(got.value)) == (type(want.value), str(want.value))
+        with pytest.raises(TypeError):
+            fn(x, no_such_argument=1)
+        with pytest.raises(TypeError):
+            fn(*args, X=x)
+        assert fn.__name__ in fn.marshal.__name__ and fn.__doc__ == fn.marshal.__doc__
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T", [1, 33])
+def test_argument_forms_agree(T):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    assert B._host is not None, "the native callables are not built"
+    g = torch.Generator(device="cuda").manual_seed(T)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda").bfloat16()
+    X, R, L = rand(T, 256), rand(4, 64, 64), rand(4, 80, 64)
+    want, Y = torch.zeros((T, 320), dtype=torch.bfloat16, device="cuda"), torch.zeros((T, 320), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(B.monarch_workspace_bytes(T, 256, 320, 4, 64, B.BF16), dtype=torch.uint8, device="cuda")
+    B.prepared(B.monarch_forward, X, R, L, want, 4, 64, 0, ws)()
+    forms = [lambda: B.monarch_forward(X, R, L, Y, 4, 64), lambda: B.monarch_forward(X, R, L, Y, 4, 64, 0, ws),
+             lambda: B.monarch_forward(X, R, L, Y=Y, r=64, nblocks=4, workspace=ws),
+             lambda: B.monarch_forward(X, R, L, Y, 4, 64, workspace=ws, stream=torch.cuda.current_stream())]
+    for call in forms:
+        Y.zero_()
+        assert call() is Y and torch.equal(Y, want)
+    side = torch.cuda.Stream()                           # the stream that is current at the call
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        Y.zero_()
+        B.monarch_forward(X, R, L, Y, 4, 64, workspace=ws)
+    side.synchronize()
+    assert torch.equal(Y, want)
+    with pytest.raises(B.BlrError) as e:                 # an error code of the library
+        B.monarch_forward(X, R, L, Y, 4, 64, workspace=ws[:16])
+    assert e.value.status == B.ERR_WORKSPACE
+    with pytest.raises(ValueError):
+        B.monarch_forward(X, R, L[:, :40], Y, 4, 64, workspace=ws)
