@@ -185,6 +185,13 @@ bool monarch_takes_fused(int64_t T, int n_in, int n_out, int b1, int b2, int rp,
     return base <= 256 && (b2 >= 16 || T <= 64);
 }
 
+// fp32 layers whose whole call is one round of workgroups of the fp32 single kernel (16 tokens x one output block each);
+// with more, the weights a workgroup streams for its 16 tokens are what the call costs.
+bool monarch_takes_f32(int64_t T, int n_in, int n_out, int b1, int b2, int rp, blr_dtype dt, unsigned flags) {
+    if (dt != BLR_F32 || (flags & (BLR_FORCE_GENERIC | BLR_ONLY_FIRST_STAGE | BLR_ONLY_LAST_STAGE | BLR_MONARCH_IN_BLOCKED | BLR_MONARCH_TWO_KERNELS))) return false;
+    return (T + 15) / 16 * b2 <= 512 && monarch_f32_supported(T, n_in, n_out, b1, b2, rp);
+}
+
 // The interleaved output order through 2-byte stores at stride b2 costs stage 2 up to twice its time
 // on large outputs (2048 -> 8192, b = 16, T = 8192: 222 us against 83 us in the blocked order). From
 // 4 M output elements on (2 M for wide rows in 16 and more blocks; graph-replay timings), stage 2 therefore writes the blocked order into the workspace, in chunks
@@ -219,6 +226,9 @@ blr_status monarch_run(const void* X, const void* R, const void* L, void* Y, int
     const bool allow_mfma = !(flags & BLR_FORCE_GENERIC);
     if (monarch_takes_fused(T, n_in, n_out, b1, b2, rp, dt, flags))
         return from_hip(launch_monarch_fused(X, R, L, Y, T, n_in, n_out, b1, b2, rp, flags & BLR_MONARCH_OUT_BLOCKED, s));
+
+    if (monarch_takes_f32(T, n_in, n_out, b1, b2, rp, dt, flags))
+        return from_hip(launch_monarch_f32(X, R, L, Y, T, n_in, n_out, b1, b2, rp, flags & BLR_MONARCH_OUT_BLOCKED, s));
 
     // stage 1: block-diagonal R; tile column n' = k*r' + rho reads row rho*b2 + k of R[l] (the
     // re-layout of the first factor done in the load index) and lands at Z'[t][k][l*r' + rho]

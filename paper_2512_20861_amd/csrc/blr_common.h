@@ -139,6 +139,11 @@ int monarch_fused_lds_bytes(int64_t T, int n_in, int n_out, int b1, int b2, int 
 hipError_t launch_monarch_fused(const void* X, const void* R, const void* L, void* Y, int64_t T, int n_in, int n_out,
                                 int b1, int b2, int rp, bool out_blocked, hipStream_t s);
 
+// the same in fp32, for few tokens (16-byte rows of both factors; a 16-token tile of X and of the intermediate in LDS)
+bool monarch_f32_supported(int64_t T, int n_in, int n_out, int b1, int b2, int rp);
+hipError_t launch_monarch_f32(const void* X, const void* R, const void* L, void* Y, int64_t T, int n_in, int n_out,
+                              int b1, int b2, int rp, bool out_blocked, hipStream_t s);
+
 // BLAST: fused stage 1 + coupling on MFMA. X[T][n_in], Vt[b][r][q], Sp[r][16][16] -> A[T][b][r] (bf16)
 bool blast_fused_supported(int64_t T, int n_in, int b, int r);
 int64_t blast_fused_tiles(int64_t T, int r);                 // workgroups the fused stage 1 + coupling kernel would launch
