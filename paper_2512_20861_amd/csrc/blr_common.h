@@ -126,7 +126,7 @@ size_t gemm_split_scratch_bytes(int64_t M, int N, int K, int G);
 bool gemm_fp8_store_supported(const GemmDesc& d);
 // few tokens (M <= 32): weight-streaming kernel, split-K inside the workgroup; same alignment contract
 bool skinny_gemm_supported(const GemmDesc& d);
-hipError_t launch_gemm_skinny(const GemmDesc& d, bool cvec, hipStream_t s);
+hipError_t launch_gemm_skinny(const GemmDesc& d, hipStream_t s);
 // the same kernel over tiles of 32 tokens (the weights are streamed once per tile): for products with
 // too few 64 x 64 tiles to fill the chip and a long contraction index
 bool skinny_gemm_tiled_supported(const GemmDesc& d);

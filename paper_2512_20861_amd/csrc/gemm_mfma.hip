@@ -957,7 +957,7 @@ hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s) {
         if (d.M > 64 && tiles8(128, 64) >= 160) return deep8 ? launch_line<128, 64, 2, 2, 64, 2>(d, s) : launch_dma<128, 64, 2, 2>(d, s);
         return deep8 ? launch_line<64, 64, 2, 2, 64, 2>(d, s) : launch_dma<64, 64, 2, 2>(d, s);
     }
-    if (skinny_gemm_supported(d)) return launch_gemm_skinny(d, c_map_vectorizes(d), s);
+    if (skinny_gemm_supported(d)) return launch_gemm_skinny(d, s);
     constexpr int kSmallK = 128;     // very short contractions: 128 x 128 tiles, two workgroups per CU overlap prologue and epilogue
                                      // (measured at K = 256, M = 1024 ... 32768: 256 x 256 tiles are 16-23 % faster)
     auto tiles = [&](int bm, int bn) { return (int64_t)((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn) * d.G; };
@@ -1050,7 +1050,7 @@ hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s) {
         const double est_us = (double)((wgs + 255) / 256) * (d.K * 96 / 55e3 + 1.0);
         // ... or under about 9 us when one round of workgroups covers at least half of the chip (4096 x 1024
         // weights at 64 ... 128 tokens: 10 us against 12-13 us; with 32 workgroups the split parts win)
-        if (est_us <= 6.5 || (wgs >= 128 && wgs <= 256 && est_us <= 9.0)) return launch_gemm_skinny(d, c_map_vectorizes(d), s);
+        if (est_us <= 6.5 || (wgs >= 128 && wgs <= 256 && est_us <= 9.0)) return launch_gemm_skinny(d, s);
     }
     if (d.split_scratch && split_plan(tiles(64, 64), d.K).nsplit > 1) return launch_dma<64, 64, 2, 2>(d, s, true);
     // the smallest tile already from 128 workgroups on: at 128 tokens it beats the weight-streaming kernel over
@@ -1066,7 +1066,7 @@ hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s) {
     if (skinny_gemm_tiled_supported(d)) {
         const int64_t wgs = ((d.M + 31) / 32) * ((d.N + 15) / 16) * d.G;
         const double est_us = (double)((wgs + 255) / 256) * (d.K * 96 / 55e3 + 1.0);
-        if (est_us < 0.85 * ((d.K + 31) / 32 * 0.17 + 3.0)) return launch_gemm_skinny(d, c_map_vectorizes(d), s);
+        if (est_us < 0.85 * ((d.K + 31) / 32 * 0.17 + 3.0)) return launch_gemm_skinny(d, s);
     }
     // too small to fill the chip with any tile: fewest, largest tiles that fit the shape
     if (d.M > 64 && d.N > 64) return tiles(64, 64) >= 64 ? launch_dma<64, 64, 2, 2>(d, s) : launch_dma<128, 128, 2, 2>(d, s);

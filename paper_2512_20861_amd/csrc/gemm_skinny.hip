@@ -1,17 +1,20 @@
-// bf16 MFMA batched "NT" GEMM for FEW tokens (M <= 32): the weight-streaming regime, HBM-bound. Also
-// used tile by tile (32 tokens per workgroup, grid.y) for products with small weights, few 64 x 64
-// tiles and a long contraction index, where the weights then come from L2.
+// bf16 MFMA batched "NT" GEMM for FEW tokens (M <= 32): the weight-streaming regime. Also used tile by tile (32 tokens
+// per workgroup) for products with small weights, few 64 x 64 tiles and a long contraction index, where the weights
+// then come from L2.
 //
-// With few tokens the product is a stream of the weights through the chip, so the tiling is turned
-// around: a workgroup owns 16 weight rows (output columns) and ALL tokens, and its four wavefronts
-// split the contraction index between them (split-K inside the workgroup, summed through LDS in a
-// fixed order, so results do not depend on timing). Every weight element is fetched from HBM exactly
-// once, straight into v_mfma_f32_16x16x32_bf16 fragments (one 16-byte load per lane and k32 step,
-// several steps in flight per wavefront to cover HBM latency); the token fragments come from L2.
-// Many small workgroups (N/16 per batch entry) put every compute unit to work on the stream, which
-// the square tiles of the large-problem kernel cannot do when there is only one row of tiles.
-// The weight fragment is the first MFMA operand, as in the large kernel: an accumulator lane holds
-// four consecutive output columns of one token. Same index maps on B rows and C columns.
+// With few tokens the product is a stream of the weights through the chip, so the tiling is turned around: a
+// workgroup owns 16 weight rows (output columns) and ALL tokens, and its wavefronts split the contraction index
+// between them (split-K inside the workgroup, summed through LDS in wavefront order, so results do not depend on
+// timing). Many small workgroups (N/16 per batch entry) put every compute unit to work on the stream.
+//
+// What bounds it: a launch (2.0 us for an empty kernel in a graph) plus one memory latency, and the instructions
+// themselves: code that runs once per launch is fetched at the latency of the L2. So the loops are rolled, the operands
+// go to LDS with direct loads (no registers, hence no unrolling, to hold what is in flight), and the index maps are
+// grid dimensions instead of divisions. Monarch 4096 x 4096, 4 blocks, r = 1024, both products with weights from the
+// memory-side cache (16.8 MB): 6.8 us for one token and 7.5 for 16, against 9.1 and 9.9 with eight unrolled register
+// buffers, cross-lane permutes and a general column map per element.
+//
+// The weight fragment is the first MFMA operand: an accumulator lane holds four consecutive output columns of one token.
 #include "blr_common.h"
 
 namespace blr {
@@ -21,139 +24,195 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 constexpr int SK_BN = 16;             // weight rows per workgroup
-constexpr int SK_WAVES = 4;           // wavefronts = K splits per workgroup
+constexpr int SK_RD = 8;              // k32 steps in flight per wavefront
 
-// MT: 16-token tiles (M <= 16 MT); D: k32 steps of loads in flight per wavefront
-template <int MT, int D>
-__global__ __launch_bounds__(64 * SK_WAVES) void gemm_skinny_kernel(GemmDesc d, int tiles_n, int cvec) {
-    __shared__ __attribute__((aligned(16))) float part[SK_WAVES][MT * 16][SK_BN + 4];   // partial sums [wave][token][column]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int g = blockIdx.x / tiles_n;
-    const int n0 = (blockIdx.x % tiles_n) * SK_BN;
-    const int l16 = lane & 15, kg = lane >> 4;          // fragment row, group of 8 consecutive k (of the step's 32)
-    const int64_t m_base = (int64_t)blockIdx.y * (MT * 16);   // more tokens than one tile: grid.y walks tiles of 16 MT tokens
+// C(g, m, s, i) = sum_k A(g, m, k) B(g, s, i, k) over segments s of n columns i each: both index maps of a GemmDesc
+// (row gather of B, column scatter of C) are products of the segment and the place in it.
+struct SkinnyArgs {
+    const bf16_t *A, *B;
+    bf16_t* C;
+    int64_t a_gs, a_rs, b_gs, c_gs, c_rs, b_s, c_s, c_i;
+    unsigned b_i;                     // row pitch of B inside a segment (elements)
+    int M, n, K;
+    int a_seg;
+    int64_t a_seg_stride;
+    int kper;                         // contraction indices per wavefront, a multiple of 32
+    int slots;                        // steps a wavefront's part of LDS holds (<= SK_RD)
+    int mtiles;                       // tiles of 16 MT tokens
+};
 
-    // A fragment (16 rows x 32 k) is LOADED with four neighbouring lanes on the 64 contiguous bytes of one
-    // row (lane = 4 row + piece: 16 requests of 64 bytes per instruction) and moved to the MFMA's order
-    // (lane = 16 piece + row) by a cross-lane permute when it is used: loaded in the MFMA's order every
-    // lane would be a 16-byte request of its own, which the load path serves several times slower.
-    const int ld_row = lane >> 2, ld_piece = lane & 3;
-    const int from_lane = (l16 * 4 + kg) * 4;           // byte index of the lane that loaded this lane's piece
-    // fragment sources: weight row n0 + ld_row, token rows mt*16 + ld_row
-    int n = n0 + ld_row;
-    if (n > d.N - 1) n = d.N - 1;                       // rows past N repeat the last row; never stored
-    const int64_t nr = d.b_div ? (int64_t)(n % d.b_div) * d.b_mul + n / d.b_div : n;
-    const bf16_t* wp = (const bf16_t*)d.B + (int64_t)g * d.b_gs + nr * d.b_rs;
-    const bf16_t* xp[MT];
+__device__ __forceinline__ bf16x8 lds_read_frag(unsigned addr) {   // (reads the compiler can see wait for all direct loads)
+    bf16x8 v;
+    asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr) : "memory");
+    return v;
+}
+
+// MT: 16-token tiles (M <= 16 MT); NW: wavefronts = K splits; TAIL: K is no multiple of 32
+template <int MT, int NW, bool TAIL>
+__global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int SLOT = (1 + MT) * 1024;                // 16 weight rows and 16 MT token rows of 64 bytes
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i0 = blockIdx.x * SK_BN, s = blockIdx.y;
+    int g = blockIdx.z, m_base = 0;
+    if (a.mtiles > 1) {
+        m_base = (g % a.mtiles) * (MT * 16);
+        g /= a.mtiles;
+    }
+    // A direct load fills 16 rows of 64 bytes: lane l brings the piece of slot l % 4 of row l / 4. The pieces are
+    // XOR-swizzled by the row so that the 16 rows a fragment read serves per clock cover all banks.
+    const int lrow = lane >> 2, piece = (lane & 3) ^ ((lrow >> 2) & 3);
+    const int kw = wave * a.kper;
+    const unsigned char* B = (const unsigned char*)(a.B + g * a.b_gs + s * a.b_s);
+    const unsigned char* A = (const unsigned char*)(a.A + g * a.a_gs + m_base * a.a_rs);
+    const int row = i0 + lrow < a.n ? i0 + lrow : a.n - 1;          // rows past the segment repeat its last one; never stored
+    unsigned woff = (unsigned)row * a.b_i, xoff[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-        int64_t m = m_base + mt * 16 + ld_row;
-        if (m > d.M - 1) m = d.M - 1;
-        xp[mt] = (const bf16_t*)d.A + (int64_t)g * d.a_gs + m * d.a_rs;
+        const int m = mt * 16 + lrow, left = a.M - m_base - 1;
+        xoff[mt] = (unsigned)(m < left ? m : left) * (unsigned)a.a_rs;
     }
-    // this wavefront's k32 steps
-    const int nk = (d.K + 31) >> 5;
-    const int per = (nk + SK_WAVES - 1) / SK_WAVES;
-    const int s_begin = wave * per;
-    int s_end = s_begin + per;
-    if (s_end > nk) s_end = nk;
-    const int nsteps = s_end > s_begin ? s_end - s_begin : 0;
-
-    // register ring, slots indexed statically; loads unconditional (clamped), zeroed on use past K
-    uint4 rw[D], rx[D][MT];
-    auto gload = [&](auto SLOT, int s) {
-        constexpr int slot = decltype(SLOT)::value;
-        int ks = s_begin + s;
-        if (ks > nk - 1) ks = nk - 1;                   // steps past the end repeat the last one; never consumed
-        int k = ks * 32 + ld_piece * 8;
-        if (k > d.K - 8) k = d.K - 8;                   // k groups past K re-read valid data (K is a multiple of 8)
-        rw[slot] = *(const uint4*)(wp + k);
-        // segmented contraction index of A: a k32 step lies inside one segment (uniform division)
-        const int64_t ka = d.a_seg ? (int64_t)((ks * 32) / d.a_seg) * (d.a_seg_stride - d.a_seg) + k : k;
+    unsigned char* mine = smem + wave * (a.slots * SLOT);
+    const int steps = a.K - kw <= 0 ? 0 : ((a.K - kw < a.kper ? a.K - kw : a.kper) + 31) >> 5;
+    int kf = kw;                                        // contraction index under the fetch cursor
+    int64_t seg_off = 0;                                // segmented contraction index of A: what to add to it (a step lies in one segment)
+    int seg_left = 0x7fffffff;
+    if (a.a_seg) {
+        seg_off = (int64_t)(kw / a.a_seg) * (a.a_seg_stride - a.a_seg);
+        seg_left = a.a_seg - kw % a.a_seg;
+    }
+    auto fetch = [&](unsigned char* slot) {
+        unsigned kl = kf + piece * 8;
+        if (TAIL) kl = kl < (unsigned)a.K ? kl : a.K - 8;           // pieces past K re-read the last one, zeroed on use
+        __builtin_amdgcn_global_load_lds(BLR_GPTR(B + (woff + kl) * 2u), BLR_LPTR(slot), 16, 0, 0);
+        const unsigned char* As = A + seg_off * 2;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) rx[slot][mt] = *(const uint4*)(xp[mt] + ka);
+        for (int mt = 0; mt < MT; ++mt)
+            __builtin_amdgcn_global_load_lds(BLR_GPTR(As + (xoff[mt] + kl) * 2u), BLR_LPTR(slot + (1 + mt) * 1024), 16, 0, 0);
+        kf += 32;
+        seg_left -= 32;
+        if (seg_left == 0) {
+            seg_left = a.a_seg;
+            seg_off += a.a_seg_stride - a.a_seg;
+        }
     };
-    auto to_mfma_order = [&](uint4 v) -> uint4 {
-        return make_uint4((unsigned)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.x), (unsigned)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.y),
-                          (unsigned)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.z), (unsigned)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.w));
-    };
+    const int l16 = lane & 15, kg = lane >> 4;
+    const unsigned frag = (unsigned)(uintptr_t)BLR_LPTR(mine) + l16 * 64 + ((kg ^ ((l16 >> 2) & 3)) * 16);
     f32x4 acc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto step = [&](auto U, int s) {
-        constexpr int u = decltype(U)::value;
-        const bool ok = (s_begin + s) * 32 + kg * 8 < d.K;
-        const uint4 w = keep_if(ok, to_mfma_order(rw[u]));
+    auto multiply = [&](bf16x8 w, const bf16x8 (&x)[MT], int t) {   // (after the wait for both)
+        if (TAIL) {
+            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+            if (kw + t * 32 + kg * 8 >= a.K) w = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x[mt], acc[mt], 0, 0, 0);
+    };
+
+    int t = 0;
+    for (; t < steps && t < a.slots; ++t) fetch(mine + t * SLOT);
+    t = 0;
+    unsigned at = 0;                                    // slot of step t (bytes)
+#pragma unroll 1
+    for (; t + SK_RD < steps; ++t) {                    // (only with all SK_RD slots: what is in flight is a constant)
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((1 + MT) * (SK_RD - 1)) : "memory");
+        bf16x8 w = lds_read_frag(frag + at), x[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) x[mt] = lds_read_frag(frag + at + (1 + mt) * 1024);
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w) :: "memory");
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) asm volatile("" : "+v"(x[mt]));
+        fetch(mine + at);
+        multiply(w, x, t);
+        at = at == (SK_RD - 1) * SLOT ? 0 : at + SLOT;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll 1
+    while (t < steps) {                                 // what is left has landed; two steps per trip share an LDS latency
+        const unsigned at1 = at == (unsigned)(a.slots - 1) * SLOT ? 0 : at + SLOT;
+        bf16x8 w0 = lds_read_frag(frag + at), w1 = lds_read_frag(frag + at1), x0[MT], x1[MT];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const uint4 x = to_mfma_order(rx[u][mt]);
-            acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8*)&w, *(const bf16x8*)&x, acc[mt], 0, 0, 0);
+            x0[mt] = lds_read_frag(frag + at + (1 + mt) * 1024);
+            x1[mt] = lds_read_frag(frag + at1 + (1 + mt) * 1024);
         }
-        gload(U, s + D);
-    };
-    static_for<D>([&](auto U) { gload(U, decltype(U)::value); });
-    int s0 = 0;
-    for (; s0 + D <= nsteps; s0 += D) static_for<D>([&](auto U) { step(U, s0 + decltype(U)::value); });
-    static_for<D - 1>([&](auto U) { if (s0 + decltype(U)::value < nsteps) step(U, s0 + decltype(U)::value); });
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w0), "+v"(w1) :: "memory");
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) asm volatile("" : "+v"(x0[mt]), "+v"(x1[mt]));
+        multiply(w0, x0, t);
+        if (t + 1 < steps) multiply(w1, x1, t + 1);     // uniform
+        t += 2;
+        at = at1 == (unsigned)(a.slots - 1) * SLOT ? 0 : at1 + SLOT;
+    }
+    __syncthreads();                                    // every wavefront is past its operands: the partial sums take their place
 
     // acc[mt][e]: token mt*16 + l16, column 4*kg + e
+    float* part = (float*)smem;                         // [wave][16 MT tokens][16 columns + 4]
+    constexpr int PSTR = SK_BN + 4;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
-        *(float4*)&part[wave][mt * 16 + l16][4 * kg] = make_float4(acc[mt][0], acc[mt][1], acc[mt][2], acc[mt][3]);
+        *(f32x4*)(part + ((wave * MT + mt) * 16 + l16) * PSTR + 4 * kg) = acc[mt];
     __syncthreads();
-
-    // sum the K splits in wavefront order and store: one item = one token x 8 columns
-    bf16_t* Cp = (bf16_t*)d.C;
-    for (int id = tid; id < MT * 16 * (SK_BN / 8); id += 64 * SK_WAVES) {
-        const int row = id / (SK_BN / 8), c8 = (id % (SK_BN / 8)) * 8;
-        const int nn = n0 + c8;
-        const int64_t mrow = m_base + row;
-        if (mrow >= d.M || nn >= d.N) continue;
-        float v[8];
+    for (int o = tid; o < MT * 256; o += 64 * NW) {
+        const int m = o >> 4, c = o & 15;
+        if (m_base + m >= a.M || i0 + c >= a.n) continue;
+        float v = part[m * PSTR + c];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = part[0][row][c8 + i];
-#pragma unroll
-        for (int w = 1; w < SK_WAVES; ++w)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] += part[w][row][c8 + i];
-        if (cvec) {                                     // 8 consecutive (8-aligned) columns are 16 contiguous bytes of C
-            const int64_t col = (int64_t)g * d.c_gs + (int64_t)(nn / d.c_div) * d.c_hi + (int64_t)(nn % d.c_div) * d.c_lo;
-            *(uint4*)(Cp + mrow * d.c_rs + col) =
-                make_uint4(pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3]), pack2_bf16(v[4], v[5]), pack2_bf16(v[6], v[7]));
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int ni = nn + i;
-                if (ni < d.N) {
-                    const int64_t col = (int64_t)g * d.c_gs + (int64_t)(ni / d.c_div) * d.c_hi + (int64_t)(ni % d.c_div) * d.c_lo;
-                    Cp[mrow * d.c_rs + col] = float_to_bf16(v[i]);
-                }
-            }
-        }
+        for (int w = 1; w < NW; ++w) v += part[(w * MT * 16 + m) * PSTR + c];
+        a.C[(m_base + m) * a.c_rs + g * a.c_gs + s * a.c_s + (i0 + c) * a.c_i] = float_to_bf16(v);
     }
 }
 
-template <int MT, int D>
-hipError_t launch_skinny(const GemmDesc& d, int cvec, hipStream_t s) {
-    const int tiles_n = (d.N + SK_BN - 1) / SK_BN;
-    const unsigned tiles_m = (unsigned)((d.M + MT * 16 - 1) / (MT * 16));
-    hipLaunchKernelGGL((gemm_skinny_kernel<MT, D>), dim3((unsigned)(tiles_n * d.G), tiles_m), dim3(64 * SK_WAVES), 0, s, d, tiles_n, cvec);
+template <int MT, int NW>
+hipError_t launch_skinny(SkinnyArgs& a, dim3 grid, hipStream_t s) {
+    const int nk = (a.K + 31) / 32, per = (nk + NW - 1) / NW;
+    a.kper = per * 32;
+    a.slots = per < SK_RD ? per : SK_RD;
+    const int lds = NW * a.slots * (1 + MT) * 1024;
+    static LdsLimitOnce lds_limit;
+    if (hipError_t e = lds_limit.set({(const void*)gemm_skinny_kernel<MT, NW, false>, (const void*)gemm_skinny_kernel<MT, NW, true>}, NW * SK_RD * (1 + MT) * 1024); e != hipSuccess) return e;
+    if (a.K % 32) hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, true>), grid, dim3(64 * NW), lds, s, a);
+    else hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, false>), grid, dim3(64 * NW), lds, s, a);
     return hipGetLastError();
+}
+
+// segments of the two index maps: the whole N without a gather, else the blocks of b_div columns
+inline bool segments(const GemmDesc& d, int& n, int& nseg) {
+    if (d.b_div == 0 && d.c_div == 1) { n = d.N; nseg = 1; return true; }
+    if (d.b_div <= 0 || d.b_div != d.c_div || d.N % d.b_div) return false;
+    n = d.b_div; nseg = d.N / d.b_div;
+    return nseg <= 65535;
+}
+
+bool shape_ok(const GemmDesc& d, int64_t mtiles) {
+    int n, nseg;
+    return segments(d, n, nseg) && mtiles * d.G <= 65535;
 }
 
 }  // namespace
 
-bool skinny_gemm_supported(const GemmDesc& d) {
-    return d.M <= 32 && (int64_t)((d.N + SK_BN - 1) / SK_BN) * d.G < (1ll << 31);
+bool skinny_gemm_supported(const GemmDesc& d) { return d.M <= 32 && shape_ok(d, 1); }
+
+hipError_t launch_gemm_skinny(const GemmDesc& d, hipStream_t s) {
+    SkinnyArgs a{};
+    int n, nseg;
+    segments(d, n, nseg);
+    a.A = (const bf16_t*)d.A; a.B = (const bf16_t*)d.B; a.C = (bf16_t*)d.C;
+    a.a_gs = d.a_gs; a.a_rs = d.a_rs; a.b_gs = d.b_gs; a.c_gs = d.c_gs; a.c_rs = d.c_rs;
+    a.M = (int)d.M; a.n = n; a.K = d.K;
+    if (d.b_div) { a.b_i = (unsigned)(d.b_mul * d.b_rs); a.b_s = d.b_rs; a.c_i = d.c_lo; a.c_s = d.c_hi; }
+    else { a.b_i = (unsigned)d.b_rs; a.b_s = 0; a.c_i = d.c_hi; a.c_s = 0; }
+    a.a_seg = d.a_seg; a.a_seg_stride = d.a_seg_stride;
+    const int mt = d.M <= 16 ? 1 : 2;                   // more than 32 tokens: one workgroup per 32-token tile and 16 weight rows
+    a.mtiles = (int)((d.M + mt * 16 - 1) / (mt * 16));
+    const dim3 grid((unsigned)((n + SK_BN - 1) / SK_BN), (unsigned)nseg, (unsigned)(d.G * a.mtiles));
+    // eight wavefronts where each still gets two or more steps (K >= 512): twice the bytes in flight of a workgroup and half its steps
+    if (mt == 1) return d.K >= 512 ? launch_skinny<1, 8>(a, grid, s) : launch_skinny<1, 4>(a, grid, s);
+    return launch_skinny<2, 4>(a, grid, s);
 }
 
-hipError_t launch_gemm_skinny(const GemmDesc& d, bool cvec, hipStream_t s) {
-    if (d.M <= 16) return launch_skinny<1, 8>(d, cvec, s);
-    return launch_skinny<2, 8>(d, cvec, s);             // more than 32 tokens: one workgroup per 32-token tile and 16 weight rows
-}
-
-bool skinny_gemm_tiled_supported(const GemmDesc& d) {
-    return d.M <= 65535ll * 32 && (int64_t)((d.N + SK_BN - 1) / SK_BN) * d.G < (1ll << 31);
-}
+bool skinny_gemm_tiled_supported(const GemmDesc& d) { return d.M < (1ll << 20) && shape_ok(d, (d.M + 31) / 32); }
 
 }  // namespace blr
