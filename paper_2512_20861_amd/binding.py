@@ -49,6 +49,25 @@ EXPORTS = ("blr_status_string", "blr_monarch_workspace_bytes", "blr_monarch_forw
            "blr_blast_group_workspace_bytes", "blr_blast_group_forward",
            "blr_monarch_group_first_factor", "blr_static_scratch_bytes", "blr_monarch_forward_static")
 
+
+
+class ChainDesc(ctypes.Structure):
+    _fields_ = [("blast", ctypes.c_int), ("layers", ctypes.c_int), ("T", ctypes.c_int64), ("hidden", ctypes.c_int), ("mlp", ctypes.c_int),
+                ("b", ctypes.c_int), ("r_square", ctypes.c_int), ("r_mlp", ctypes.c_int), ("eps", ctypes.c_float)]
+
+
+class ChainFactors(ctypes.Structure):
+    _fields_ = [("first", ctypes.c_void_p), ("second", ctypes.c_void_p)]
+
+
+class ChainLayer(ctypes.Structure):
+    _fields_ = [(n, ChainFactors) for n in ("qkv", "o", "gate_up", "down")]
+
+
+class ChainBuffers(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("h", "h2", "n", "a", "o", "dn", "qkv", "gu", "m", "workspace")] + [("workspace_bytes", ctypes.c_size_t)]
+
+
 _lib = None
 
 
@@ -117,6 +136,12 @@ def lib() -> ctypes.CDLL:
         L.blr_sum3_scaled_ld.argtypes = [vp, vp, vp, vp, i64, ci, i64, cf, ci, vp]
         L.blr_silu_mul_ld.restype = ci
         L.blr_silu_mul_ld.argtypes = [vp, vp, vp, i64, ci, i64, ci, vp]
+        L.blr_chain_create.restype = ci
+        L.blr_chain_create.argtypes = [ctypes.POINTER(ChainDesc), ctypes.POINTER(ChainLayer), ctypes.POINTER(ChainBuffers), ctypes.POINTER(vp)]
+        L.blr_chain_forward.restype = ci
+        L.blr_chain_forward.argtypes = [vp, vp]
+        L.blr_chain_destroy.restype = None
+        L.blr_chain_destroy.argtypes = [vp]
         _lib = L
     return _lib
 
@@ -424,3 +449,23 @@ def silu_mul(G, U, M, stream=None):
             raise ValueError("column slices must share one row stride and the output must be contiguous")
         return ("blr_silu_mul_ld", (_ptr_rows(G), _ptr_rows(U), _ptr(M), T, d, G.stride(0), _dt(G), _stream(stream)), M, (G, U, M))
     return ("blr_silu_mul", (_ptr(G), _ptr(U), _ptr(M), T, d, _dt(G), _stream(stream)), M, (G, U, M))
+
+
+def chain_create(desc, layers, buffers):
+    """Handle of a native decoder-layer chain (include/blr_chain.h), or None where its shapes have no grouped execution.
+    The tensors behind the pointers have to outlive it; chain_destroy ends it."""
+    handle = ctypes.c_void_p()
+    st = lib().blr_chain_create(ctypes.byref(desc), layers, ctypes.byref(buffers), ctypes.byref(handle))
+    if st == ERR_UNSUPPORTED:
+        return None
+    _check(st, "blr_chain_create")
+    return handle
+
+
+def chain_forward(handle, stream=None):
+    """One pass of the chain, in place on its residual stream."""
+    _check(lib().blr_chain_forward(handle, _stream(stream)), "blr_chain_forward")
+
+
+def chain_destroy(handle):
+    lib().blr_chain_destroy(handle)

@@ -16,6 +16,9 @@ first factors are interleaved (done once at set-up by blr_monarch_group_first_fa
 larger ones; their outputs lie side by side in one tensor and the glue reads them as column slices.
 In an all-BLAST chain the same linears run as one grouped BLAST call each (stages 1 and 2 on the
 members' concatenated rank indices, one stage-3 product per member).
+
+A pass of a grouped bf16 chain is one call of the library (include/blr_chain.h), which enqueues the same
+steps, or fewer and larger ones, from native code; the call list below is the step-by-step form of it.
 """
 from __future__ import annotations
 
@@ -164,6 +167,36 @@ class DeviceChain:
         need = max([lin.workspace_bytes(T) for layer in self.layers for lin in layer.values()] +
                    [grp.workspace_bytes(T) for layer in self.groups for grp in layer.values()])
         self.ws = torch.empty(max(need, 16), dtype=torch.uint8, device="cuda")
+        self._native = self._create_native() if self.grouped and td == torch.bfloat16 and T > 0 else None
+
+    def _create_native(self):
+        """Handle of the library's chain object over this object's factors and buffers, or None where it has none."""
+        L0 = self.layers[0]
+        def factors(lin):
+            if isinstance(lin, _MonarchGroup):
+                return lin.R, lin.L
+            if isinstance(lin, _BlastGroup):
+                return lin.packed, lin.U
+            return (lin.R, lin.L) if lin.op == "monarch" else (getattr(lin, "packed", None), lin.U)
+        layers = (B.ChainLayer * len(self.layers))()
+        for i, L in enumerate(self.layers):
+            lins = (self.groups[i]["qkv"], L["o"], self.groups[i]["gu"], L["down"])
+            for field, lin in zip(("qkv", "o", "gate_up", "down"), lins):
+                first, second = factors(lin)
+                if first is None:
+                    return None
+                setattr(layers[i], field, B.ChainFactors(first.data_ptr(), second.data_ptr()))
+        self.h2 = torch.empty_like(self.h)
+        buffers = B.ChainBuffers(*(t.data_ptr() for t in (self.h, self.h2, self.n, self.a, self.o, self.dn, self.qkv, self.gu, self.m, self.ws)), self.ws.numel())
+        blast = L0["q"].op == "blast"
+        desc = B.ChainDesc(int(blast), len(self.layers), self.T, self.hidden, self.mlp, L0["q"].b if blast else L0["q"].nb, L0["q"].r, L0["gate"].r, self.eps)
+        same = all(L[n].r == L0[n].r for L in self.layers for n in LINEARS) and all(L0[n].r == L0["q"].r for n in "kvo") and L0["down"].r == L0["gate"].r
+        return B.chain_create(desc, layers, buffers) if same else None
+
+    def __del__(self):
+        if getattr(self, "_native", None):
+            B.chain_destroy(self._native)
+            self._native = None
 
     def call_list(self):
         """[(label, (fn, *args)), ...] in execution order; h must hold the input when the first one runs."""
@@ -199,6 +232,9 @@ class DeviceChain:
         recorded under the labels of its member linears, each with its own slice of the output);
         `rows` (an index tensor) restricts the copies to those token rows."""
         self.h.copy_(x0)
+        if self._native and not record:
+            B.chain_forward(self._native)
+            return self.h
         taps = {}
         keep = (lambda t: t.clone()) if rows is None else (lambda t: t[rows].clone())
         for label, args in self.call_list():

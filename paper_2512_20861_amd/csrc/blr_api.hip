@@ -90,6 +90,10 @@ inline int64_t fused_min_tiles(int n_in, int b) {
 // 16-token tiles is ahead (BLAST 4096 x 4096, r = 640: 13.6 against 14.4 us at 33 tokens, 16.5 against 15.9 at 64,
 // 17.4 against 15.5 at 100, 19.0 against 16.3 at 128).
 constexpr int64_t kSmallCouplingTokens = 48;
+// Up to this many tokens the workgroups of stage 3 compute the coupling themselves: one launch less (3.5 us of host time in
+// a loop of separate calls) at level GPU time (4096 x 4096, r = 640 at 1 / 2 / 4 tokens: 7.3 / 7.6 / 8.7 us against 7.9 / 8.0 / 8.0
+// with the coupling as a launch; every workgroup repeats it, so it grows with the tokens).
+constexpr int64_t kCoupledTokens = 2;
 
 // The single kernel for few, wide blocks: forced by its flag, else where it was measured ahead of the three kernels.
 bool blast_narrow_possible(int64_t T, int n_in, int n_out, int b, int r, unsigned flags) {
@@ -278,6 +282,14 @@ bool monarch_rect_shape_ok(int64_t T, int n_in, int n_out, int b1, int b2, int r
 
 }  // namespace
 
+namespace blr {
+void blast_packed_parts(const void* packed, int n_in, int n_out, int b, int r, const void** Vt, const void** Sc) {
+    const PackLayout pk = pack_layout(n_in, n_out, b, r);
+    *Vt = (const unsigned char*)packed + pk.off_Vt;
+    *Sc = (const unsigned char*)packed + pk.off_Sc;
+}
+}  // namespace blr
+
 // A group runs on the bf16 MFMA kernels of stages 1 and 2 with the concatenated rank, or not at all.
 static bool blast_group_ok(int64_t T, int n_in, int n_out, int b, int r, int members, blr_dtype dt, unsigned flags) {
     if (members <= 0 || r <= 0 || r % 8 || (int64_t)r * members > (1 << 24) || dt != BLR_BF16 || b > 16) return false;   // 8 | r: every member's range of A starts on a 16-byte boundary
@@ -367,6 +379,17 @@ static blr_status blast_run(const void* X, const void* U, const void* S, const v
             if (st != BLR_OK) return st;
         }
         return last ? run_stage3(0, T, true) : BLR_OK;
+    }
+    // A handful of tokens: stage 1, then stage 3 of all members with the coupling computed in its workgroups
+    GemmDesc s3c = s3;
+    s3c.B = U; s3c.C = Y; s3c.G = members * b;
+    if (first && last && !(flags & BLR_BLAST_Z_FP8) && T <= kCoupledTokens && skinny_source_supported(s3c)) {
+        s1.B = Vt; s1.b_gs = (int64_t)q * r; s1.b_rs = q; s1.b_ks = 1; s1.b_div = 0;
+        blr_status st = run_gemm(s1, dt, true, s);
+        if (st != BLR_OK) return st;
+        SkinnySource src{};
+        src.a = (const bf16_t*)Zws; src.y = (const bf16_t*)(pack + pk.off_Sc); src.d = r; src.b = b;
+        return from_hip(launch_gemm_skinny_from(kSrcCoupling, s3c, src, s));
     }
     // three kernels per chunk of tokens: stage-1 GEMM -> Z, MFMA coupling Z -> A, stage-3 GEMM
     s1.B = Vt; s1.b_gs = (int64_t)q * r; s1.b_rs = q; s1.b_ks = 1; s1.b_div = 0;

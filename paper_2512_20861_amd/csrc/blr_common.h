@@ -127,6 +127,21 @@ bool gemm_fp8_store_supported(const GemmDesc& d);
 // few tokens (M <= 32): weight-streaming kernel, split-K inside the workgroup; same alignment contract
 bool skinny_gemm_supported(const GemmDesc& d);
 hipError_t launch_gemm_skinny(const GemmDesc& d, hipStream_t s);
+// The same kernel for a handful of tokens with its rows A(g, m, :) computed by every workgroup from what they are made of:
+enum { kSrcInput = 0, kSrcNorm, kSrcSum3, kSrcSilu, kSrcCoupling };
+constexpr int kSourceTokens = 8;       // at most
+struct SkinnySource {
+    const bf16_t* a;                   // norm: H[M][d]; sum, gate: the tensor whose column slices are combined; coupling: Z[M][b][d]
+    const bf16_t* y;                   // norm: Y[M][d], added first (or null); coupling: S[b][b][d]
+    bf16_t* out;                       // norm: receives H + Y (not H itself; or null)
+    int64_t ld, slice, gs, seg_stride; // sum, gate: row pitch, distance of the slices, of the batch entries, of the segments
+    int d, seg, b;                     // norm, coupling: row length (G K; members r); sum, gate: segment length (8 | seg); coupling: blocks
+    float scale;                       // sum: factor; norm: eps
+};
+// norm: row slice [g K, g K + K) of H' / sqrt(mean(H'^2) + eps), H' = H + Y. sum, gate: elements (k / seg) seg_stride + k % seg
+// + g gs of the slices. coupling: G = members * b batch entries (member, output block), K = r, A[t][rho] = sum_j S[i][j][.] Z[t][j][.].
+bool skinny_source_supported(const GemmDesc& d);
+hipError_t launch_gemm_skinny_from(int kind, const GemmDesc& d, const SkinnySource& src, hipStream_t s);
 // the same kernel over tiles of 32 tokens (the weights are streamed once per tile): for products with
 // too few 64 x 64 tiles to fill the chip and a long contraction index
 bool skinny_gemm_tiled_supported(const GemmDesc& d);
@@ -173,6 +188,12 @@ hipError_t launch_blast_narrow(const void* X, const void* Vt, const void* S, con
 
 // stand-alone coupling reading the packed tiles Sp[r][16][16] (bf16)
 hipError_t launch_coupling_small(const void* Z, const void* S, void* A, int64_t T, int b, int r, hipStream_t s);   // few tokens; canonical S
+
+// where a packed BLAST buffer of the multi-kernel executions holds Vt[b][r][q] and the canonical S[b][b][r]
+void blast_packed_parts(const void* packed, int n_in, int n_out, int b, int r, const void** Vt, const void** Sc);
+
+// O = A + B over n bf16 elements (16-byte aligned, 8 | n)
+hipError_t launch_add(const void* A, const void* B, void* O, int64_t n, hipStream_t s);
 
 // BLAST weight re-layout (bf16): Sp always; Vt (row-major transpose) if non-null; Vf and Uf if non-null
 // the fused stage 1 + coupling kernel walks the contraction index in chunks aligned to this many GLOBAL input

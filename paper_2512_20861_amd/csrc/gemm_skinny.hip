@@ -15,6 +15,11 @@
 // buffers, cross-lane permutes and a general column map per element.
 //
 // The weight fragment is the first MFMA operand: an accumulator lane holds four consecutive output columns of one token.
+//
+// For a handful of tokens the step in front of a product is cheaper inside it than as a launch: every workgroup computes
+// the rows it multiplies (or the slice of them that its batch entry reads) into LDS while its weights are on the way.
+// Sources of those rows (SkinnySource): the product's input itself; the RMS normalisation of a residual stream to which
+// the previous linear's output is added first; the scaled sum of three column slices; the SiLU gate; BLAST's coupling.
 #include "blr_common.h"
 
 namespace blr {
@@ -22,6 +27,7 @@ namespace {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));   // (arrays of HIP's uint4 struct stay in scratch memory)
 
 constexpr int SK_BN = 16;             // weight rows per workgroup
 constexpr int SK_RD = 8;              // k32 steps in flight per wavefront
@@ -47,11 +53,139 @@ __device__ __forceinline__ bf16x8 lds_read_frag(unsigned addr) {   // (reads the
     return v;
 }
 
+__device__ __forceinline__ float silu(float x) { return x / (1.f + __expf(-x)); }
+template <int PERM>
+__device__ __forceinline__ float quad_permute(float v) {                       // (a data-parallel move inside the vector ALU; __shfl_xor goes through LDS)
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), PERM, 0xF, 0xF, true));
+}
+__device__ __forceinline__ void unpack8(u32x4 v, float (&f)[8]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { f[2 * i] = __uint_as_float(v[i] << 16); f[2 * i + 1] = __uint_as_float(v[i] & 0xFFFF0000u); }
+}
+__device__ __forceinline__ u32x4 pack8(const float (&f)[8]) {
+    return u32x4{pack2_bf16(f[0], f[1]), pack2_bf16(f[2], f[3]), pack2_bf16(f[4], f[5]), pack2_bf16(f[6], f[7])};
+}
+
+// Rows [M][K] of batch entry g (coupling: output block s of member g), bf16, row pitch xs bytes, from their source.
+// Every thread of the workgroup takes part; the caller's barrier follows. `red`: 8 M floats of scratch.
+template <int SRC, int NW>
+__device__ __forceinline__ void source_rows(const SkinnySource& q, int M, int K, int g, int s, unsigned char* rows, unsigned xs, float* red) {
+    const int tid = threadIdx.x;
+    if constexpr (SRC == kSrcNorm) {
+        // H' = H + Y rounded to storage, n = H' / rms(H'): the whole row for the sum, the slice [g K, g K + K) for the product
+        const int wave = tid >> 6, k0 = g * K;
+        for (int m = 0; m < M; ++m) {
+            const bf16_t* h = q.a + (int64_t)m * q.d;
+            float ss = 0.f;
+            for (int c = tid * 8; c < q.d; c += NW * 64 * 8) {
+                u32x4 v = *(const u32x4*)(h + c);
+                float f[8];
+                unpack8(v, f);
+                if (q.y) {
+                    float y[8];
+                    unpack8(*(const u32x4*)(q.y + (int64_t)m * q.d + c), y);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) f[i] += y[i];
+                    v = pack8(f);
+                    unpack8(v, f);
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) ss += f[i] * f[i];
+                if (c >= k0 && c < k0 + K) *(u32x4*)(rows + m * xs + (c - k0) * 2) = v;
+                if (q.out && (blockIdx.x | blockIdx.y | blockIdx.z) == 0) *(u32x4*)(q.out + (int64_t)m * q.d + c) = v;   // (a buffer nobody reads in this launch)
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+            if ((tid & 63) == 0) red[m * 8 + wave] = ss;
+        }
+        __syncthreads();
+        for (int it = tid; it < M * (K >> 3); it += NW * 64) {
+            const int m = it / (K >> 3), c = it - m * (K >> 3);
+            float ss = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) ss += red[m * 8 + w];
+            const float scale = rsqrtf(ss / (float)q.d + q.scale);             // scale: eps
+            unsigned char* p = rows + m * xs + c * 16;
+            float f[8];
+            unpack8(*(const u32x4*)p, f);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) f[i] *= scale;
+            *(u32x4*)p = pack8(f);
+        }
+    } else if constexpr (SRC == kSrcSum3 || SRC == kSrcSilu) {
+        // elementwise on column slices of one tensor with rows of ld elements, slices `slice` elements apart;
+        // segmented contraction index as in GemmDesc
+        for (int it = tid; it < M * (K >> 3); it += NW * 64) {
+            const int m = it / (K >> 3), e = (it - m * (K >> 3)) * 8;
+            const int sg = e / q.seg;
+            const bf16_t* p = q.a + (int64_t)m * q.ld + (int64_t)g * q.gs + (int64_t)sg * q.seg_stride + (e - sg * q.seg);
+            float f0[8], f1[8];
+            unpack8(*(const u32x4*)p, f0);
+            unpack8(*(const u32x4*)(p + q.slice), f1);
+            if constexpr (SRC == kSrcSum3) {
+                float f2[8];
+                unpack8(*(const u32x4*)(p + 2 * q.slice), f2);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) f0[i] = (f0[i] + f1[i] + f2[i]) * q.scale;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) f0[i] = silu(f0[i]) * f1[i];
+            }
+            *(u32x4*)(rows + m * xs + e * 2) = pack8(f0);
+        }
+    } else if constexpr (SRC == kSrcCoupling) {
+        // A[t][rho] = sum_j S[s][j][rho] Z[t][j][rho]: four neighbouring lanes take a quarter of the input blocks each, 8 rank indices at a time
+        const int jq = tid & 3;
+        const bf16_t* S = q.y + (int64_t)s * q.b * q.d + g * K;                // S[b][b][d], member g's ranks
+        const bf16_t* Z = q.a + g * K;                                         // Z[t][b][d]
+        for (int c = (tid >> 2) * 8; c < K; c += NW * 16 * 8) {
+            int off[4];
+            u32x4 sv[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int j = jq * 4 + u < q.b ? jq * 4 + u : q.b - 1;
+                off[u] = j * q.d + c;
+                sv[u] = *(const u32x4*)(S + off[u]);
+                if (jq * 4 + u >= q.b) sv[u] = u32x4{0u, 0u, 0u, 0u};
+            }
+#pragma unroll 1
+            for (int m0 = 0; m0 < M; m0 += 2) {          // two tokens' loads in flight
+                u32x4 zv[2][4];
+#pragma unroll
+                for (int v = 0; v < 2; ++v)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) zv[v][u] = *(const u32x4*)(Z + (int64_t)(m0 + v < M ? m0 + v : m0) * q.b * q.d + off[u]);
+#pragma unroll
+                for (int v = 0; v < 2; ++v) {
+                    if (m0 + v >= M) break;              // uniform
+                    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        float fs[8], fz[8];
+                        unpack8(sv[u], fs);
+                        unpack8(zv[v][u], fz);
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) acc[i] = fmaf(fs[i], fz[i], acc[i]);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        acc[i] += quad_permute<0xB1>(acc[i]);          // lane ^ 1
+                        acc[i] += quad_permute<0x4E>(acc[i]);          // lane ^ 2
+                    }
+                    if (jq == 0) *(u32x4*)(rows + (m0 + v) * xs + c * 2) = pack8(acc);
+                }
+            }
+        }
+    }
+}
+
 // MT: 16-token tiles (M <= 16 MT); NW: wavefronts = K splits; TAIL: K is no multiple of 32
-template <int MT, int NW, bool TAIL>
-__global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a) {
+template <int MT, int NW, bool TAIL, int SRC>
+__global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, SkinnySource src) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int SLOT = (1 + MT) * 1024;                // 16 weight rows and 16 MT token rows of 64 bytes
+    constexpr int XL = SRC == kSrcInput ? MT : 0;        // token rows that come as direct loads, per step
+    constexpr int SLOT = (1 + XL) * 1024;                // 16 weight rows and 16 XL token rows of 64 bytes
+    static_assert(SRC == kSrcInput || MT == 1, "computed rows: a handful of tokens");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i0 = blockIdx.x * SK_BN, s = blockIdx.y;
@@ -69,7 +203,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a) {
     const int row = i0 + lrow < a.n ? i0 + lrow : a.n - 1;          // rows past the segment repeat its last one; never stored
     unsigned woff = (unsigned)row * a.b_i, xoff[MT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
+    for (int mt = 0; mt < XL; ++mt) {
         const int m = mt * 16 + lrow, left = a.M - m_base - 1;
         xoff[mt] = (unsigned)(m < left ? m : left) * (unsigned)a.a_rs;
     }
@@ -78,7 +212,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a) {
     int kf = kw;                                        // contraction index under the fetch cursor
     int64_t seg_off = 0;                                // segmented contraction index of A: what to add to it (a step lies in one segment)
     int seg_left = 0x7fffffff;
-    if (a.a_seg) {
+    if (XL && a.a_seg) {
         seg_off = (int64_t)(kw / a.a_seg) * (a.a_seg_stride - a.a_seg);
         seg_left = a.a_seg - kw % a.a_seg;
     }
@@ -88,23 +222,32 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a) {
         __builtin_amdgcn_global_load_lds(BLR_GPTR(B + (woff + kl) * 2u), BLR_LPTR(slot), 16, 0, 0);
         const unsigned char* As = A + seg_off * 2;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int mt = 0; mt < XL; ++mt)
             __builtin_amdgcn_global_load_lds(BLR_GPTR(As + (xoff[mt] + kl) * 2u), BLR_LPTR(slot + (1 + mt) * 1024), 16, 0, 0);
         kf += 32;
         seg_left -= 32;
-        if (seg_left == 0) {
+        if (XL && seg_left == 0) {
             seg_left = a.a_seg;
             seg_off += a.a_seg_stride - a.a_seg;
         }
     };
     const int l16 = lane & 15, kg = lane >> 4;
     const unsigned frag = (unsigned)(uintptr_t)BLR_LPTR(mine) + l16 * 64 + ((kg ^ ((l16 >> 2) & 3)) * 16);
+    // computed rows lie behind the wavefronts' slots
+    const unsigned xs = a.K * 2 + 16;
+    unsigned char* rows = smem + NW * (a.slots * SLOT);
+    const unsigned row_frag = (unsigned)(uintptr_t)BLR_LPTR(rows) + (l16 < a.M ? l16 : a.M - 1) * xs;
+    auto x_frag = [&](int mt, unsigned at, int t) {      // token fragment of step t, whose slot is at
+        if constexpr (SRC == kSrcInput) return lds_read_frag(frag + at + (1 + mt) * 1024);
+        int k = kw + t * 32 + kg * 8;
+        if (TAIL) k = k < a.K ? k : a.K - 8;
+        return lds_read_frag(row_frag + k * 2);
+    };
     f32x4 acc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto multiply = [&](bf16x8 w, const bf16x8 (&x)[MT], int t) {   // (after the wait for both)
         if (TAIL) {
-            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
             if (kw + t * 32 + kg * 8 >= a.K) w = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
         }
 #pragma unroll
@@ -113,14 +256,18 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a) {
 
     int t = 0;
     for (; t < steps && t < a.slots; ++t) fetch(mine + t * SLOT);
+    if constexpr (SRC != kSrcInput) {
+        source_rows<SRC, NW>(src, a.M, a.K, g, s, rows, xs, (float*)(rows + a.M * xs));
+        __syncthreads();
+    }
     t = 0;
     unsigned at = 0;                                    // slot of step t (bytes)
 #pragma unroll 1
     for (; t + SK_RD < steps; ++t) {                    // (only with all SK_RD slots: what is in flight is a constant)
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((1 + MT) * (SK_RD - 1)) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((1 + XL) * (SK_RD - 1)) : "memory");
         bf16x8 w = lds_read_frag(frag + at), x[MT];
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) x[mt] = lds_read_frag(frag + at + (1 + mt) * 1024);
+        for (int mt = 0; mt < MT; ++mt) x[mt] = x_frag(mt, at, t);
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w) :: "memory");
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) asm volatile("" : "+v"(x[mt]));
@@ -135,8 +282,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a) {
         bf16x8 w0 = lds_read_frag(frag + at), w1 = lds_read_frag(frag + at1), x0[MT], x1[MT];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            x0[mt] = lds_read_frag(frag + at + (1 + mt) * 1024);
-            x1[mt] = lds_read_frag(frag + at1 + (1 + mt) * 1024);
+            x0[mt] = x_frag(mt, at, t);
+            x1[mt] = x_frag(mt, at1, t + 1 < steps ? t + 1 : t);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w0), "+v"(w1) :: "memory");
 #pragma unroll
@@ -165,16 +312,20 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a) {
     }
 }
 
-template <int MT, int NW>
-hipError_t launch_skinny(SkinnyArgs& a, dim3 grid, hipStream_t s) {
+template <int MT, int NW, int SRC>
+hipError_t launch_skinny(SkinnyArgs& a, const SkinnySource& src, dim3 grid, hipStream_t s) {
+    constexpr int SLOT = (1 + (SRC == kSrcInput ? MT : 0)) * 1024;
     const int nk = (a.K + 31) / 32, per = (nk + NW - 1) / NW;
     a.kper = per * 32;
     a.slots = per < SK_RD ? per : SK_RD;
-    const int lds = NW * a.slots * (1 + MT) * 1024;
+    const int operands = NW * a.slots * SLOT, sums = NW * MT * 16 * (SK_BN + 4) * 4;
+    int lds = operands;
+    if (SRC != kSrcInput) lds += a.M * (a.K * 2 + 16) + a.M * 8 * 4;
+    if (lds < sums) lds = sums;
     static LdsLimitOnce lds_limit;
-    if (hipError_t e = lds_limit.set({(const void*)gemm_skinny_kernel<MT, NW, false>, (const void*)gemm_skinny_kernel<MT, NW, true>}, NW * SK_RD * (1 + MT) * 1024); e != hipSuccess) return e;
-    if (a.K % 32) hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, true>), grid, dim3(64 * NW), lds, s, a);
-    else hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, false>), grid, dim3(64 * NW), lds, s, a);
+    if (hipError_t e = lds_limit.set({(const void*)gemm_skinny_kernel<MT, NW, false, SRC>, (const void*)gemm_skinny_kernel<MT, NW, true, SRC>}, 160 * 1024); e != hipSuccess) return e;
+    if (a.K % 32) hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, true, SRC>), grid, dim3(64 * NW), lds, s, a, src);
+    else hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, false, SRC>), grid, dim3(64 * NW), lds, s, a, src);
     return hipGetLastError();
 }
 
@@ -195,22 +346,53 @@ bool shape_ok(const GemmDesc& d, int64_t mtiles) {
 
 bool skinny_gemm_supported(const GemmDesc& d) { return d.M <= 32 && shape_ok(d, 1); }
 
-hipError_t launch_gemm_skinny(const GemmDesc& d, hipStream_t s) {
+static SkinnyArgs skinny_args(const GemmDesc& d) {
     SkinnyArgs a{};
-    int n, nseg;
-    segments(d, n, nseg);
+    int nseg;
+    segments(d, a.n, nseg);
     a.A = (const bf16_t*)d.A; a.B = (const bf16_t*)d.B; a.C = (bf16_t*)d.C;
     a.a_gs = d.a_gs; a.a_rs = d.a_rs; a.b_gs = d.b_gs; a.c_gs = d.c_gs; a.c_rs = d.c_rs;
-    a.M = (int)d.M; a.n = n; a.K = d.K;
+    a.M = (int)d.M; a.K = d.K;
     if (d.b_div) { a.b_i = (unsigned)(d.b_mul * d.b_rs); a.b_s = d.b_rs; a.c_i = d.c_lo; a.c_s = d.c_hi; }
     else { a.b_i = (unsigned)d.b_rs; a.b_s = 0; a.c_i = d.c_hi; a.c_s = 0; }
     a.a_seg = d.a_seg; a.a_seg_stride = d.a_seg_stride;
+    a.mtiles = 1;
+    return a;
+}
+
+// eight wavefronts where each still gets two or more steps: twice the bytes in flight of a workgroup and half its steps
+static bool eight_waves(int K) { return K >= 512; }
+
+hipError_t launch_gemm_skinny(const GemmDesc& d, hipStream_t s) {
+    SkinnyArgs a = skinny_args(d);
     const int mt = d.M <= 16 ? 1 : 2;                   // more than 32 tokens: one workgroup per 32-token tile and 16 weight rows
     a.mtiles = (int)((d.M + mt * 16 - 1) / (mt * 16));
-    const dim3 grid((unsigned)((n + SK_BN - 1) / SK_BN), (unsigned)nseg, (unsigned)(d.G * a.mtiles));
-    // eight wavefronts where each still gets two or more steps (K >= 512): twice the bytes in flight of a workgroup and half its steps
-    if (mt == 1) return d.K >= 512 ? launch_skinny<1, 8>(a, grid, s) : launch_skinny<1, 4>(a, grid, s);
-    return launch_skinny<2, 4>(a, grid, s);
+    const dim3 grid((unsigned)((a.n + SK_BN - 1) / SK_BN), (unsigned)(d.b_div ? d.N / d.b_div : 1), (unsigned)(d.G * a.mtiles));
+    if (mt == 2) return launch_skinny<2, 4, kSrcInput>(a, {}, grid, s);
+    return eight_waves(d.K) ? launch_skinny<1, 8, kSrcInput>(a, {}, grid, s) : launch_skinny<1, 4, kSrcInput>(a, {}, grid, s);
+}
+
+bool skinny_source_supported(const GemmDesc& d) {
+    return d.M >= 1 && d.M <= kSourceTokens && mfma_gemm_supported(d) && shape_ok(d, 1) && d.K <= 4096;      // (rows of 8 tokens: 64 KB of LDS behind the weights)
+}
+
+template <int SRC>
+static hipError_t launch_source(const GemmDesc& d, const SkinnySource& src, unsigned grid_y, unsigned grid_z, hipStream_t s) {
+    SkinnyArgs a = skinny_args(d);
+    if (SRC == kSrcCoupling) { a.b_s = d.b_gs; a.c_s = d.c_gs; a.b_gs = d.b_gs * src.b; a.c_gs = d.c_gs * src.b; }   // (output block, member) are grid dimensions
+    const dim3 grid((unsigned)((a.n + SK_BN - 1) / SK_BN), grid_y, grid_z);
+    return eight_waves(d.K) ? launch_skinny<1, 8, SRC>(a, src, grid, s) : launch_skinny<1, 4, SRC>(a, src, grid, s);
+}
+
+hipError_t launch_gemm_skinny_from(int kind, const GemmDesc& d, const SkinnySource& src, hipStream_t s) {
+    const unsigned nseg = d.b_div ? d.N / d.b_div : 1;
+    switch (kind) {
+        case kSrcNorm: return launch_source<kSrcNorm>(d, src, nseg, d.G, s);
+        case kSrcSum3: return launch_source<kSrcSum3>(d, src, nseg, d.G, s);
+        case kSrcSilu: return launch_source<kSrcSilu>(d, src, nseg, d.G, s);
+        case kSrcCoupling: return launch_source<kSrcCoupling>(d, src, src.b, d.G / src.b, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 bool skinny_gemm_tiled_supported(const GemmDesc& d) { return d.M < (1ll << 20) && shape_ok(d, (d.M + 31) / 32); }

@@ -173,6 +173,12 @@ hipError_t run_elementwise_rows(const void* A, const void* B, const void* C, voi
     return hipGetLastError();
 }
 
+}  // namespace
+
+hipError_t launch_add(const void* A, const void* B, void* O, int64_t n, hipStream_t s) { return run_elementwise<bf16_t, 2>(A, B, nullptr, O, n, 1.f, s); }
+
+namespace {
+
 inline blr_status status_of(hipError_t e) { return e == hipSuccess ? BLR_OK : BLR_ERR_LAUNCH; }
 inline bool dims_ok(int64_t T, int d, blr_dtype dt) { return T >= 0 && d > 0 && T < (1ll << 31) && (dt == BLR_F32 || dt == BLR_BF16); }
 

@@ -1,0 +1,52 @@
+"""DeviceChain.forward as one call of the library: the fused launches of a handful of tokens, the step list of more, the
+graph that later passes replay, each against the oracle's chain and against the step-by-step call list."""
+import numpy as np
+import pytest
+
+import blr_inputs as bi
+import oracle
+from oracle import chain as oc
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+PARAMS = {"monarch": dict(nblocks=4, r_square=64, r_mlp=128), "blast": dict(b=4, r_square=136, r_mlp=72)}
+
+
+@pytest.mark.parametrize("op", ["monarch", "blast"])
+@pytest.mark.parametrize("T", [1, 2, 4, 5, 33])
+def test_native_chain(op, T):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    from paper_2512_20861_amd.chain import DeviceChain
+    layers = bi.chain_layers(op, n_layers=2, hidden=512, mlp=768, params=PARAMS[op], dtype="bf16")
+    x0, x1 = bi.activations(T, 512, "bf16"), bi.activations(T, 512, "bf16", seed=99)
+    lin = (lambda x, f: oracle.monarch_forward(x, f.R.f64, f.L.f64)) if op == "monarch" else (lambda x, f: oracle.blast_forward(x, f.U.f64, f.S.f64, f.V.f64))
+    chain = DeviceChain(layers, T, eps=oc.EPS)
+    assert chain.grouped and chain._native
+    refs = [oc.chain_forward(x.f64, layers, lin) for x in (x0, x1)]
+    steps = gu.to_f64(chain.forward(gu.to_dev(x0), record=True)[0])
+    first = []
+    for n in range(5):                                   # separate launches, then the graph; other work in between
+        for x, ref, keep in ((x0, refs[0], first), (x1, refs[1], None)):
+            got = chain.forward(gu.to_dev(x)).clone()
+            torch.cuda.synchronize()
+            # two bf16 implementations of a 2-layer chain: the bound of the chain tests
+            assert gu.rel_err(gu.to_f64(got), ref) <= 2e-2
+            if keep is not None:
+                keep.append(got)
+    assert all(torch.equal(f, first[0]) for f in first)
+    assert gu.rel_err(gu.to_f64(first[0]), steps) <= 2e-2
+    # a stream that is being captured takes the launches themselves
+    side = torch.cuda.Stream()
+    xd = gu.to_dev(x0)
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=side):
+        chain.forward(xd)
+    for _ in range(3):
+        chain.h.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(chain.h, first[0])
