@@ -468,4 +468,5 @@ def chain_forward(handle, stream=None):
 
 
 def chain_destroy(handle):
-    lib().blr_chain_destroy(handle)
+    if _lib is not None:
+        _lib.blr_chain_destroy(handle)

@@ -194,7 +194,7 @@ class DeviceChain:
         return B.chain_create(desc, layers, buffers) if same else None
 
     def __del__(self):
-        if getattr(self, "_native", None):
+        if getattr(self, "_native", None) and B is not None and B.chain_destroy is not None:   # (at interpreter exit the module may be gone)
             B.chain_destroy(self._native)
             self._native = None
 

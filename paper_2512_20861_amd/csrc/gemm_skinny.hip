@@ -179,16 +179,18 @@ __device__ __forceinline__ void source_rows(const SkinnySource& q, int M, int K,
     }
 }
 
-// MT: 16-token tiles (M <= 16 MT); NW: wavefronts = K splits; TAIL: K is no multiple of 32
-template <int MT, int NW, bool TAIL, int SRC>
+// MT: 16-token tiles (M <= 16 MT); NW: wavefronts; TAIL: K is no multiple of 32
+// ROWS: every wavefront owns 16 weight rows and the whole contraction index instead of a part of it (computed rows only:
+// the rows serve 16 NW outputs then, and there are no partial sums to add)
+template <int MT, int NW, bool TAIL, int SRC, bool ROWS>
 __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, SkinnySource src) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int XL = SRC == kSrcInput ? MT : 0;        // token rows that come as direct loads, per step
     constexpr int SLOT = (1 + XL) * 1024;                // 16 weight rows and 16 XL token rows of 64 bytes
-    static_assert(SRC == kSrcInput || MT == 1, "computed rows: a handful of tokens");
+    static_assert(SRC == kSrcInput ? !ROWS : MT == 1, "computed rows: a handful of tokens");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int i0 = blockIdx.x * SK_BN, s = blockIdx.y;
+    const int i0 = (ROWS ? blockIdx.x * NW + wave : blockIdx.x) * SK_BN, s = blockIdx.y;
     int g = blockIdx.z, m_base = 0;
     if (a.mtiles > 1) {
         m_base = (g % a.mtiles) * (MT * 16);
@@ -197,7 +199,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, Skin
     // A direct load fills 16 rows of 64 bytes: lane l brings the piece of slot l % 4 of row l / 4. The pieces are
     // XOR-swizzled by the row so that the 16 rows a fragment read serves per clock cover all banks.
     const int lrow = lane >> 2, piece = (lane & 3) ^ ((lrow >> 2) & 3);
-    const int kw = wave * a.kper;
+    const int kw = ROWS ? 0 : wave * a.kper;
     const unsigned char* B = (const unsigned char*)(a.B + g * a.b_gs + s * a.b_s);
     const unsigned char* A = (const unsigned char*)(a.A + g * a.a_gs + m_base * a.a_rs);
     const int row = i0 + lrow < a.n ? i0 + lrow : a.n - 1;          // rows past the segment repeat its last one; never stored
@@ -293,6 +295,15 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, Skin
         t += 2;
         at = at1 == (unsigned)(a.slots - 1) * SLOT ? 0 : at1 + SLOT;
     }
+    if constexpr (ROWS) {                               // acc[e]: token l16, column 4*kg + e
+        if (l16 < a.M)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int c = i0 + 4 * kg + e;
+                if (c < a.n) a.C[l16 * a.c_rs + g * a.c_gs + s * a.c_s + c * a.c_i] = float_to_bf16(acc[0][e]);
+            }
+        return;
+    }
     __syncthreads();                                    // every wavefront is past its operands: the partial sums take their place
 
     // acc[mt][e]: token mt*16 + l16, column 4*kg + e
@@ -312,20 +323,20 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, Skin
     }
 }
 
-template <int MT, int NW, int SRC>
+template <int MT, int NW, int SRC, bool ROWS = false>
 hipError_t launch_skinny(SkinnyArgs& a, const SkinnySource& src, dim3 grid, hipStream_t s) {
     constexpr int SLOT = (1 + (SRC == kSrcInput ? MT : 0)) * 1024;
-    const int nk = (a.K + 31) / 32, per = (nk + NW - 1) / NW;
+    const int nk = (a.K + 31) / 32, per = ROWS ? nk : (nk + NW - 1) / NW;
     a.kper = per * 32;
     a.slots = per < SK_RD ? per : SK_RD;
-    const int operands = NW * a.slots * SLOT, sums = NW * MT * 16 * (SK_BN + 4) * 4;
+    const int operands = NW * a.slots * SLOT, sums = ROWS ? 0 : NW * MT * 16 * (SK_BN + 4) * 4;
     int lds = operands;
     if (SRC != kSrcInput) lds += a.M * (a.K * 2 + 16) + a.M * 8 * 4;
     if (lds < sums) lds = sums;
     static LdsLimitOnce lds_limit;
-    if (hipError_t e = lds_limit.set({(const void*)gemm_skinny_kernel<MT, NW, false, SRC>, (const void*)gemm_skinny_kernel<MT, NW, true, SRC>}, 160 * 1024); e != hipSuccess) return e;
-    if (a.K % 32) hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, true, SRC>), grid, dim3(64 * NW), lds, s, a, src);
-    else hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, false, SRC>), grid, dim3(64 * NW), lds, s, a, src);
+    if (hipError_t e = lds_limit.set({(const void*)gemm_skinny_kernel<MT, NW, false, SRC, ROWS>, (const void*)gemm_skinny_kernel<MT, NW, true, SRC, ROWS>}, 160 * 1024); e != hipSuccess) return e;
+    if (a.K % 32) hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, true, SRC, ROWS>), grid, dim3(64 * NW), lds, s, a, src);
+    else hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, false, SRC, ROWS>), grid, dim3(64 * NW), lds, s, a, src);
     return hipGetLastError();
 }
 
@@ -376,11 +387,16 @@ bool skinny_source_supported(const GemmDesc& d) {
     return d.M >= 1 && d.M <= kSourceTokens && mfma_gemm_supported(d) && shape_ok(d, 1) && d.K <= 4096;      // (rows of 8 tokens: 64 KB of LDS behind the weights)
 }
 
+// From this many 16-row tiles on a wavefront owns a tile: there are workgroups enough, and the source is computed a quarter as often.
+constexpr int64_t kRowsTiles = 768;
+
 template <int SRC>
 static hipError_t launch_source(const GemmDesc& d, const SkinnySource& src, unsigned grid_y, unsigned grid_z, hipStream_t s) {
     SkinnyArgs a = skinny_args(d);
     if (SRC == kSrcCoupling) { a.b_s = d.b_gs; a.c_s = d.c_gs; a.b_gs = d.b_gs * src.b; a.c_gs = d.c_gs * src.b; }   // (output block, member) are grid dimensions
-    const dim3 grid((unsigned)((a.n + SK_BN - 1) / SK_BN), grid_y, grid_z);
+    const unsigned tiles = (unsigned)((a.n + SK_BN - 1) / SK_BN);
+    if ((int64_t)tiles * grid_y * grid_z >= kRowsTiles) return launch_skinny<1, 4, SRC, true>(a, src, dim3((tiles + 3) / 4, grid_y, grid_z), s);
+    const dim3 grid(tiles, grid_y, grid_z);
     return eight_waves(d.K) ? launch_skinny<1, 8, SRC>(a, src, grid, s) : launch_skinny<1, 4, SRC>(a, src, grid, s);
 }
 
