@@ -66,7 +66,7 @@ typedef void* blr_stream;      /* a hipStream_t */
  * (a) stage 1 and the coupling fused in one kernel (Z stays on chip; the paper's optimisation 4 with
  * the coupling on the matrix cores) followed by the stage-3 GEMM, and (b) three kernels over
  * cache-resident token chunks (the paper's optimisation 5). By default the library picks (a) when
- * the call has enough 128-token x 64-rank tiles to fill the chip and (b) otherwise; these flags
+ * the input blocks are short and the call's 128-token x 64-rank tiles fill the chip, (b) otherwise; these flags
  * force one of them (mutually exclusive) so that tests and the benchmark can run both. */
 #define BLR_BLAST_FUSED_STAGE12     0x800u
 #define BLR_BLAST_THREE_KERNELS     0x1000u

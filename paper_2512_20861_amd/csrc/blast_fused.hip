@@ -164,15 +164,16 @@ __device__ __forceinline__ void store_a_tile(const unsigned char* Zs, bf16_t* __
     }
 }
 
-// Stand-alone coupling (the middle kernel of the three-kernel path): Z[T][b][r] -> A[T][b][r].
+// Stand-alone coupling (the middle kernel of the three-kernel path): Z[T][b][r] -> A[T][b][r]; A may be Z (a workgroup
+// reads its tile of all blocks before it writes it).
 // The Z tile is read with full-line loads (8 lanes per 128-byte row segment) and transposed on its
 // way into LDS; blocks j and j+1 travel together so that every LDS write is a bf16 pair.
-// TNT tokens per workgroup: 64, or 32 or 16 when larger tiles would leave most of the chip idle.
+// TNT tokens per workgroup: 16 or 32.
 // Z8: Z holds 8-bit floats (E4M3, written by the stage-1 product of the quantised-intermediate execution),
 // one byte per element in the same [T][b][r] order; they are widened to bf16 (exactly) on their way into LDS.
 template <int TNT, bool Z8>
 __global__ __launch_bounds__(512)
-void blast_coupling_kernel(const bf16_t* __restrict__ Z, const bf16_t* __restrict__ Sp, bf16_t* __restrict__ A,
+void blast_coupling_kernel(const bf16_t* Z, const bf16_t* __restrict__ Sp, bf16_t* A,
                            int64_t T, int b, int r, int tiles_r, int nblk) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     unsigned char* Zs = smem;
@@ -510,13 +511,14 @@ static hipError_t launch_coupling_inst(const void* Z, const void* Sp, void* A, i
 }
 
 hipError_t launch_blast_coupling(const void* Z, const void* Sp, void* A, int64_t T, int b, int r, hipStream_t s, bool z_fp8) {
-    // 64-token tiles unless they would leave most compute units without a workgroup
-    const int64_t tiles64 = ((T + 63) / 64) * ((r + TR - 1) / TR);
-    if (z_fp8) return tiles64 < 200 ? launch_coupling_inst<32, true>(Z, Sp, A, T, b, r, s) : launch_coupling_inst<64, true>(Z, Sp, A, T, b, r, s);
-    // ... and 16-token tiles for the fewest tokens (4096 x 4096, r = 640 at 192 ... 384 tokens: 0.5 ... 1 us of the 20 ... 26 us call)
-    if (tiles64 <= 64) return launch_coupling_inst<16, false>(Z, Sp, A, T, b, r, s);
-    if (tiles64 < 200) return launch_coupling_inst<32, false>(Z, Sp, A, T, b, r, s);
-    return launch_coupling_inst<64, false>(Z, Sp, A, T, b, r, s);
+    // A workgroup loads its tile, couples it and stores it, one after the other: several on a compute unit overlap these
+    // phases, so small tiles are faster at every size (r = 1024 at 2048 tokens 25.7 -> 20.7 us, 6.5 TB/s; r = 640 20.6 -> 14.7;
+    // 64-token tiles hold one workgroup per compute unit). Between one and a few rounds of 16-token tiles, 32 tokens are
+    // level or 5 % ahead.
+    const int64_t tiles16 = ((T + 15) / 16) * ((r + TR - 1) / TR);
+    if (z_fp8) return launch_coupling_inst<32, true>(Z, Sp, A, T, b, r, s);
+    if (tiles16 <= 256 || tiles16 >= 600) return launch_coupling_inst<16, false>(Z, Sp, A, T, b, r, s);
+    return launch_coupling_inst<32, false>(Z, Sp, A, T, b, r, s);
 }
 
 namespace {

@@ -73,18 +73,36 @@ struct BlastPlan {
     size_t off_A, off_Z, off_pack, total;
 };
 
-// The three-kernel path (stage-1 GEMM, MFMA coupling, stage-3 GEMM) walks the tokens in chunks whose
-// two intermediates (Z and A, b*r bf16 per token each) together stay well inside the 256 MB
-// memory-side cache, so that they are produced and consumed without a round trip to HBM.
+// The three-kernel path (stage-1 GEMM, MFMA coupling, stage-3 GEMM) walks the tokens in chunks whose intermediate (b*r bf16
+// per token; the coupling turns Z into A in place, every workgroup reads its tile of all blocks before it writes it) stays
+// well inside the 256 MB memory-side cache, so that it is produced and consumed without a round trip to HBM. The workspace
+// holds two parts of kChunkBytes: one buffer of both for the 16-bit Z, Z and A side by side for the 8-bit one.
 constexpr size_t kChunkBytes = 48u << 20;
-// The fused stage 1 + coupling kernel runs one workgroup per compute unit; below a number of 128-token
-// tiles it leaves too much of the chip idle and the three-kernel path (finer tiles) is faster. What the
-// fused kernel saves, the round trip of Z, grows with b r per token; what it pays, a stage 1 on tiles
-// of half the arithmetic intensity of the GEMM's, grows with n_in r: the longer the input block
-// q = n_in / b, the more tiles it takes to come out ahead (measured at q = 64 ... 688, r = 256 ... 1024).
-inline int64_t fused_min_tiles(int n_in, int b) {
+// Tokens per chunk: whole rounds of the 256 x 256 tiles of stage 1 as far as they fit. 11008 -> 4096, r = 1024 at 8192
+// tokens: 472 us in chunks of 1536 tokens (1.5 rounds), 421 in chunks of 2048 (2 rounds).
+int64_t blast_chunk_tokens(int64_t T, int b, int r, int64_t most) {
+    if (T <= most) return T;
+    const int64_t per_row = (int64_t)b * ((r + 255) / 256);           // tiles of 256 tokens
+    auto rounds = [&](int64_t tokens) { return (((tokens + 255) / 256) * per_row + 255) / 256; };
+    int64_t best = most, best_cost = 0;
+    for (int64_t c = 256; c <= most; c += 256) {
+        const int64_t n = T / c, rest = T % c;
+        const int64_t cost = 4 * (n * rounds(c) + (rest ? rounds(rest) : 0)) + (n + (rest != 0));   // (a chunk's fixed cost: a quarter of a round)
+        if (!best_cost || cost < best_cost) { best = c; best_cost = cost; }
+    }
+    return best;
+}
+// The fused stage 1 + coupling kernel runs one workgroup per compute unit on 128-token x 64-rank tiles. What it saves, the
+// round trip of Z, grows with b r per token; what it pays, a stage 1 on tiles of half the arithmetic intensity of the
+// GEMM's, grows with n_in r. Input blocks longer than 256 columns always lose to three kernels (11008 -> 4096, r = 1024 at
+// 2048 / 8192 tokens 124 / 502 against 101 / 402 us; 8192 -> 2048, r = 768: 83 / 291 against 75 / 247). Up to 256 the fused
+// kernel is ahead or level while its rounds of workgroups are full (r = 1024, 4096 x 4096 at 4096 tokens 147 against 164;
+// 2048 -> 8192, r = 512 at 8192 tokens 170 against 188) and behind with a last round half empty (r = 640 at 4096 / 8192
+// tokens, 1.25 / 2.5 rounds: 115 / 214 against 100 / 199); with too few tiles it leaves too much of the chip idle.
+bool fused_pays(int64_t T, int n_in, int b, int r) {
     const int q = n_in / b;
-    return q <= 128 ? 80 : q <= 256 ? 120 : 224;
+    const int64_t tiles = blast_fused_tiles(T, r), rounds = (tiles + 255) / 256;
+    return q <= 256 && tiles >= (q <= 128 ? 80 : 120) && (rounds == 1 || tiles * 10 >= rounds * 256 * 9);
 }
 // Up to this many tokens the coupling runs as one thread per 8 outputs; from there on the MFMA coupling kernel on its
 // 16-token tiles is ahead (BLAST 4096 x 4096, r = 640: 13.6 against 14.4 us at 33 tokens, 16.5 against 15.9 at 64,
@@ -131,15 +149,23 @@ BlastPlan blast_plan(int64_t T, int n_in, int n_out, int b, int r, blr_dtype dt,
         else if (blast_full_fusion_supported(T, n_in, n_out, b, r)) pl.path = BlastPlan::MFMA_FULL;
         else if (blast_takes_narrow(T, n_in, n_out, b, r, flags)) pl.path = BlastPlan::MFMA_NARROW;
         else if (!(flags & BLR_BLAST_THREE_KERNELS) && blast_fused_supported(T, n_in, b, r) &&
-                 ((flags & BLR_BLAST_FUSED_STAGE12) || blast_fused_tiles(T, r) >= fused_min_tiles(n_in, b))) pl.path = BlastPlan::MFMA_STAGE12;
+                 ((flags & BLR_BLAST_FUSED_STAGE12) || fused_pays(T, n_in, b, r))) pl.path = BlastPlan::MFMA_STAGE12;
         else pl.path = BlastPlan::MFMA_THREE;
         if (pl.path == BlastPlan::MFMA_STAGE12) { pl.off_A = off; off += align_up((size_t)T * per_token); }
         if (pl.path == BlastPlan::MFMA_THREE) {
             int64_t c = (int64_t)(kChunkBytes / per_token) / 256 * 256;
             if (c < 256) c = 256;
-            if (c < T) pl.chunk = c;
-            pl.off_A = off; off += align_up((size_t)pl.chunk * per_token);
-            pl.off_Z = off; off += align_up((size_t)pl.chunk * per_token / ((flags & BLR_BLAST_Z_FP8) ? 2 : 1));   // one byte per element of an 8-bit Z
+            const int64_t part = c < T ? c : T;         // tokens of one of the two parts
+            pl.off_A = off; off += align_up((size_t)part * per_token);
+            if (flags & BLR_BLAST_Z_FP8) {
+                pl.chunk = part;
+                pl.off_Z = off; off += align_up((size_t)part * per_token / 2);                  // one byte per element of an 8-bit Z
+            } else {
+                pl.chunk = blast_chunk_tokens(T, b, r, 2 * c);
+                // (the coupling of the fewest tokens does not work in place)
+                pl.off_Z = T > part ? pl.off_A : off;
+                off += align_up((size_t)part * per_token);
+            }
         }
         if (!packed) { pl.off_pack = off; off += pack_layout(n_in, n_out, b, r).total; }
     }
@@ -394,17 +420,26 @@ static blr_status blast_run(const void* X, const void* U, const void* S, const v
     // three kernels per chunk of tokens: stage-1 GEMM -> Z, MFMA coupling Z -> A, stage-3 GEMM
     s1.B = Vt; s1.b_gs = (int64_t)q * r; s1.b_rs = q; s1.b_ks = 1; s1.b_div = 0;
     const bool z8 = flags & BLR_BLAST_Z_FP8;
+    // Input blocks that are no whole number of cache lines (q = 688): the operand rows of a step straddle lines and every
+    // request is two. The large tiles then read the blocks in 64-column chunks of the whole input row against the
+    // chunk-aligned copy of Vt (stage 1 of 11008 -> 4096, r = 1024 at 2048 tokens: 65 -> 58 us).
+    const bool aligned_blocks = q % 64 && n_in % 64 == 0 && blast_chunk(n_in, b) == 64;
     s1.c_fp8 = z8 ? 1 : 0;                              // Z[t][j][rho] as bytes: the same strides, counted in bytes
     for (int64_t c0 = 0; c0 < T; c0 += pl.chunk) {
         const int64_t tc = T - c0 < pl.chunk ? T - c0 : pl.chunk;
         if (first) {
             s1.A = (const unsigned char*)X + (size_t)c0 * n_in * 2;
             s1.M = tc;
-            blr_status st = run_gemm(s1, dt, true, s);
+            GemmDesc s1t = s1;
+            if (aligned_blocks && gemm_whole_line_tiles(s1)) {
+                s1t.k_align = 1;
+                s1t.B = pack + pk.off_Va; s1t.b_rs = blast_va_row(q, 64); s1t.b_gs = (int64_t)r * s1t.b_rs;
+            }
+            blr_status st = run_gemm(s1t, dt, true, s);
             if (st != BLR_OK) return st;
             // few tokens: one thread per 8 outputs
             st = from_hip(z8 ? launch_blast_coupling(Zws, Sp, Aws, tc, b, r, s, true)
-                          : tc <= kSmallCouplingTokens ? launch_coupling_small(Zws, pack + pk.off_Sc, Aws, tc, b, r, s)
+                          : T <= kSmallCouplingTokens ? launch_coupling_small(Zws, pack + pk.off_Sc, Aws, tc, b, r, s)
                                                        : launch_blast_coupling(Zws, Sp, Aws, tc, b, r, s));
             if (st != BLR_OK) return st;
         }

@@ -95,6 +95,10 @@ struct GemmDesc {
     const void* B; int64_t b_gs; int64_t b_rs; int64_t b_ks; int b_div; int b_mul;
     void* C; int64_t c_rs; int64_t c_gs; int c_div; int64_t c_hi; int64_t c_lo;
     int64_t M; int N; int K; int G;
+    // k_align: the batch entries' windows [g K, (g + 1) K) of A's rows are read in whole steps of 64 elements, i.e. from the multiple of 64
+    // at or below their start to the one at or above their end (a_gs is not used; a_rs is a multiple of 64), against rows of B that hold zeros
+    // where the window is a neighbour's (blast_chunk's Va). For tiles of gemm_whole_line_tiles only.
+    int k_align;
     float* split_scratch; size_t split_scratch_bytes;   // optional: room for fp32 partial tiles of a split contraction
     int c_fp8;                         // C is stored as 8-bit floats (E4M3, round to nearest even, clamped to +-448): one byte per
                                        // element, strides and offsets of C then count bytes; tile kernels of launch_gemm_mfma only
@@ -124,6 +128,8 @@ hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s);
 size_t gemm_split_scratch_bytes(int64_t M, int N, int K, int G);
 // can C of this product be written as 8-bit floats (16 consecutive columns = 16 contiguous, aligned bytes)?
 bool gemm_fp8_store_supported(const GemmDesc& d);
+// does this product run on the 64-deep tiles that take k_align?
+bool gemm_whole_line_tiles(const GemmDesc& d);
 // few tokens (M <= 32): weight-streaming kernel, split-K inside the workgroup; same alignment contract
 bool skinny_gemm_supported(const GemmDesc& d);
 hipError_t launch_gemm_skinny(const GemmDesc& d, hipStream_t s);

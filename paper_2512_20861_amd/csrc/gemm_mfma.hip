@@ -483,9 +483,15 @@ __global__ __launch_bounds__(512) void gemm_wide_kernel(GemmDesc d, int tiles_m,
     workgroup_tile(d, tiles_m, tiles_n, order, g, tile_m, tile_n);
     const int64_t m0 = (int64_t)tile_m * BM;
     const int n0 = tile_n * BN;
-    const unsigned char* Abase = (const unsigned char*)((const bf16_t*)d.A + (int64_t)g * d.a_gs + m0 * d.a_rs);
+    int nk = (d.K + C::BK - 1) / C::BK;
+    int64_t a_first = (int64_t)g * d.a_gs;              // first contraction index of this batch entry in A's rows
+    if (C::BK == 64 && d.k_align) {
+        const int c0 = (g * d.K) >> 6;
+        nk = (((g + 1) * d.K + 63) >> 6) - c0;
+        a_first = (int64_t)c0 * 64;
+    }
+    const unsigned char* Abase = (const unsigned char*)((const bf16_t*)d.A + a_first + m0 * d.a_rs);
     const unsigned char* Bbase = (const unsigned char*)((const bf16_t*)d.B + (int64_t)g * d.b_gs);
-    const int nk = (d.K + C::BK - 1) / C::BK;
     unsigned off[C::LPW];
     bool bad[C::LPW];
     deep_load_offsets<C, BM, TAIL>(d, wave, lane, m0, n0, nk, off, bad);
@@ -627,9 +633,15 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_line_kernel(GemmDesc d, i
     workgroup_tile(d, tiles_m, tiles_n, order, g, tile_m, tile_n);
     const int64_t m0 = (int64_t)tile_m * BM;
     const int n0 = tile_n * BN;
-    const unsigned char* Abase = (const unsigned char*)((const bf16_t*)d.A + (int64_t)g * d.a_gs + m0 * d.a_rs);
+    int nk = (d.K + C::BK - 1) / C::BK;
+    int64_t a_first = (int64_t)g * d.a_gs;              // first contraction index of this batch entry in A's rows
+    if (C::BK == 64 && d.k_align) {
+        const int c0 = (g * d.K) >> 6;
+        nk = (((g + 1) * d.K + 63) >> 6) - c0;
+        a_first = (int64_t)c0 * 64;
+    }
+    const unsigned char* Abase = (const unsigned char*)((const bf16_t*)d.A + a_first + m0 * d.a_rs);
     const unsigned char* Bbase = (const unsigned char*)((const bf16_t*)d.B + (int64_t)g * d.b_gs);
-    const int nk = (d.K + C::BK - 1) / C::BK;
     unsigned off[C::LPW];
     bool bad[C::LPW];
     deep_load_offsets<C, BM, TAIL>(d, wave, lane, m0, n0, nk, off, bad);
@@ -886,7 +898,7 @@ hipError_t launch_wide(const GemmDesc& d, hipStream_t s) {
     const bool vec = c_map_vectorizes(d);
     dim3 grid((unsigned)((int64_t)tiles_m * tiles_n * d.G), 1u, 1u);
     const int order = launch_tile_order(d, vec);
-    if (d.K % 64)
+    if (d.K % 64 && !d.k_align)
         hipLaunchKernelGGL((gemm_wide_kernel<true>), grid, dim3(C::THREADS), C::LDS_BYTES, s, d, tiles_m, tiles_n, vec ? 1 : 0, order);
     else
         hipLaunchKernelGGL((gemm_wide_kernel<false>), grid, dim3(C::THREADS), C::LDS_BYTES, s, d, tiles_m, tiles_n, vec ? 1 : 0, order);
@@ -904,7 +916,7 @@ hipError_t launch_line(const GemmDesc& d, hipStream_t s) {
     const bool vec = c_map_vectorizes(d);
     dim3 grid((unsigned)((int64_t)tiles_m * tiles_n * d.G), 1u, 1u);
     const int order = launch_tile_order(d, vec);
-    if (d.K % BK)
+    if (d.K % BK && !d.k_align)
         hipLaunchKernelGGL((gemm_line_kernel<BM, BN, WGM, WGN, BK, NS, true>), grid, dim3(C::THREADS), C::LDS_BYTES, s, d, tiles_m, tiles_n, vec ? 1 : 0, order);
     else
         hipLaunchKernelGGL((gemm_line_kernel<BM, BN, WGM, WGN, BK, NS, false>), grid, dim3(C::THREADS), C::LDS_BYTES, s, d, tiles_m, tiles_n, vec ? 1 : 0, order);
@@ -943,6 +955,10 @@ static int64_t compute_units() {
         return cus;
     }();
     return n;
+}
+
+bool gemm_whole_line_tiles(const GemmDesc& d) {
+    return d.M > 64 && d.N > 64 && d.K >= 128 && d.a_seg == 0 && (int64_t)((d.M + 127) / 128) * ((d.N + 127) / 128) * d.G >= 160;
 }
 
 hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s) {
