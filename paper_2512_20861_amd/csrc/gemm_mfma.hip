@@ -23,6 +23,7 @@ namespace {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 // Tile and batch index of this workgroup. The grid is one-dimensional over all tiles of all batches;
 // workgroup ids are remapped so that each XCD owns a contiguous range of logical ids. Three orders:
@@ -68,6 +69,12 @@ __device__ inline void workgroup_tile(const GemmDesc& d, int tiles_m, int tiles_
     tile_n = in_group / gm;
 }
 
+constexpr int batch_of(int n, int most) {                // largest divisor of n up to `most`
+    int b = most < n ? most : n;
+    while (n % b) --b;
+    return b;
+}
+
 // Epilogue: accumulators -> bf16 C tile in LDS -> global memory. With the weight fragment as first
 // MFMA operand, accumulator element e of tile (i, j) is output column j*32 + 8*(e/4) + 4*(lane/32) + e%4
 // of token i*32 + lane%32: 8-byte LDS writes, then 16-byte row-contiguous stores (or element-wise
@@ -96,50 +103,58 @@ __device__ __forceinline__ void store_c_tile(const GemmDesc& d, const f32x16 (&a
     // The sweeps go in batches: all LDS reads of a batch are issued, then its stores, so that the LDS
     // latency is paid once per batch and not once per store.
     bf16_t* Cp = (bf16_t*)d.C;
+    // (tiles whose width is no power of two go out in parts of 64 columns)
+    constexpr int BNP = (BN & (BN - 1)) == 0 ? BN : BN % 64 == 0 ? 64 : 32;
     if (cvec) {
         // groups of 8 consecutive columns map to 8 consecutive, 16-byte aligned elements of C
-        constexpr int CPRC = BN / 8;
-        static_assert(THREADS % CPRC == 0, "a thread keeps its column group");
-        constexpr int RPS = THREADS / CPRC, SWEEPS = BM / RPS, UB = SWEEPS < 8 ? SWEEPS : 8;
+        constexpr int CPRC = BNP / 8;
+        static_assert(THREADS % CPRC == 0 && BN % BNP == 0, "a thread keeps its column group");
+        constexpr int RPS = THREADS / CPRC, SWEEPS = BM / RPS, UB = batch_of(SWEEPS, 8);
         static_assert(BM % RPS == 0 && SWEEPS % UB == 0, "whole sweeps, whole batches");
         const int cc = tid % CPRC, row0 = tid / CPRC;
-        const int n = n0 + cc * 8;
-        if (n < d.N) {
-            const int64_t col = (int64_t)g * d.c_gs + (int64_t)(n / d.c_div) * d.c_hi + (int64_t)(n % d.c_div) * d.c_lo;
-            const unsigned char* src = Cs + row0 * CSTR + cc * 16;
-            bf16_t* dst = Cp + (m0 + row0) * d.c_rs + col;
-            const int64_t rows_left = d.M - m0 - row0;   // rows of this thread's first sweep and below that exist
 #pragma unroll
-            for (int s0 = 0; s0 < SWEEPS; s0 += UB) {
-                u32x4 v[UB];                            // (a native vector type: arrays of HIP's uint4 struct stay in scratch memory)
+        for (int part = 0; part < BN / BNP; ++part) {
+            const int n = n0 + part * BNP + cc * 8;
+            if (n < d.N) {
+                const int64_t col = (int64_t)g * d.c_gs + (int64_t)(n / d.c_div) * d.c_hi + (int64_t)(n % d.c_div) * d.c_lo;
+                const unsigned char* src = Cs + row0 * CSTR + part * BNP * 2 + cc * 16;
+                bf16_t* dst = Cp + (m0 + row0) * d.c_rs + col;
+                const int64_t rows_left = d.M - m0 - row0;   // rows of this thread's first sweep and below that exist
 #pragma unroll
-                for (int u = 0; u < UB; ++u) v[u] = *(const u32x4*)(src + (s0 + u) * (RPS * CSTR));
-                __builtin_amdgcn_sched_barrier(0);
+                for (int s0 = 0; s0 < SWEEPS; s0 += UB) {
+                    u32x4 v[UB];                            // (a native vector type: arrays of HIP's uint4 struct stay in scratch memory)
 #pragma unroll
-                for (int u = 0; u < UB; ++u)
-                    if ((int64_t)(s0 + u) * RPS < rows_left) *(u32x4*)(dst + (int64_t)(s0 + u) * RPS * d.c_rs) = v[u];
+                    for (int u = 0; u < UB; ++u) v[u] = *(const u32x4*)(src + (s0 + u) * (RPS * CSTR));
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int u = 0; u < UB; ++u)
+                        if ((int64_t)(s0 + u) * RPS < rows_left) *(u32x4*)(dst + (int64_t)(s0 + u) * RPS * d.c_rs) = v[u];
+                }
             }
         }
     } else {
-        static_assert(THREADS % BN == 0, "a thread keeps its column");
-        constexpr int RPS = THREADS / BN, SWEEPS = BM / RPS, UB = SWEEPS < 16 ? SWEEPS : 16;
+        static_assert(THREADS % BNP == 0, "a thread keeps its column");
+        constexpr int RPS = THREADS / BNP, SWEEPS = BM / RPS, UB = batch_of(SWEEPS, 16);
         static_assert(BM % RPS == 0 && SWEEPS % UB == 0, "whole sweeps, whole batches");
-        const int nn = tid % BN, row0 = tid / BN;
-        const int n = n0 + nn;
-        if (n < d.N) {
-            const int64_t col = (int64_t)g * d.c_gs + (int64_t)(n / d.c_div) * d.c_hi + (int64_t)(n % d.c_div) * d.c_lo;
-            const unsigned char* src = Cs + row0 * CSTR + nn * 2;
-            bf16_t* dst = Cp + (m0 + row0) * d.c_rs + col;
-            const int64_t rows_left = d.M - m0 - row0;
+        const int nn = tid % BNP, row0 = tid / BNP;
 #pragma unroll
-            for (int s0 = 0; s0 < SWEEPS; s0 += UB) {
-                bf16_t v[UB];
+        for (int part = 0; part < BN / BNP; ++part) {
+            const int n = n0 + part * BNP + nn;
+            if (n < d.N) {
+                const int64_t col = (int64_t)g * d.c_gs + (int64_t)(n / d.c_div) * d.c_hi + (int64_t)(n % d.c_div) * d.c_lo;
+                const unsigned char* src = Cs + row0 * CSTR + (part * BNP + nn) * 2;
+                bf16_t* dst = Cp + (m0 + row0) * d.c_rs + col;
+                const int64_t rows_left = d.M - m0 - row0;
 #pragma unroll
-                for (int u = 0; u < UB; ++u) v[u] = *(const bf16_t*)(src + (s0 + u) * (RPS * CSTR));
-                __builtin_amdgcn_sched_barrier(0);
+                for (int s0 = 0; s0 < SWEEPS; s0 += UB) {
+                    bf16_t v[UB];
 #pragma unroll
-                for (int u = 0; u < UB; ++u)
-                    if ((int64_t)(s0 + u) * RPS < rows_left) dst[(int64_t)(s0 + u) * RPS * d.c_rs] = v[u];
+                    for (int u = 0; u < UB; ++u) v[u] = *(const bf16_t*)(src + (s0 + u) * (RPS * CSTR));
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int u = 0; u < UB; ++u)
+                        if ((int64_t)(s0 + u) * RPS < rows_left) dst[(int64_t)(s0 + u) * RPS * d.c_rs] = v[u];
+                }
             }
         }
     }
@@ -759,8 +774,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_line_kernel(GemmDesc d, i
 #pragma unroll
     for (int j = 0; j < C::NI; ++j) asm volatile("" :: "v"(bfr[0][j]));
     __syncthreads();
-    if (d.c_fp8) store_c_tile_fp8<BM, BN, C::WTM, C::WTN, C::MI, C::NI, C::THREADS>(d, acc, smem, m0, n0, g, wm, wn);
-    else store_c_tile<BM, BN, C::WTM, C::WTN, C::MI, C::NI, C::CSTR, C::THREADS>(d, acc, smem, m0, n0, g, wm, wn, cvec);
+    if constexpr ((BN & (BN - 1)) == 0) {
+        if (d.c_fp8) {
+            store_c_tile_fp8<BM, BN, C::WTM, C::WTN, C::MI, C::NI, C::THREADS>(d, acc, smem, m0, n0, g, wm, wn);
+            return;
+        }
+    }
+    store_c_tile<BM, BN, C::WTM, C::WTN, C::MI, C::NI, C::CSTR, C::THREADS>(d, acc, smem, m0, n0, g, wm, wn, cvec);
 }
 
 // Second kernel of a split contraction: adds the nsplit partial tiles in index order (so the result
@@ -1043,17 +1063,22 @@ hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s) {
     // unit, so nothing else hides the fixed cost of a step. Measured on the 4096- and 11008-wide layers at
     // 256 ... 2048 tokens: 5-25 % faster for one round; with more workgroups than compute units the
     // 32-deep steps, whose smaller LDS footprint lets two or three workgroups share a compute unit, stay.
+    // Eight wavefronts then, of 64 x 32 or 32 x 32 each: two on a SIMD cover each other's waits where nothing else on the
+    // compute unit does (128 x 128 tiles: 512 -> 512, 4 blocks at 2048 tokens 9.2 -> 8.3 us, interleaved 11.3 -> 10.3;
+    // 1024 -> 4096 at 1000 tokens 12.4 -> 11.6; 128 x 64: 1024 -> 1024, 4 blocks at 512 tokens 9.0 -> 8.2; 64 x 128: 1488 ->
+    // 4096 at 300 tokens 14.4 -> 10.8). With these two in steps of 64 on four stages up to K = 1280, of 128 on three beyond (11.4 -> 10.8).
+    const bool long_k = d.K > 1280 && deep_ok(d, 128);
     auto one_round = [&](int bm, int bn) { return d.K >= 256 && deep_ok(d, 128) && tiles(bm, bn) <= 256; };
     // With more workgroups than that: steps of 64 on two stages, whose 32 ... 64 KB of LDS let two or three workgroups
     // share a compute unit as the 32-deep kernel's do, in whole cache lines and on the schedule of gemm_line_kernel
     // (768 x 768 at 6304 tokens: 19.1 -> 14.4 us; 3072 -> 768: 58.6 -> 40.8 us; 1152 x 1152 at 1024 tokens: 10.9 -> 8.0 us)
     const bool rounds_deep = d.K >= 128 && deep_ok(d, 64);   // (from two steps on: 128 -> 2304 at 32768 tokens 53.7 -> 46.0 us; 192 -> 768 at 6304 tokens 8.4 -> 7.4 us)
     if (d.M > 64 && d.N > 64 && tiles(128, 128) >= kFill)
-        return one_round(128, 128) ? launch_line<128, 128, 2, 2, 64, 4>(d, s) : rounds_deep ? launch_line<128, 128, 2, 2, 64, 2>(d, s) : launch_dma<128, 128, 2, 2>(d, s);
+        return one_round(128, 128) ? launch_line<128, 128, 2, 4, 64, 4>(d, s) : rounds_deep ? launch_line<128, 128, 2, 2, 64, 2>(d, s) : launch_dma<128, 128, 2, 2>(d, s);
     if (d.M > 64 && tiles(128, 64) >= kFill)
-        return one_round(128, 64) ? launch_line<128, 64, 2, 2, 128, 3>(d, s) : rounds_deep ? launch_line<128, 64, 2, 2, 64, 2>(d, s) : launch_dma<128, 64, 2, 2>(d, s);
+        return one_round(128, 64) ? (long_k ? launch_line<128, 64, 4, 2, 128, 3>(d, s) : launch_line<128, 64, 4, 2, 64, 4>(d, s)) : rounds_deep ? launch_line<128, 64, 2, 2, 64, 2>(d, s) : launch_dma<128, 64, 2, 2>(d, s);
     if (d.N > 64 && tiles(64, 128) >= kFill)
-        return one_round(64, 128) ? launch_line<64, 128, 2, 2, 128, 3>(d, s) : rounds_deep ? launch_line<64, 128, 2, 2, 64, 2>(d, s) : launch_dma<64, 128, 2, 2>(d, s);
+        return one_round(64, 128) ? (long_k ? launch_line<64, 128, 2, 4, 128, 3>(d, s) : launch_line<64, 128, 2, 4, 64, 4>(d, s)) : rounds_deep ? launch_line<64, 128, 2, 2, 64, 2>(d, s) : launch_dma<64, 128, 2, 2>(d, s);
     // few tiles and a long contraction: 64 x 64 tiles, contraction index split over several workgroups
     // Few tiles and a long contraction index that would be split (two launches: the parts, then their
     // sum), small weights: the weight-streaming kernel over tiles of 32 tokens instead, one launch.
