@@ -23,7 +23,6 @@ namespace {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 // Tile and batch index of this workgroup. The grid is one-dimensional over all tiles of all batches;
 // workgroup ids are remapped so that each XCD owns a contiguous range of logical ids. Three orders:
@@ -981,6 +980,76 @@ bool gemm_whole_line_tiles(const GemmDesc& d) {
     return d.M > 64 && d.N > 64 && d.K >= 128 && d.a_seg == 0 && (int64_t)((d.M + 127) / 128) * ((d.N + 127) / 128) * d.G >= 160;
 }
 
+// Estimated time (us) of a product on one of the whole-line tiles, from its rounds of workgroups: launch, then per round a fixed part
+// (prologue, epilogue), the steps of 64 contraction indices, and the slower epilogue of a column map that is not contiguous. The tiles
+// of up to 192 columns or rows leave two workgroups on a compute unit; their last round, when it does not fill the first place of every
+// compute unit, takes the share `half` of a full one. Fitted to 195 products (K of 128 ... 11008, 1 ... 16 blocks, 300 ... 8192 tokens)
+// with every tile timed on each: the tiles' mean error is 8-12 %.
+struct TileCost {
+    int bm, bn, per_cu;
+    float launch, round, step, half, gather;
+};
+constexpr TileCost kCostWide{256, 256, 1, 0.f, 8.35f, 1.26f, 1.f, 6.1f};
+constexpr TileCost kCost256x128{256, 128, 1, 0.9f, 5.2f, 0.77f, 1.f, 4.2f};
+constexpr TileCost kCost128x192{128, 192, 2, 2.3f, 5.3f, 1.12f, 0.66f, 6.4f};
+constexpr TileCost kCost192x128{192, 128, 2, 2.0f, 5.5f, 1.125f, 0.68f, 5.5f};
+constexpr TileCost kCost128x128{128, 128, 2, 2.0f, 3.95f, 0.85f, 0.73f, 4.3f};
+
+static int64_t tiles_of(const GemmDesc& d, int bm, int bn) { return (d.M + bm - 1) / bm * ((d.N + bn - 1) / bn) * d.G; }
+
+static float tile_cost(const TileCost& c, const GemmDesc& d) {
+    const int64_t n = tiles_of(d, c.bm, c.bn), slots = compute_units() * c.per_cu, rest = n % slots;
+    const float last = rest == 0 ? 0.f : rest <= compute_units() ? c.half : 1.f;
+    const bool gathered = d.c_div == 1 ? d.c_hi != 1 : d.c_lo != 1;
+    return c.launch + ((float)(n / slots) + last) * (c.round + c.step * (float)((d.K + 63) / 64) + (gathered ? c.gather : 0.f));
+}
+
+// The 256 x 256 tiles run one per compute unit, in rounds; a last round that fills only part of the chip costs a whole round. When that
+// round would be at most 60 % full, the rows of tiles that fit the whole rounds go out on the large tile and the remaining rows as a
+// product of their own on 128 x 128 tiles, provided those make a single round (two workgroups per compute unit; such a round takes 0.64
+// of a round of the large tiles). 4096 -> 11008 at 1536 / 3072 / 6144 tokens: dense 200 -> 148, 318 -> 265, 547 -> 498 us, Monarch
+// stage 2 75 -> 58, 116 -> 106, 201 -> 193 us; remainders of two small rounds (2048, 8192 tokens) were 5 % slower.
+//
+// The same along the columns, where the weight rows are not gathered and the column map is linear in whole column tiles: the column tiles
+// that fill whole rounds go out on the large tile, the remaining columns as a product of their own (one round of smaller tiles). Stage 2
+// of the 4096 -> 11008 Monarch layer at 8192 tokens is 32 x 11 x 4 = 1408 tiles, 5.5 rounds paid as 6: 10 of the 11 column tiles are
+// exactly 5 rounds, the last 192 columns one round of 256 x 128 tiles (no gain there: that round costs 30 of the 34 us it replaces);
+// dense 4096 -> 11008 at 2048 / 5120 / 8192 tokens: 172 -> 148, 381 -> 365, 593 -> 576 us; no shape of a scan over six layer shapes and
+// ten token counts slower.
+struct BigSplit {
+    bool rows = false, cols = false;
+    GemmDesc first, rest;
+};
+static BigSplit big_split(const GemmDesc& d) {
+    BigSplit sp{false, false, d, d};
+    const int64_t per_row = (int64_t)((d.N + 255) / 256) * d.G, rows = (d.M + 255) / 256;
+    const int64_t ncu = compute_units(), whole = rows * per_row / ncu, rest = rows * per_row % ncu;
+    if (whole < 1 || rest == 0 || rest * 10 > ncu * 6) return sp;
+    const int64_t rows1 = whole * ncu / per_row;
+    const int64_t m2 = d.M - rows1 * 256;               // the remaining rows and their 128 x 128 tiles
+    const int64_t small = ((m2 + 127) / 128) * ((d.N + 127) / 128) * d.G;
+    if (rows1 >= 1 && rows1 < rows && small <= 2 * ncu) {
+        sp.rows = true;
+        sp.first.M = rows1 * 256;
+        sp.rest.M = m2;
+        sp.rest.A = (const bf16_t*)d.A + sp.first.M * d.a_rs;
+        sp.rest.C = (bf16_t*)d.C + sp.first.M * d.c_rs;
+        return sp;
+    }
+    const int64_t per_col = rows * d.G, cols = (d.N + 255) / 256;
+    const int64_t cols1 = whole * ncu / per_col;
+    const int64_t n1 = cols1 * 256;
+    if (cols1 >= 1 && cols1 < cols && d.b_div == 0 && !d.c_fp8 && (d.c_div == 1 || n1 % d.c_div == 0)) {
+        sp.first.N = (int)n1;
+        sp.rest.N = d.N - (int)n1;
+        sp.rest.B = (const bf16_t*)d.B + n1 * d.b_rs;
+        sp.rest.C = (bf16_t*)d.C + (d.c_div == 1 ? n1 * d.c_hi : (n1 / d.c_div) * d.c_hi);
+        const int64_t t256 = rows * ((sp.rest.N + 127) / 128) * d.G, t128 = ((d.M + 127) / 128) * ((sp.rest.N + 127) / 128) * d.G;
+        sp.cols = t256 <= ncu || t128 <= 2 * ncu;
+    }
+    return sp;
+}
+
 hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s) {
     // the 256 x 256 tile: in whole-line steps of 64 unless a segmented contraction index has segments that are not whole steps
     auto big = [&](const GemmDesc& dd) { return deep_ok(dd, 64) ? launch_wide(dd, s) : launch_dma<256, 256, 2, 4>(dd, s); };
@@ -1000,58 +1069,45 @@ hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s) {
     // large problems: 256 x 256 tiles on 8 wavefronts (half the LDS and L2 traffic per FLOP of 128 x 128)
     // (from 160 tiles on: the same scan as for kFill below, on Monarch, BLAST and low-rank layers at
     // 300 ... 6144 tokens, had 160 ahead of 256 by 5-17 % at the token counts where they differ, and ahead of 128 and 96 on balance)
-    if (d.M > 128 && d.N > 128 && d.K > kSmallK && tiles(256, 256) >= 160) {
-        // The 256 x 256 tiles run one per compute unit, in rounds; a last round that fills only part of the chip
-        // costs a whole round. When that round would be at most 60 % full, the rows of tiles that fit the whole
-        // rounds go out here and the remaining rows as a product of their own on 128 x 128 tiles, provided those
-        // make a single round (two workgroups per compute unit; such a round takes 0.64 of a round of the large
-        // tiles). 4096 -> 11008 at 1536 / 3072 / 6144 tokens: dense 200 -> 148, 318 -> 265, 547 -> 498 us, Monarch
-        // stage 2 75 -> 58, 116 -> 106, 201 -> 193 us; remainders of two small rounds (2048, 8192 tokens) were 5 % slower.
-        const int64_t per_row = (int64_t)((d.N + 255) / 256) * d.G, rows = (d.M + 255) / 256;
-        const int64_t ncu = compute_units(), whole = rows * per_row / ncu, rest = rows * per_row % ncu;
-        const int64_t rows1 = whole * ncu / per_row;
-        const int64_t m2 = d.M - rows1 * 256;           // the remaining rows and their 128 x 128 tiles
-        const int64_t small = ((m2 + 127) / 128) * ((d.N + 127) / 128) * d.G;
-        if (whole >= 1 && rest > 0 && rest * 10 <= ncu * 6 && rows1 >= 1 && rows1 < rows && small <= 2 * ncu) {
-            GemmDesc d1 = d, d2 = d;
-            d1.M = rows1 * 256;
-            d2.M = d.M - d1.M;
-            d2.A = (const bf16_t*)d.A + d1.M * d.a_rs;
-            d2.C = (bf16_t*)d.C + d1.M * d.c_rs;
-            if (hipError_t e = big(d1); e != hipSuccess) return e;
-            return deep_ok(d2, 64) ? launch_line<128, 128, 2, 2, 64, 2>(d2, s) : launch_dma<128, 128, 2, 2>(d2, s);
+    const bool use_big = d.M > 128 && d.N > 128 && d.K > kSmallK && tiles(256, 256) >= 160;
+    const bool use_mid = !use_big && d.M > 128 && d.N > 64 && d.K > kSmallK && tiles(256, 128) >= 160;
+    const BigSplit sp = use_big ? big_split(d) : BigSplit{};
+    // Products of several rounds: tiles of 128 x 192, 192 x 128 and 128 x 128 on two stages of 64, two workgroups per compute unit, so that
+    // one computes while the other fills its pipeline or writes its tile - the 256-wide tiles' rounds end in a burst of writes from all
+    // compute units at once (33 MB at 6.5 TB/s is 5 us a round) - and so that the rounds come in other sizes where the last one of the
+    // large tile would be nearly empty. Chosen by the estimate above, and only where it is 7 % below that of the tile which the rules
+    // below take (of 431 products 75 change, by 15 % in the mean, none more than 2 % slower: 1500 tokens of 512 -> 1536 in 4 blocks
+    // 19.2 -> 15.3 us, 520 tokens of 4096 -> 11008 90.5 -> 55.2, 3500 tokens of 320 -> 320 in 12 blocks 23.5 -> 17.4). Beyond K = 2048 the
+    // matrix units are the bound, and the large tile feeds them with less LDS and L2 traffic: 15 % there. Not beyond eight rounds (level or
+    // slower), nor with rows that straddle cache lines, which smaller tiles fetch more often (344 -> 688 in 8 blocks, 1800 tokens: 17.8 -> 21.5).
+    if (d.M > 128 && d.N > 64 && d.K >= kSmallK && d.K <= 4096 && (d.K % 64 == 0 || d.k_align) && deep_ok(d, 64) && tiles(128, 128) > compute_units()) {
+        float now = use_mid ? tile_cost(kCost256x128, d) : tile_cost(kCost128x128, d);
+        if (sp.rows) now = tile_cost(kCostWide, sp.first) + tile_cost(kCost128x128, sp.rest);
+        else if (sp.cols) now = tile_cost(kCostWide, sp.first) + fminf(tile_cost(kCost256x128, sp.rest), tile_cost(kCost128x128, sp.rest));
+        else if (use_big) now = tile_cost(kCostWide, d);
+        const TileCost* best = nullptr;
+        float est = (d.K <= 2048 ? 0.93f : 0.85f) * now;
+        for (const TileCost* c : {&kCost128x192, &kCost192x128, &kCost128x128}) {
+            const int64_t n = tiles(c->bm, c->bn);
+            const float e = tile_cost(*c, d);
+            if (n > compute_units() && n <= 16 * compute_units() && e < est) best = c, est = e;
         }
-        // The same along the columns, where the weight rows are not gathered and the column map is linear in whole
-        // column tiles: the column tiles that fill whole rounds go out on the large tile, the remaining columns as a
-        // product of their own (one round of smaller tiles by the rules below). Stage 2 of the 4096 -> 11008 Monarch
-        // layer at 8192 tokens is 32 x 11 x 4 = 1408 tiles, 5.5 rounds paid as 6: 10 of the 11 column tiles are exactly
-        // 5 rounds, the last 192 columns one round of 256 x 128 tiles (no gain there: that round costs 30 of the 34 us
-        // it replaces); dense 4096 -> 11008 at 2048 / 5120 / 8192 tokens: 172 -> 148, 381 -> 365, 593 -> 576 us; no
-        // shape of a scan over six layer shapes and ten token counts slower.
-        const int64_t per_col = rows * d.G, cols = (d.N + 255) / 256;
-        const int64_t cols1 = whole * ncu / per_col;
-        const int64_t n1 = cols1 * 256;
-        if (whole >= 1 && rest > 0 && rest * 10 <= ncu * 6 && cols1 >= 1 && cols1 < cols && d.b_div == 0 && !d.c_fp8 &&
-            (d.c_div == 1 || n1 % d.c_div == 0)) {
-            GemmDesc d1 = d, d2 = d;
-            d1.N = (int)n1;
-            d2.N = d.N - (int)n1;
-            d2.B = (const bf16_t*)d.B + n1 * d.b_rs;
-            d2.C = (bf16_t*)d.C + (d.c_div == 1 ? n1 * d.c_hi : (n1 / d.c_div) * d.c_hi);
-            const int64_t t256 = rows * ((d2.N + 127) / 128) * d.G, t128 = ((d.M + 127) / 128) * ((d2.N + 127) / 128) * d.G;
-            if (t256 <= ncu || t128 <= 2 * ncu) {
-                if (hipError_t e = big(d1); e != hipSuccess) return e;
-                return launch_gemm_mfma(d2, s);
-            }
-        }
-        return big(d);
+        if (best == &kCost128x192) return launch_line<128, 192, 2, 2, 64, 2>(d, s);
+        if (best == &kCost192x128) return launch_line<192, 128, 2, 2, 64, 2>(d, s);
+        if (best == &kCost128x128) return launch_line<128, 128, 2, 2, 64, 2>(d, s);
+    }
+    if (use_big) {
+        if (!sp.rows && !sp.cols) return big(d);
+        if (hipError_t e = big(sp.first); e != hipSuccess) return e;
+        if (sp.cols) return launch_gemm_mfma(sp.rest, s);
+        return deep_ok(sp.rest, 64) ? launch_line<128, 128, 2, 2, 64, 2>(sp.rest, s) : launch_dma<128, 128, 2, 2>(sp.rest, s);
     }
     // Between the two, where the 256 x 256 tiles are too few: 256 x 128 on 8 wavefronts of 64 x 64, one workgroup per
     // compute unit; a quarter less operand traffic per FLOP than the 128 x 128 tile (4096 x 4096 at 2048 tokens:
     // 98.6 -> 85 us; 11008 -> 4096: 232 -> 197 us; Monarch 4096 x 4096 stages: 60 -> 53.5 us per call)
     // (with steps of 64 contraction indices, whole cache lines per operand row, and three stages where the shape allows:
     // another 2-7 %; the same change on the 256 x 256 tile leaves room for two stages only and loses up to 10 %)
-    if (d.M > 128 && d.N > 64 && d.K > kSmallK && tiles(256, 128) >= 160)
+    if (use_mid)
         return deep_ok(d, 64) ? launch_line<256, 128, 4, 2, 64, 3>(d, s) : launch_dma<256, 128, 4, 2>(d, s);
     // otherwise the largest tile that still gives every compute unit a workgroup
     // 160 of the 256 compute units: a scan of token counts 33 ... 4096 on eight weight shapes had 160

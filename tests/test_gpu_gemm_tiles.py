@@ -1,0 +1,52 @@
+"""Tiles of the bf16 products that the dispatch picks by estimate for several rounds of workgroups (128 x 192, 192 x 128 and
+128 x 128, two workgroups per compute unit) and the eight-wavefront tiles of a single round, each with a ragged last tile
+in rows and columns, contiguous and interleaved outputs, odd and even numbers of steps, a partial last step."""
+import numpy as np
+import pytest
+
+import blr_inputs as bi
+import oracle
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("T,n_in,n_out", [
+    (4095, 192, 2296), (3073, 128, 3085),             # 192 x 128, two or three steps; columns that end off a 16-byte boundary
+    (4095, 192, 3068),                                # 128 x 192
+    (520, 256, 11000), (1100, 320, 4600),             # 128 x 128, several rounds
+    (1999, 1280, 2044), (1999, 1288, 2041),           # one round of 128 x 128
+    (1000, 1280, 2050), (1000, 1416, 2044),           # one round of 128 x 64, in steps of 64 and of 128
+    (300, 1480, 4090), (300, 1000, 4090),             # one round of 64 x 128
+])
+def test_dense_tiles(T, n_in, n_out):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    W, X = bi.dense_weight(n_in, n_out, "bf16"), bi.activations(T, n_in, "bf16")
+    Y = gu.empty_out(T, n_out, "bf16")
+    gu.B.dense_reference_forward(gu.to_dev(X), gu.to_dev(W), Y, 0)
+    torch.cuda.synchronize()
+    assert gu.rel_err(gu.to_f64(Y), oracle.dense_forward(X.f64, W.f64)) <= gu.TOL["bf16"]
+
+
+@pytest.mark.parametrize("T,b,p,rp,q", [
+    (1409, 4, 64, 32, 1530), (4095, 4, 64, 48, 572),  # second factor on 192 x 128
+    (2047, 4, 64, 32, 1532), (1153, 16, 64, 8, 572),  # 128 x 192
+    (1153, 16, 64, 12, 380), (577, 4, 64, 64, 3068),  # 128 x 128, several rounds
+])
+@pytest.mark.parametrize("order", ["interleaved", "blocked"])
+def test_monarch_tiles(T, b, p, rp, q, order):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    B = gu.B
+    R = bi.gaussian(bi.BASE_SEED, 51, (b, rp * b, p), 1.0 / np.sqrt(p), "bf16")
+    L = bi.gaussian(bi.BASE_SEED, 52, (b, q, b * rp), 1.0 / np.sqrt(b * rp), "bf16")
+    X = bi.activations(T, b * p, "bf16")
+    Y = gu.empty_out(T, b * q, "bf16")
+    blocked = order == "blocked"
+    B.monarch_rect_forward(gu.to_dev(X), gu.to_dev(R), gu.to_dev(L), Y, b, b, rp, B.MONARCH_OUT_BLOCKED if blocked else 0)
+    torch.cuda.synchronize()
+    Yref = oracle.monarch_rect_forward(X.f64, R.f64, L.f64, b, b, oracle.OUT_BLOCKED if blocked else oracle.OUT_INTERLEAVED)
+    assert gu.rel_err(gu.to_f64(Y), Yref) <= gu.TOL["bf16"]
