@@ -431,10 +431,9 @@ static blr_status blast_run(const void* X, const void* U, const void* S, const v
             s1.A = (const unsigned char*)X + (size_t)c0 * n_in * 2;
             s1.M = tc;
             GemmDesc s1t = s1;
-            if (aligned_blocks && gemm_whole_line_tiles(s1)) {
-                s1t.k_align = 1;
-                s1t.B = pack + pk.off_Va; s1t.b_rs = blast_va_row(q, 64); s1t.b_gs = (int64_t)r * s1t.b_rs;
-            }
+            s1t.k_align = 1;
+            s1t.B = pack + pk.off_Va; s1t.b_rs = blast_va_row(q, 64); s1t.b_gs = (int64_t)r * s1t.b_rs;
+            if (!aligned_blocks || !gemm_whole_line_tiles(s1) || !mfma_gemm_supported(s1t)) s1t = s1;
             blr_status st = run_gemm(s1t, dt, true, s);
             if (st != BLR_OK) return st;
             // few tokens: one thread per 8 outputs

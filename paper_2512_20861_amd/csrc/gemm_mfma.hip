@@ -1045,7 +1045,8 @@ static BigSplit big_split(const GemmDesc& d) {
         sp.rest.B = (const bf16_t*)d.B + n1 * d.b_rs;
         sp.rest.C = (bf16_t*)d.C + (d.c_div == 1 ? n1 * d.c_hi : (n1 / d.c_div) * d.c_hi);
         const int64_t t256 = rows * ((sp.rest.N + 127) / 128) * d.G, t128 = ((d.M + 127) / 128) * ((sp.rest.N + 127) / 128) * d.G;
-        sp.cols = t256 <= ncu || t128 <= 2 * ncu;
+        // (whole-line windows only exist on the whole-line tiles: the remaining columns have to take them too)
+        sp.cols = (t256 <= ncu || t128 <= 2 * ncu) && (!d.k_align || gemm_whole_line_tiles(sp.rest));
     }
     return sp;
 }

@@ -52,3 +52,24 @@ def test_chunks_agree_with_one_chunk(T):
     torch.cuda.synchronize()
     err = (whole.double() - parts.double()).abs().max() / parts.double().abs().max()
     assert torch.isfinite(whole).all() and float(err) <= 3 * 2.0 ** -9
+
+
+def test_unaligned_blocks_and_a_last_column_tile():
+    """Stage 1 of 16 x 17 large tiles on 256 compute units: the columns past the whole round are a product of their own, with
+    too few tiles for the kernels that read input blocks in 64-column windows. Two stored intermediates and the output are
+    rounded to bf16, 2^-9 of each value, and the sums in between average it: 1e-2 as for the other cases."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    B = gu.B
+    T, b, r, q, p = 256, 16, 4352, 1376, 16
+    g = torch.Generator(device="cuda").manual_seed(7)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda")
+    U, S, V = (rand(b, p, r) / r ** 0.5).bfloat16(), (rand(b, b, r) / b ** 0.5).bfloat16(), (rand(b, q, r) / q ** 0.5).bfloat16()
+    X = rand(T, b * q).bfloat16()
+    packed = B.blast_pack(U, S, V, b * q, b * p, b, r)
+    Y = torch.full((T, b * p), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.blast_forward(X, U, None, packed, Y, b, r, B.BLAST_PACKED | B.BLAST_THREE_KERNELS)
+    Z = [X[:, j * q:(j + 1) * q].float() @ V[j].float() for j in range(b)]
+    ref = torch.cat([sum(S[i, j].float() * Z[j] for j in range(b)) @ U[i].float().t().contiguous() for i in range(b)], dim=1)
+    assert float((Y.float() - ref).norm() / ref.norm()) <= 1e-2
