@@ -49,7 +49,7 @@ typedef struct {
 blr_status blr_chain_create(const blr_chain_desc* desc, const blr_chain_layer* layers, const blr_chain_buffers* buffers, blr_chain** out);
 /* Runs the chain on the residual stream that h holds, in place. */
 blr_status blr_chain_forward(blr_chain* chain, blr_stream stream);
-/* Waits for the device if the chain ever replayed its graph. */
+/* Waits for the last pass if that was a replay of the graph. */
 void blr_chain_destroy(blr_chain* chain);
 
 #ifdef __cplusplus

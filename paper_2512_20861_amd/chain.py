@@ -170,8 +170,10 @@ class DeviceChain:
         self._native = self._create_native() if self.grouped and td == torch.bfloat16 and T > 0 else None
 
     def _create_native(self):
-        """Handle of the library's chain object over this object's factors and buffers, or None where it has none."""
+        """Handle of the library's chain object over this object's factors and buffers, or None where it has none.
+        The handle holds addresses, so the tensors behind it live as long as it does."""
         L0 = self.layers[0]
+        self._held = []
         def factors(lin):
             if isinstance(lin, _MonarchGroup):
                 return lin.R, lin.L
@@ -186,12 +188,23 @@ class DeviceChain:
                 if first is None:
                     return None
                 setattr(layers[i], field, B.ChainFactors(first.data_ptr(), second.data_ptr()))
+                self._held += (first, second)
         self.h2 = torch.empty_like(self.h)
-        buffers = B.ChainBuffers(*(t.data_ptr() for t in (self.h, self.h2, self.n, self.a, self.o, self.dn, self.qkv, self.gu, self.m, self.ws)), self.ws.numel())
+        work = (self.h, self.h2, self.n, self.a, self.o, self.dn, self.qkv, self.gu, self.m, self.ws)
+        self._held += work
+        buffers = B.ChainBuffers(*(t.data_ptr() for t in work), self.ws.numel())
         blast = L0["q"].op == "blast"
         desc = B.ChainDesc(int(blast), len(self.layers), self.T, self.hidden, self.mlp, L0["q"].b if blast else L0["q"].nb, L0["q"].r, L0["gate"].r, self.eps)
         same = all(L[n].r == L0[n].r for L in self.layers for n in LINEARS) and all(L0[n].r == L0["q"].r for n in "kvo") and L0["down"].r == L0["gate"].r
         return B.chain_create(desc, layers, buffers) if same else None
+
+    def __getstate__(self):
+        """A copy (copy.deepcopy, pickle) makes a handle of its own over its own tensors."""
+        return {k: v for k, v in self.__dict__.items() if k not in ("_native", "_held", "h2")} | {"_native": self._native is not None}
+
+    def __setstate__(self, state):
+        self.__dict__.update(state)
+        self._native = self._create_native() if state["_native"] else None
 
     def __del__(self):
         if getattr(self, "_native", None) and B is not None and B.chain_destroy is not None:   # (at interpreter exit the module may be gone)

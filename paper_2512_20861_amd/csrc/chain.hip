@@ -6,8 +6,9 @@
 #include "../../include/blr_chain.h"
 #include "blr_common.h"
 #include <cmath>
+#include <exception>
+#include <memory>
 #include <mutex>
-#include <new>
 #include <vector>
 
 using namespace blr;
@@ -20,6 +21,7 @@ struct blr_chain {
     int calls = 0;
     bool graph_failed = false;
     hipGraphExec_t exec = nullptr;
+    hipEvent_t replayed = nullptr;                      // recorded behind every replay
 };
 
 namespace {
@@ -214,12 +216,15 @@ blr_status blr_chain_create(const blr_chain_desc* desc, const blr_chain_layer* l
         if (n > need) need = n;
     }
     if (b.workspace_bytes < need) return BLR_ERR_WORKSPACE;
-    blr_chain* c = new (std::nothrow) blr_chain;
-    if (!c) return BLR_ERR_LAUNCH;
-    c->d = d;
-    c->layers.assign(layers, layers + d.layers);
-    c->buf = b;
-    *out = c;
+    try {                                               // (no exception leaves a C entry)
+        std::unique_ptr<blr_chain> c(new blr_chain);
+        c->d = d;
+        c->layers.assign(layers, layers + d.layers);
+        c->buf = b;
+        *out = c.release();
+    } catch (const std::exception&) {
+        return BLR_ERR_LAUNCH;
+    }
     return BLR_OK;
 }
 
@@ -235,18 +240,23 @@ blr_status blr_chain_forward(blr_chain* c, blr_stream stream) {
         std::lock_guard<std::mutex> g(c->lock);
         // the first pass runs as separate launches: a chain that is used once pays for no graph
         if (c->calls++ >= 1 && !c->exec && !c->graph_failed) {
-            c->exec = capture(*c);
+            c->exec = hipEventCreateWithFlags(&c->replayed, hipEventDisableTiming) == hipSuccess ? capture(*c) : nullptr;
             c->graph_failed = !c->exec;
+            if (c->graph_failed && c->replayed) { (void)hipEventDestroy(c->replayed); c->replayed = nullptr; }
         }
         exec = c->exec;
     }
-    return exec ? from_hip(hipGraphLaunch(exec, s)) : run_pass(*c, s);
+    if (!exec) return run_pass(*c, s);
+    if (hipGraphLaunch(exec, s) != hipSuccess) return BLR_ERR_LAUNCH;
+    return from_hip(hipEventRecord(c->replayed, s));
 }
 
 void blr_chain_destroy(blr_chain* c) {
     if (!c) return;
     if (c->exec) {
-        (void)hipDeviceSynchronize();                   // a replay may still be running
+        // a replay may still be running; the wait is for it alone: one for the device breaks a capture under way on another stream
+        (void)hipEventSynchronize(c->replayed);
+        (void)hipEventDestroy(c->replayed);
         (void)hipGraphExecDestroy(c->exec);
     }
     delete c;

@@ -50,3 +50,34 @@ def test_native_chain(op, T):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(chain.h, first[0])
+
+
+@pytest.mark.parametrize("T", [2, 33])
+def test_copies_and_lifetimes(T):
+    """A copied chain has buffers and a handle of its own; a chain that ends while another stream is under capture leaves
+    the capture alone."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import copy
+    import gpu_util as gu
+    from paper_2512_20861_amd.chain import DeviceChain
+    layers = bi.chain_layers("monarch", n_layers=1, hidden=512, mlp=768, params=PARAMS["monarch"], dtype="bf16")
+    x0, x1 = (gu.to_dev(bi.activations(T, 512, "bf16", seed=n)) for n in (1, 2))
+    chain = DeviceChain(layers, T, eps=oc.EPS)
+    want = [chain.forward(x).clone() for x in (x0, x1, x0)]
+    other = copy.deepcopy(chain)
+    assert other._native and other.h.data_ptr() != chain.h.data_ptr()
+    kept = chain.forward(x0)
+    for n in range(3):
+        assert torch.equal(other.forward(x1), want[1]) and torch.equal(kept, want[0])
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        other.h.copy_(x0)
+        del chain
+        other.forward(x0)
+    for _ in range(3):
+        other.h.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(other.h, want[0])
