@@ -1,0 +1,38 @@
+"""Infinities and NaN keep to the outputs that depend on them: what a kernel reads past the end of its contraction index
+meets a zero there, and an infinity times zero would be NaN. All factors
+are positive, so that an infinity in an input is an infinity, not NaN, in every output it reaches."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _agree(got, ref, tol):
+    """The same infinities and NaN, and finite values within the repository's bound of the largest of them."""
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+    ok = np.isfinite(ref)
+    assert ok.any() and not ok.all() and np.abs(got[ok] - ref[ok]).max() <= tol * np.abs(ref[ok]).max()
+
+
+@pytest.mark.parametrize("T,p,q,b1,b2,rp", [(3, 68, 24, 2, 2, 20), (17, 4, 16, 1, 3, 4), (5, 132, 100, 3, 5, 12), (8, 64, 64, 4, 4, 16)])
+def test_fp32_monarch(T, p, q, b1, b2, rp):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    n_in, n_out = b1 * p, b2 * q
+    rng = np.random.default_rng(T + p)
+    R, L, X = (rng.uniform(0.5, 1.0, s).astype(np.float32) for s in ((b1, rp * b2, p), (b2, q, b1 * rp), (T, n_in)))
+    X[0, n_in - 1] = np.inf                              # in the last four of a block
+    X[T // 2, p - 4] = np.nan
+    R[b1 - 1, (rp - 1) * b2] = 2e38                      # the last of the intermediate of output block 0 overflows, with finite inputs
+    Y = gu.empty_out(T, n_out, "f32")
+    gu.B.monarch_rect_forward(*(torch.from_numpy(t).cuda() for t in (X, R, L)), Y, b1, b2, rp, 0)
+    torch.cuda.synchronize()
+    Z = np.zeros((T, b2, b1 * rp), np.float32)           # the intermediate as fp32 holds it, then fp64 again
+    with np.errstate(all="ignore"):
+        for l in range(b1):
+            z = X[:, l * p:(l + 1) * p].astype(np.float64) @ R[l].astype(np.float64).T
+            Z[:, :, l * rp:(l + 1) * rp] = z.astype(np.float32).reshape(T, rp, b2).transpose(0, 2, 1)
+        ref = np.stack([Z[:, k].astype(np.float64) @ L[k].astype(np.float64).T for k in range(b2)], axis=2).reshape(T, n_out)
+    _agree(gu.to_f64(Y), ref, gu.TOL["f32"])
