@@ -155,6 +155,12 @@ __device__ __forceinline__ void source_rows(const SkinnySource& q, int M, int K,
                 for (int v = 0; v < 2; ++v)
 #pragma unroll
                     for (int u = 0; u < 4; ++u) zv[v][u] = *(const u32x4*)(Z + (int64_t)(m0 + v < M ? m0 + v : m0) * q.b * q.d + off[u]);
+                if (q.b < 16)                            // both factors of an absent block are zero (an infinity times zero would be NaN)
+#pragma unroll
+                    for (int v = 0; v < 2; ++v)
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            if (jq * 4 + u >= q.b) zv[v][u] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
                 for (int v = 0; v < 2; ++v) {
                     if (m0 + v >= M) break;              // uniform

@@ -1,8 +1,11 @@
-"""Infinities and NaN keep to the outputs that depend on them: what a kernel reads past the end of its contraction index
-meets a zero there, and an infinity times zero would be NaN. All factors
+"""Infinities and NaN keep to the outputs that depend on them: what a kernel reads past its range (the end of a contraction
+index, an absent block, a neighbour's columns) meets a zero there, and an infinity times zero would be NaN. All factors
 are positive, so that an infinity in an input is an infinity, not NaN, in every output it reaches."""
 import numpy as np
 import pytest
+
+import blr_inputs as bi
+import oracle
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -36,3 +39,29 @@ def test_fp32_monarch(T, p, q, b1, b2, rp):
             Z[:, :, l * rp:(l + 1) * rp] = z.astype(np.float32).reshape(T, rp, b2).transpose(0, 2, 1)
         ref = np.stack([Z[:, k].astype(np.float64) @ L[k].astype(np.float64).T for k in range(b2)], axis=2).reshape(T, n_out)
     _agree(gu.to_f64(Y), ref, gu.TOL["f32"])
+
+
+def _blast(T, q, p, b, r, bad, flags):
+    """bad: (token, column) of an infinity in X"""
+    import gpu_util as gu
+    rng = np.random.default_rng(q + r)
+    make = lambda scale, *s: torch.from_numpy((rng.uniform(0.5, 1.0, s) * scale).astype(np.float32)).bfloat16()
+    U, S, V, X = make(1 / r, b, p, r), make(1 / b, b, b, r), make(1 / q, b, q, r), make(1, T, b * q)
+    for t, c in bad:
+        X[t, c] = float("inf")
+    Xd, Ud, Sd, Vd = (t.cuda() for t in (X, U, S, V))
+    Y = gu.empty_out(T, b * p, "bf16")
+    packed = gu.B.blast_pack(Ud, Sd, Vd, b * q, b * p, b, r)
+    gu.B.blast_forward(Xd, Ud, None, packed, Y, b, r, flags | gu.B.BLAST_PACKED)
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        ref = oracle.blast_forward(*(t.double().numpy() for t in (X, U, S, V)))
+    _agree(gu.to_f64(Y), ref, gu.TOL["bf16"])
+
+
+@pytest.mark.parametrize("T,b", [(2, 1), (2, 3), (2, 4), (2, 15)])
+def test_coupling_of_absent_blocks(T, b):
+    """One or two tokens: the coupling takes 16 input blocks in four lanes, whatever their number."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    _blast(T, 64, 40, b, 128, [(1, b * 64 - 1)], 0)
