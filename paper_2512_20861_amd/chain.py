@@ -170,33 +170,56 @@ class DeviceChain:
         self._native = self._create_native() if self.grouped and td == torch.bfloat16 and T > 0 else None
 
     def _create_native(self):
-        """Handle of the library's chain object over this object's factors and buffers, or None where it has none.
-        The handle holds addresses, so the tensors behind it live as long as it does."""
-        L0 = self.layers[0]
-        self._held = []
-        def factors(lin):
-            if isinstance(lin, _MonarchGroup):
-                return lin.R, lin.L
-            if isinstance(lin, _BlastGroup):
-                return lin.packed, lin.U
-            return (lin.R, lin.L) if lin.op == "monarch" else (getattr(lin, "packed", None), lin.U)
-        layers = (B.ChainLayer * len(self.layers))()
-        for i, L in enumerate(self.layers):
-            lins = (self.groups[i]["qkv"], L["o"], self.groups[i]["gu"], L["down"])
-            for field, lin in zip(("qkv", "o", "gate_up", "down"), lins):
-                first, second = factors(lin)
-                if first is None:
-                    return None
-                setattr(layers[i], field, B.ChainFactors(first.data_ptr(), second.data_ptr()))
-                self._held += (first, second)
-        self.h2 = torch.empty_like(self.h)
-        work = (self.h, self.h2, self.n, self.a, self.o, self.dn, self.qkv, self.gu, self.m, self.ws)
-        self._held += work
-        buffers = B.ChainBuffers(*(t.data_ptr() for t in work), self.ws.numel())
-        blast = L0["q"].op == "blast"
-        desc = B.ChainDesc(int(blast), len(self.layers), self.T, self.hidden, self.mlp, L0["q"].b if blast else L0["q"].nb, L0["q"].r, L0["gate"].r, self.eps)
-        same = all(L[n].r == L0[n].r for L in self.layers for n in LINEARS) and all(L0[n].r == L0["q"].r for n in "kvo") and L0["down"].r == L0["gate"].r
-        return B.chain_create(desc, layers, buffers) if same else None
+        """Handle of the library's chain object over this object's factors and buffers, or None where it has none: only where
+        the call list is, call by call, what the handle runs. It holds addresses, so the tensors behind it live as long as it does."""
+        T, d, m, ws, n = self.T, self.hidden, self.mlp, self.ws, len(self.layers)
+        calls = self._held = [args for _, args in self.call_list()]
+        linears = calls[1::2]                            # four per layer: q/k/v, o, gate/up, down
+        if len(calls) != 1 + 8 * n or any(len(c) < 9 for c in linears):
+            return None
+        blast = linears[0][0] is B.blast_group_forward
+        b = linears[0][5]
+        r_square, r_mlp = (linears[0][6], linears[2][6]) if blast else (linears[0][7] * b, linears[2][7] * b)
+
+        def linear(given, X, Y, r, members):
+            """The call of a linear or group with the factors of the given one, and those factors."""
+            if blast:
+                first, second = given[3 if members > 1 else 4], given[2]
+                return ((B.blast_group_forward, X, second, first, Y, b, r, members, 0, ws) if members > 1 else
+                        (B.blast_forward, X, second, None, first, Y, b, r, B.BLAST_PACKED, ws)), (first, second)
+            first, second = given[2], given[3]
+            return ((B.monarch_rect_forward, X, first, second, Y, b, members * b, r // b, B.MONARCH_OUT_BLOCKED, ws) if members > 1 else
+                    (B.monarch_forward, X, first, second, Y, b, r, B.MONARCH_IN_BLOCKED, ws)), (first, second)
+
+        want, factors = [(B.rmsnorm, self.h, self.n, self.eps)], []
+        for i, (qkv, o, gu, down) in enumerate(zip(*(linears[k::4] for k in range(4)))):
+            steps = (linear(qkv, self.n, self.qkv, r_square, 3), linear(o, self.a, self.o, r_square, 1),
+                     linear(gu, self.n, self.gu, r_mlp, 2), linear(down, self.m, self.dn, r_mlp, 1))
+            factors.append([f for _, f in steps])
+            want += [steps[0][0], (B.sum3_scaled, self.q, self.k, self.v, self.a, 1.0 / math.sqrt(3.0)), steps[1][0],
+                     (B.residual_add_rmsnorm, self.h, self.o, self.n, self.eps), steps[2][0], (B.silu_mul, self.g, self.u, self.m), steps[3][0],
+                     (B.residual_add_rmsnorm, self.h, self.dn, None if i == n - 1 else self.n, self.eps)]
+        same = lambda x, y: x is y or (not isinstance(x, torch.Tensor) and not isinstance(y, torch.Tensor) and x == y)
+        column = lambda t, whole, at, width: (t.data_ptr() == whole.data_ptr() + 2 * at and tuple(t.shape) == (T, width) and
+                                              t.stride() == (whole.shape[1], 1) and t.dtype == whole.dtype)
+        widths = [(t, d) for t in (self.h, self.n, self.a, self.o, self.dn)] + [(self.qkv, 3 * d), (self.gu, 2 * m), (self.m, m)]
+        if not (len(calls) == len(want) and all(len(c) == len(w) and all(map(same, c, w)) for c, w in zip(calls, want)) and
+                all(t.dtype == torch.bfloat16 and tuple(t.shape) == (T, w) for t, w in widths) and
+                all(column(t, self.qkv, i * d, d) for i, t in enumerate((self.q, self.k, self.v))) and
+                column(self.g, self.gu, 0, m) and column(self.u, self.gu, m, m)):
+            return None
+        try:
+            for c in calls:
+                c[0].marshal(*c[1:])                     # the checks of the separate calls
+            layers = (B.ChainLayer * n)()
+            for layer, four in zip(layers, factors):
+                for field, (first, second) in zip(("qkv", "o", "gate_up", "down"), four):
+                    setattr(layer, field, B.ChainFactors(first.data_ptr(), second.data_ptr()))
+            self.h2 = torch.empty_like(self.h)
+            buffers = B.ChainBuffers(*(t.data_ptr() for t in (self.h, self.h2, self.n, self.a, self.o, self.dn, self.qkv, self.gu, self.m, ws)), ws.numel())
+            return B.chain_create(B.ChainDesc(int(blast), n, T, d, m, b, r_square, r_mlp, self.eps), layers, buffers)
+        except (ValueError, TypeError, B.BlrError):      # the separate calls say what is wrong, when they run
+            return None
 
     def __getstate__(self):
         """A copy (copy.deepcopy, pickle) makes a handle of its own over its own tensors."""

@@ -81,3 +81,37 @@ def test_copies_and_lifetimes(T):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(other.h, want[0])
+
+
+def _lin(x, f):
+    return oracle.monarch_forward(x, f.R.f64, f.L.f64) if hasattr(f, "R") else oracle.blast_forward(x, f.U.f64, f.S.f64, f.V.f64)
+
+
+@pytest.mark.parametrize("kind", ["monarch, wider blocks in the MLP", "blast, fewer blocks in the MLP", "blast with a monarch output projection"])
+@pytest.mark.parametrize("T", [2, 33])
+def test_layers_that_differ_inside(kind, T):
+    """The native chain has one block count and one kind of linear; a chain of several runs its own call list."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    from paper_2512_20861_amd.chain import DeviceChain
+    make = lambda op, **prm: bi.chain_layers(op, n_layers=2, hidden=512, mlp=1024, params=prm, dtype="bf16")
+    op = kind.split()[0].rstrip(",")
+    layers = make(op, **PARAMS[op])
+    if "output" in kind:
+        other = make("monarch", nblocks=4, r_square=136, r_mlp=128)
+        names = ("o",)
+    else:
+        other = make(op, **(dict(nblocks=8, r_square=64, r_mlp=128) if op == "monarch" else dict(b=2, r_square=136, r_mlp=72)))
+        names = ("gate", "up", "down")
+    for layer, o in zip(layers, other):
+        for name in names:
+            layer[name] = o[name]
+    x = bi.activations(T, 512, "bf16")
+    chain = DeviceChain(layers, T, eps=oc.EPS)
+    assert chain.grouped
+    ref = oc.chain_forward(x.f64, layers, _lin)
+    for _ in range(3):
+        got = chain.forward(gu.to_dev(x))
+        torch.cuda.synchronize()
+        assert gu.rel_err(gu.to_f64(got), ref) <= 2e-2
