@@ -451,6 +451,18 @@ def silu_mul(G, U, M, stream=None):
     return ("blr_silu_mul", (_ptr(G), _ptr(U), _ptr(M), T, d, _dt(G), _stream(stream)), M, (G, U, M))
 
 
+def snapshot(objects, keep) -> bytes:
+    """Identities of the objects of a tuple and of the attributes of instances among them, and the addresses and layouts of
+    the tensors; the list `keep` receives all of them (csrc/host_call.cpp)."""
+    lib()
+    return _host.snapshot(objects, keep)
+
+
+def unchanged(objects, row) -> bool:
+    """Would snapshot() say `row` again? As long as the objects kept from that snapshot live: nothing was replaced or moved."""
+    return _host.unchanged(objects, row)
+
+
 def chain_create(desc, layers, buffers):
     """Handle of a native decoder-layer chain (include/blr_chain.h), or None where its shapes have no grouped execution.
     The tensors behind the pointers have to outlive it; chain_destroy ends it."""

@@ -167,13 +167,45 @@ class DeviceChain:
         need = max([lin.workspace_bytes(T) for layer in self.layers for lin in layer.values()] +
                    [grp.workspace_bytes(T) for layer in self.groups for grp in layer.values()])
         self.ws = torch.empty(max(need, 16), dtype=torch.uint8, device="cuda")
-        self._native = self._create_native() if self.grouped and td == torch.bfloat16 and T > 0 else None
+        self._native, self._parts = None, None
+        if self.grouped and td == torch.bfloat16 and T > 0:
+            self._native = self._create_native()
+
+    def _made_of(self):
+        """What a pass of a grouped chain is made of."""
+        parts = [self.T, self.eps, self.hidden, self.mlp, self.blocked, self.grouped, len(self.layers) == len(self.groups), self.h, self.n, self.a, self.o, self.dn,
+                 self.q, self.k, self.v, self.g, self.u, self.qkv, self.gu, self.m, self.ws]
+        for L, G in zip(self.layers, self.groups):
+            parts += (G["qkv"], L["o"], G["gu"], L["down"])
+        return tuple(parts)
+
+    def _handle(self):
+        """The library's chain object, if it is still made of what this object holds: the same objects, their tensors at the
+        same addresses. After a change a pass runs step by step; the first pass that finds the parts of the one before makes
+        the handle anew."""
+        if self._parts is None:
+            return None
+        if not B.unchanged(self._made_of(), self._parts):
+            self._drop_native()
+            self._tried, self._kept = False, []
+            self._parts = B.snapshot(self._made_of(), self._kept)
+            return None
+        if not self._tried:
+            self._native = self._create_native()
+        return self._native
+
+    def _drop_native(self):
+        if self._native and B is not None and B.chain_destroy is not None:   # (at interpreter exit the module may be gone)
+            B.chain_destroy(self._native)
+        self._native = None
 
     def _create_native(self):
         """Handle of the library's chain object over this object's factors and buffers, or None where it has none: only where
-        the call list is, call by call, what the handle runs. It holds addresses, so the tensors behind it live as long as it does."""
+        the call list is, call by call, what the handle runs."""
+        self._tried, self._kept = True, []
+        self._parts = B.snapshot(self._made_of(), self._kept)
         T, d, m, ws, n = self.T, self.hidden, self.mlp, self.ws, len(self.layers)
-        calls = self._held = [args for _, args in self.call_list()]
+        calls = [args for _, args in self.call_list()]
         linears = calls[1::2]                            # four per layer: q/k/v, o, gate/up, down
         if len(calls) != 1 + 8 * n or any(len(c) < 9 for c in linears):
             return None
@@ -223,16 +255,17 @@ class DeviceChain:
 
     def __getstate__(self):
         """A copy (copy.deepcopy, pickle) makes a handle of its own over its own tensors."""
-        return {k: v for k, v in self.__dict__.items() if k not in ("_native", "_held", "h2")} | {"_native": self._native is not None}
+        return {k: v for k, v in self.__dict__.items() if k not in ("_native", "_parts", "_kept", "_tried", "h2")} | {"_native": self._native is not None}
 
     def __setstate__(self, state):
         self.__dict__.update(state)
-        self._native = self._create_native() if state["_native"] else None
+        native, self._native, self._parts = self._native, None, None
+        if native:
+            self._native = self._create_native()
 
     def __del__(self):
-        if getattr(self, "_native", None) and B is not None and B.chain_destroy is not None:   # (at interpreter exit the module may be gone)
-            B.chain_destroy(self._native)
-            self._native = None
+        if getattr(self, "_native", None):
+            self._drop_native()
 
     def call_list(self):
         """[(label, (fn, *args)), ...] in execution order; h must hold the input when the first one runs."""
@@ -268,8 +301,9 @@ class DeviceChain:
         recorded under the labels of its member linears, each with its own slice of the output);
         `rows` (an index tensor) restricts the copies to those token rows."""
         self.h.copy_(x0)
-        if self._native and not record:
-            B.chain_forward(self._native)
+        handle = None if record else self._handle()
+        if handle:
+            B.chain_forward(handle)
             return self.h
         taps = {}
         keep = (lambda t: t.clone()) if rows is None else (lambda t: t[rows].clone())

@@ -318,7 +318,83 @@ PyObject* make_launcher(PyObject*, PyObject* args) {
     Py_RETURN_NONE;
 }
 
-PyMethodDef methods[] = {{"launcher", make_launcher, METH_VARARGS, nullptr}, {}};
+// Objects, the attributes of the instances of Python classes among them, and where and how every tensor of these lies in
+// memory, as a row of numbers: written to `out`, or compared with an earlier row as it goes.
+struct Row {
+    std::string* out;
+    const char *at, *end;
+    bool put(int64_t v) {
+        if (out) {
+            out->append((const char*)&v, sizeof v);
+            return true;
+        }
+        if (at == end || memcmp(at, &v, sizeof v)) return false;
+        at += sizeof v;
+        return true;
+    }
+};
+
+// false: another row (or an error is set). `keep` receives the objects, so that none of their identities is given out again.
+bool describe(PyObject* o, bool attributes, Row& row, PyObject* keep) {
+    if (!row.put((int64_t)(intptr_t)o) || (keep && PyList_Append(keep, o) < 0)) return false;
+    if (PyObject_TypeCheck(o, (PyTypeObject*)THPVariableClass)) {
+        const at::Tensor& t = THPVariable_Unpack(o);
+        if (!row.put(t.has_storage() ? (int64_t)(intptr_t)t.unsafeGetTensorImpl()->unsafe_storage().data() : -1) ||
+            !row.put(t.has_storage() ? t.storage_offset() : 0) || !row.put((int64_t)t.scalar_type() << 8 | (uint8_t)t.device().index()) || !row.put(t.dim())) return false;
+        for (int64_t v : t.sizes())
+            if (!row.put(v)) return false;
+        for (int64_t v : t.strides())
+            if (!row.put(v)) return false;
+        return true;
+    }
+    if (!attributes || !PyType_HasFeature(Py_TYPE(o), Py_TPFLAGS_HEAPTYPE)) return true;
+    PyObject* d = PyObject_GenericGetDict(o, nullptr);
+    if (!d) {                                            // an instance without attributes of its own
+        PyErr_Clear();
+        return true;
+    }
+    bool ok = row.put(PyDict_GET_SIZE(d));
+    Py_ssize_t pos = 0;
+    PyObject *key, *value;
+    while (ok && PyDict_Next(d, &pos, &key, &value)) ok = row.put((int64_t)(intptr_t)key) && describe(value, false, row, keep);
+    Py_DECREF(d);
+    return ok;
+}
+
+bool describe_all(PyObject* objects, Row& row, PyObject* keep) {
+    for (Py_ssize_t i = 0; i < PyTuple_GET_SIZE(objects); ++i)
+        if (!describe(PyTuple_GET_ITEM(objects, i), true, row, keep)) return false;
+    return true;
+}
+
+// snapshot(objects, keep) -> the row as bytes; the list `keep` receives the objects
+PyObject* snapshot(PyObject*, PyObject* args) {
+    PyObject *objects, *keep;
+    if (!PyArg_ParseTuple(args, "O!O!", &PyTuple_Type, &objects, &PyList_Type, &keep)) return nullptr;
+    try {
+        std::string out;
+        Row row{&out, nullptr, nullptr};
+        if (!describe_all(objects, row, keep)) return nullptr;
+        return PyBytes_FromStringAndSize(out.data(), (Py_ssize_t)out.size());
+    } catch (const std::exception& e) {
+        return PyErr_Format(PyExc_RuntimeError, "%s", e.what());
+    }
+}
+
+// unchanged(objects, row) -> True while nothing was replaced or moved since the snapshot (whose objects live)
+PyObject* unchanged(PyObject*, PyObject* args) {
+    PyObject *objects, *bytes;
+    if (!PyArg_ParseTuple(args, "O!O!", &PyTuple_Type, &objects, &PyBytes_Type, &bytes)) return nullptr;
+    try {
+        const char* p = PyBytes_AS_STRING(bytes);
+        Row row{nullptr, p, p + PyBytes_GET_SIZE(bytes)};
+        return PyBool_FromLong(describe_all(objects, row, nullptr) && row.at == row.end);
+    } catch (const std::exception& e) {
+        return PyErr_Format(PyExc_RuntimeError, "%s", e.what());
+    }
+}
+
+PyMethodDef methods[] = {{"launcher", make_launcher, METH_VARARGS, nullptr}, {"snapshot", snapshot, METH_VARARGS, nullptr}, {"unchanged", unchanged, METH_VARARGS, nullptr}, {}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_host", nullptr, -1, methods};
 
 }  // namespace

@@ -115,3 +115,55 @@ def test_layers_that_differ_inside(kind, T):
         got = chain.forward(gu.to_dev(x))
         torch.cuda.synchronize()
         assert gu.rel_err(gu.to_f64(got), ref) <= 2e-2
+
+
+@pytest.mark.parametrize("op", ["monarch", "blast"])
+@pytest.mark.parametrize("T", [2, 33])
+def test_replaced_parts_are_used(op, T):
+    """A pass uses the factors, buffers and settings that the chain holds at the time, also after passes with others: those
+    of a pass step by step (bit for bit where the native chain runs the same steps)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    from paper_2512_20861_amd.chain import DeviceChain
+    layers = bi.chain_layers(op, n_layers=2, hidden=512, mlp=768, params=PARAMS[op], dtype="bf16")
+    others = bi.chain_layers(op, n_layers=2, hidden=512, mlp=768, params=PARAMS[op], dtype="bf16", seed=77)
+    x = gu.to_dev(bi.activations(T, 512, "bf16"))
+    chain, spare = DeviceChain(layers, T, eps=oc.EPS), DeviceChain(others, T, eps=oc.EPS)
+    factor = "R" if op == "monarch" else "U"
+
+    def agrees(passes=4):
+        want = chain.forward(x, record=True)[0].clone()
+        for _ in range(passes):
+            chain.h.fill_(float("nan"))
+            got = chain.forward(x)
+            assert got is chain.h
+            assert torch.equal(got, want) if T > 4 else gu.rel_err(gu.to_f64(got), gu.to_f64(want)) <= 2e-2
+        return want
+
+    handle = chain._native
+    seen = [agrees()]
+    assert handle and chain._native is handle
+    lin, other = chain.layers[1]["o"], spare.layers[1]["o"]
+    old = getattr(lin, factor)
+
+    def changes():
+        setattr(lin, factor, getattr(other, factor)); yield
+        getattr(lin, factor).data = old.clone(); yield                    # the same tensor object, other memory
+        chain.layers[0]["down"] = spare.layers[0]["down"]; yield
+        chain.groups[1] = spare.groups[1]; yield
+        chain.eps = 0.5; yield
+    for _ in changes():
+        seen.append(agrees())
+        assert chain._native                             # made anew
+        assert not torch.equal(seen[-1], seen[-2])
+    for name in ("h", "n", "ws", "m"):                   # buffers of the same layout: the same result in the new ones
+        setattr(chain, name, torch.empty_like(getattr(chain, name)))
+        assert torch.equal(agrees(), seen[-1])
+    for i in range(3):                                   # another factor for every pass
+        setattr(lin, factor, (old, getattr(other, factor))[i % 2])
+        agrees(1)
+    lin.r = lin.r // 2                                   # refused by the call list, and so by a pass
+    for _ in range(3):
+        with pytest.raises(ValueError):
+            chain.forward(x)

@@ -53,3 +53,40 @@ def test_argument_forms_agree(T):
     assert e.value.status == B.ERR_WORKSPACE
     with pytest.raises(ValueError):
         B.monarch_forward(X, R, L[:, :40], Y, 4, 64, workspace=ws)
+
+
+def test_snapshot_tells_what_was_replaced():
+    """unchanged() until one of the ways to put another tensor, address, layout or number in a part's place."""
+    B.lib()
+
+    class Part:
+        def __init__(self):
+            self.w, self.n = torch.arange(24.0).reshape(4, 6), 1024
+
+    parts, eps, kept = [Part(), Part()], 0.5, []
+    row = B.snapshot((*parts, eps), kept)
+    same = lambda: B.unchanged((*parts, eps), row)
+    assert all(same() for _ in range(20))
+    part, w, n = parts[0], parts[0].w, parts[0].n
+    data, other = w.data, parts[1]
+    assert any(o is w for o in kept)
+
+    def change_and_back():
+        part.w = w.clone(); yield
+        part.w = w; yield
+        w.data = w.clone(); yield                        # the same tensor object
+        w.data = data; yield
+        w.t_(); yield
+        w.t_(); yield
+        part.n = n + 1; yield
+        part.n = n; yield
+        parts[1] = Part(); yield
+        parts[1] = other; yield
+        parts.append(w); yield
+        parts.pop(); yield
+    assert [same() for _ in change_and_back()] == [False, True] * 6
+    w.add_(1.0)
+    assert same()                                        # values are not looked at
+    assert not B.unchanged((*parts, n), row) and not B.unchanged((*parts,), row)
+    with pytest.raises(TypeError):
+        B.snapshot(parts, [])
