@@ -96,8 +96,9 @@ struct GemmDesc {
     void* C; int64_t c_rs; int64_t c_gs; int c_div; int64_t c_hi; int64_t c_lo;
     int64_t M; int N; int K; int G;
     // k_align: the batch entries' windows [g K, (g + 1) K) of A's rows are read in whole steps of 64 elements, i.e. from the multiple of 64
-    // at or below their start to the one at or above their end (a_gs is not used; a_rs is a multiple of 64), against rows of B that hold zeros
-    // where the window is a neighbour's (blast_chunk's Va). For tiles of gemm_whole_line_tiles only.
+    // at or below their start to the one at or above their end (a_gs is not used; a_rs is a multiple of 64), against rows of B with the
+    // same shift (blast_chunk's Va). Where the window is a neighbour's both operands are zero (a neighbour's infinity times zero would be
+    // NaN); 8 | K, so that such pieces of 8 are whole. For tiles of gemm_whole_line_tiles only.
     int k_align;
     float* split_scratch; size_t split_scratch_bytes;   // optional: room for fp32 partial tiles of a split contraction
     int c_fp8;                         // C is stored as 8-bit floats (E4M3, round to nearest even, clamped to +-448): one byte per

@@ -471,6 +471,36 @@ __device__ __forceinline__ void deep_load_offsets(const GemmDesc& d, int wave, i
     }
 }
 
+// k_align: the window of a batch entry in A's rows, in steps of 64 from the multiple of 64 at or below its start; what it
+// holds of the neighbours is [0, lo) of the first step and [hi, 64) of the last one.
+struct Window {
+    int first, nk, lo, hi;
+    __device__ Window(int g, int K) {
+        const int c0 = (g * K) >> 6, c1 = ((g + 1) * K + 63) >> 6;
+        first = c0 * 64;
+        nk = c1 - c0;
+        lo = g * K - first;
+        hi = (g + 1) * K - (c1 - 1) * 64;
+    }
+};
+// Zeros in place of the 16-byte pieces [from, to) of the BM A rows of a stage that has landed, and a barrier: their
+// product with the zeros of B would be NaN for a neighbour's infinity. In LDS, once per end of a window: a choice of
+// address per lane behind every load cost the 11008 -> 4096 layer 5 % at 8192 tokens. addr(row): the row's LDS address.
+template <class C, int BM, class Addr>
+__device__ __forceinline__ void clear_pieces(int from, int to, Addr addr) {
+    if (from == to) return;                             // uniform
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    constexpr int SWEEP = C::THREADS / C::PPR;          // rows per sweep; rows a sweep apart are swizzled alike
+    static_assert(BM % SWEEP == 0 && (SWEEP >> C::SH) % C::PPR == 0, "a thread keeps its piece");
+    const int row = threadIdx.x / C::PPR, p = threadIdx.x % C::PPR;
+    const unsigned slot = (unsigned)(p ^ ((row >> C::SH) & (C::PPR - 1))) * 16u;
+    if (p >= from && p < to)
+#pragma unroll
+        for (int r = 0; r < BM; r += SWEEP)             // (a store the compiler can see would wait for all direct loads)
+            asm volatile("ds_write_b128 %0, %1" :: "v"(addr(row + r) + slot), "v"(zero) : "memory");
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // ---------------------------------------------------------------------------------------------
 // The 256 x 256 tile in steps of 64 contraction indices. The L2 serves one request per channel and clock whether
 // it asks for 64 or for 128 bytes of a line (measured: 260 G requests/s over the chip either way), so the 32-deep
@@ -484,7 +514,8 @@ __device__ __forceinline__ void deep_load_offsets(const GemmDesc& d, int wave, i
 // while its sibling keeps the matrix pipe full (measured: an address add per load made the load phase three times
 // longer): the loop body therefore has NO vector ALU work besides the MFMAs - loads address as scalar base +
 // a fixed 32-bit lane offset, fragment reads use addresses computed once per stage and k16 step.
-template <bool TAIL>
+// EDGE: 0, the contraction index is whole steps; 1, its last step is partial; 2, k_align.
+template <int EDGE>
 __global__ __launch_bounds__(512) void gemm_wide_kernel(GemmDesc d, int tiles_m, int tiles_n, int cvec, int order) {
     constexpr int BM = 256, BN = 256, WGN = 4;
     using C = DeepCfg<BM, BN, 2, WGN, 64, 2>;
@@ -497,18 +528,14 @@ __global__ __launch_bounds__(512) void gemm_wide_kernel(GemmDesc d, int tiles_m,
     workgroup_tile(d, tiles_m, tiles_n, order, g, tile_m, tile_n);
     const int64_t m0 = (int64_t)tile_m * BM;
     const int n0 = tile_n * BN;
-    int nk = (d.K + C::BK - 1) / C::BK;
-    int64_t a_first = (int64_t)g * d.a_gs;              // first contraction index of this batch entry in A's rows
-    if (C::BK == 64 && d.k_align) {
-        const int c0 = (g * d.K) >> 6;
-        nk = (((g + 1) * d.K + 63) >> 6) - c0;
-        a_first = (int64_t)c0 * 64;
-    }
+    const Window win(g, d.K);
+    const int nk = EDGE == 2 ? win.nk : (d.K + C::BK - 1) / C::BK;
+    const int64_t a_first = EDGE == 2 ? (int64_t)win.first : (int64_t)g * d.a_gs;   // first contraction index of this batch entry in A's rows
     const unsigned char* Abase = (const unsigned char*)((const bf16_t*)d.A + a_first + m0 * d.a_rs);
     const unsigned char* Bbase = (const unsigned char*)((const bf16_t*)d.B + (int64_t)g * d.b_gs);
     unsigned off[C::LPW];
     bool bad[C::LPW];
-    deep_load_offsets<C, BM, TAIL>(d, wave, lane, m0, n0, nk, off, bad);
+    deep_load_offsets<C, BM, EDGE == 1>(d, wave, lane, m0, n0, nk, off, bad);
     const bool on_a = C::RPL * C::LPW * wave < BM;      // this wavefront's loads bring A rows (uniform)
 
     int kf = 0;                                         // step under the fetch cursor (uniform)
@@ -518,7 +545,7 @@ __global__ __launch_bounds__(512) void gemm_wide_kernel(GemmDesc d, int tiles_m,
     auto issue = [&](int stage_off, auto H) {
         constexpr int h = decltype(H)::value;
         asm volatile("" : "+v"(off[h]));                // the 32-bit offset stays a register operand: scalar base + lane offset addressing, no address arithmetic
-        if (TAIL && kf == nk - 1) {
+        if (EDGE == 1 && kf == nk - 1) {
             // A branch, not a select: only the fetch of the last step pays for the per-lane choice. (The non-temporal
             // hint does no harm there and keeps the compiler from merging the two loads into one with a selected address.)
             unsigned o = off[h];
@@ -569,8 +596,11 @@ __global__ __launch_bounds__(512) void gemm_wide_kernel(GemmDesc d, int tiles_m,
         static_for<C::MI>([&](auto I) { af[ks & 1][decltype(I)::value] = lds_read_b128<decltype(I)::value * 32 * C::RB>(fa[st][ks]); });
         static_for<C::NI>([&](auto J) { bfr[ks & 1][decltype(J)::value] = lds_read_b128<decltype(J)::value * 32 * C::RB>(fb[st][ks]); });
     };
-    // one step on stage ST
-    auto step = [&](auto ST) {
+    auto clear = [&](int stage_off, int from, int to) {
+        clear_pieces<C, BM>(from, to, [&](int row) { return lds0 + stage_off + row * C::RB; });
+    };
+    // step kt, on stage ST
+    auto step = [&](auto ST, int kt) {
         constexpr int st = decltype(ST)::value;
         static_for<C::KS>([&](auto KSC) {
             constexpr int ks = decltype(KSC)::value, b = ks & 1;
@@ -597,6 +627,7 @@ __global__ __launch_bounds__(512) void gemm_wide_kernel(GemmDesc d, int tiles_m,
                 if constexpr (ks == C::KS - 1 && q == C::MI * C::NI / 2 - 1) {
                     // every wavefront is past its last read of this stage; the other stage has landed (own loads: vmcnt; the others': barrier)
                     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+                    if (EDGE == 2 && kt == nk - 2) clear((1 - st) * C::STAGE, win.hi >> 3, C::PPR);
                     read_frags(std::integral_constant<int, 1 - st>{}, std::integral_constant<int, 0>{});
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -607,13 +638,14 @@ __global__ __launch_bounds__(512) void gemm_wide_kernel(GemmDesc d, int tiles_m,
     static_for<C::LPW>([&](auto H) { issue(0, H); });
     advance();
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    if (EDGE == 2) clear(0, 0, win.lo >> 3);
     read_frags(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
 #pragma unroll 1
     for (int kt = 0; kt + 1 < nk; kt += 2) {            // (stages alternate: two steps per trip keep them compile-time constants)
-        step(std::integral_constant<int, 0>{});
-        step(std::integral_constant<int, 1>{});
+        step(std::integral_constant<int, 0>{}, kt);
+        step(std::integral_constant<int, 1>{}, kt + 1);
     }
-    if (nk & 1) step(std::integral_constant<int, 0>{});
+    if (nk & 1) step(std::integral_constant<int, 0>{}, nk - 1);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the fragments read ahead behind the last step are not used
 #pragma unroll
     for (int i = 0; i < C::MI; ++i) asm volatile("" :: "v"(af[0][i]));     // (their registers stay theirs until they have arrived)
@@ -633,7 +665,7 @@ __global__ __launch_bounds__(512) void gemm_wide_kernel(GemmDesc d, int tiles_m,
 // trip keep the stage a compile-time constant. Against the same tiles with per-step address arithmetic and the
 // barrier at the step's start: dense 4096 x 4096 at 128 / 512 / 2048 tokens 15.7 -> 13.9, 25.9 -> 24.2,
 // 64.9 -> 61.2 us.
-template <int BM, int BN, int WGM, int WGN, int BKT, int NS, bool TAIL>
+template <int BM, int BN, int WGM, int WGN, int BKT, int NS, int EDGE>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_line_kernel(GemmDesc d, int tiles_m, int tiles_n, int cvec, int order) {
     using C = DeepCfg<BM, BN, WGM, WGN, BKT, NS>;
     constexpr int MFMAS = C::MI * C::NI, HALF = (MFMAS + 1) / 2;
@@ -647,18 +679,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_line_kernel(GemmDesc d, i
     workgroup_tile(d, tiles_m, tiles_n, order, g, tile_m, tile_n);
     const int64_t m0 = (int64_t)tile_m * BM;
     const int n0 = tile_n * BN;
-    int nk = (d.K + C::BK - 1) / C::BK;
-    int64_t a_first = (int64_t)g * d.a_gs;              // first contraction index of this batch entry in A's rows
-    if (C::BK == 64 && d.k_align) {
-        const int c0 = (g * d.K) >> 6;
-        nk = (((g + 1) * d.K + 63) >> 6) - c0;
-        a_first = (int64_t)c0 * 64;
-    }
+    const Window win(g, d.K);
+    const int nk = EDGE == 2 ? win.nk : (d.K + C::BK - 1) / C::BK;
+    const int64_t a_first = EDGE == 2 ? (int64_t)win.first : (int64_t)g * d.a_gs;   // first contraction index of this batch entry in A's rows
     const unsigned char* Abase = (const unsigned char*)((const bf16_t*)d.A + a_first + m0 * d.a_rs);
     const unsigned char* Bbase = (const unsigned char*)((const bf16_t*)d.B + (int64_t)g * d.b_gs);
     unsigned off[C::LPW];
     bool bad[C::LPW];
-    deep_load_offsets<C, BM, TAIL>(d, wave, lane, m0, n0, nk, off, bad);
+    deep_load_offsets<C, BM, EDGE == 1>(d, wave, lane, m0, n0, nk, off, bad);
 
     int kf = 0;                                         // step under the fetch cursor (uniform)
     int a_pos = 0;                                      // position inside the current segment of a segmented contraction index
@@ -670,7 +698,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_line_kernel(GemmDesc d, i
         const bool isa = C::RPL * (C::LPW * wave + h) < BM;               // uniform
         asm volatile("" : "+v"(off[h]));                // the 32-bit offset stays a register operand: scalar base + lane offset addressing, no address arithmetic
         const unsigned char* base = isa ? asrc : bsrc;
-        if (TAIL && kf == nk - 1) {                     // (a branch, a different cache hint and its own copy of the offset, as in gemm_wide_kernel)
+        if (EDGE == 1 && kf == nk - 1) {                     // (a branch, a different cache hint and its own copy of the offset, as in gemm_wide_kernel)
             unsigned o = off[h];
             asm volatile("" : "+v"(o));
             __builtin_amdgcn_global_load_lds(BLR_GPTR(bad[h] ? zero_piece : base + o), BLR_LPTR(smem + ((C::LPW * wave + h) * NS + st) * 1024), 16, 0, 2);
@@ -721,8 +749,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_line_kernel(GemmDesc d, i
         static_for<C::MI>([&](auto I) { af[ks & 1][decltype(I)::value] = lds_read_b128<decltype(I)::value * 32 * C::RB * NS + st * 1024>(fa[ks]); });
         static_for<C::NI>([&](auto J) { bfr[ks & 1][decltype(J)::value] = lds_read_b128<decltype(J)::value * 32 * C::RB * NS + st * 1024>(fb[ks]); });
     };
-    // one step on stage ST: fetches the step NS - 1 ahead into the stage that was computed on one step ago
-    auto step = [&](auto ST) __attribute__((always_inline)) {
+    auto clear = [&](int st, int from, int to) __attribute__((always_inline)) {
+        clear_pieces<C, BM>(from, to, [&](int row) { return lds0 + st * 1024 + (row / C::RPL) * (NS * 1024) + (row % C::RPL) * C::RB; });
+    };
+    // step kt, on stage ST: fetches the step NS - 1 ahead into the stage that was computed on one step ago
+    auto step = [&](auto ST, int kt) __attribute__((always_inline)) {
         constexpr int st = decltype(ST)::value;
         static_for<C::KS>([&](auto KSC) {
             constexpr int ks = decltype(KSC)::value, b = ks & 1;
@@ -749,6 +780,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_line_kernel(GemmDesc d, i
                 if constexpr (ks == C::KS - 1 && q == HALF - 1) {
                     // every wavefront is past its last read of this stage; the next stage has landed (own loads: vmcnt; the others': barrier)
                     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(C::LPW * (NS - 2)) : "memory");
+                    if (EDGE == 2 && kt == nk - 2) clear((st + 1) % NS, win.hi >> 3, C::PPR);
                     read_frags(std::integral_constant<int, (st + 1) % NS>{}, std::integral_constant<int, 0>{});
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -761,12 +793,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_line_kernel(GemmDesc d, i
         advance();
     });
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(C::LPW * (NS - 2)) : "memory");
+    if (EDGE == 2) clear(0, 0, win.lo >> 3);
     read_frags(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
     int kt = 0;
 #pragma unroll 1
-    for (; kt + NS <= nk; kt += NS) static_for<NS>([&](auto S) { step(S); });      // (NS steps per trip keep the stage a compile-time constant)
+    for (; kt + NS <= nk; kt += NS) static_for<NS>([&](auto S) { step(S, kt + decltype(S)::value); });      // (NS steps per trip keep the stage a compile-time constant)
     const int rem = nk - kt;
-    static_for<NS - 1>([&](auto S) { if (decltype(S)::value < rem) step(S); });
+    static_for<NS - 1>([&](auto S) { if (decltype(S)::value < rem) step(S, kt + decltype(S)::value); });
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // the repeated loads of the last steps and the fragments read ahead behind the last one
 #pragma unroll
     for (int i = 0; i < C::MI; ++i) asm volatile("" :: "v"(af[0][i]));     // (their registers stay theirs until they have arrived)
@@ -911,34 +944,31 @@ hipError_t launch_dma(const GemmDesc& d, hipStream_t s, bool allow_split = false
 hipError_t launch_wide(const GemmDesc& d, hipStream_t s) {
     using C = DeepCfg<256, 256, 2, 4, 64, 2>;
     static LdsLimitOnce lds_limit;
-    if (hipError_t e = lds_limit.set({(const void*)gemm_wide_kernel<false>, (const void*)gemm_wide_kernel<true>}, C::LDS_BYTES); e != hipSuccess) return e;
+    if (hipError_t e = lds_limit.set({(const void*)gemm_wide_kernel<0>, (const void*)gemm_wide_kernel<1>, (const void*)gemm_wide_kernel<2>}, C::LDS_BYTES); e != hipSuccess) return e;
     const int tiles_m = (int)((d.M + 255) / 256);
     const int tiles_n = (d.N + 255) / 256;
     const bool vec = c_map_vectorizes(d);
     dim3 grid((unsigned)((int64_t)tiles_m * tiles_n * d.G), 1u, 1u);
     const int order = launch_tile_order(d, vec);
-    if (d.K % 64 && !d.k_align)
-        hipLaunchKernelGGL((gemm_wide_kernel<true>), grid, dim3(C::THREADS), C::LDS_BYTES, s, d, tiles_m, tiles_n, vec ? 1 : 0, order);
-    else
-        hipLaunchKernelGGL((gemm_wide_kernel<false>), grid, dim3(C::THREADS), C::LDS_BYTES, s, d, tiles_m, tiles_n, vec ? 1 : 0, order);
+    auto* kernel = d.k_align ? gemm_wide_kernel<2> : d.K % 64 ? gemm_wide_kernel<1> : gemm_wide_kernel<0>;
+    hipLaunchKernelGGL(kernel, grid, dim3(C::THREADS), C::LDS_BYTES, s, d, tiles_m, tiles_n, vec ? 1 : 0, order);
     return hipGetLastError();
 }
 
 template <int BM, int BN, int WGM, int WGN, int BK, int NS>
 hipError_t launch_line(const GemmDesc& d, hipStream_t s) {
     using C = DeepCfg<BM, BN, WGM, WGN, BK, NS>;
+    constexpr int WINDOW = BK == 64 ? 2 : 0;            // (k_align is for steps of 64)
     static LdsLimitOnce lds_limit;
-    if (hipError_t e = lds_limit.set({(const void*)gemm_line_kernel<BM, BN, WGM, WGN, BK, NS, false>,
-                                      (const void*)gemm_line_kernel<BM, BN, WGM, WGN, BK, NS, true>}, C::LDS_BYTES); e != hipSuccess) return e;
+    if (hipError_t e = lds_limit.set({(const void*)gemm_line_kernel<BM, BN, WGM, WGN, BK, NS, 0>, (const void*)gemm_line_kernel<BM, BN, WGM, WGN, BK, NS, 1>,
+                                      (const void*)gemm_line_kernel<BM, BN, WGM, WGN, BK, NS, WINDOW>}, C::LDS_BYTES); e != hipSuccess) return e;
     const int tiles_m = (int)((d.M + BM - 1) / BM);
     const int tiles_n = (d.N + BN - 1) / BN;
     const bool vec = c_map_vectorizes(d);
     dim3 grid((unsigned)((int64_t)tiles_m * tiles_n * d.G), 1u, 1u);
     const int order = launch_tile_order(d, vec);
-    if (d.K % BK && !d.k_align)
-        hipLaunchKernelGGL((gemm_line_kernel<BM, BN, WGM, WGN, BK, NS, true>), grid, dim3(C::THREADS), C::LDS_BYTES, s, d, tiles_m, tiles_n, vec ? 1 : 0, order);
-    else
-        hipLaunchKernelGGL((gemm_line_kernel<BM, BN, WGM, WGN, BK, NS, false>), grid, dim3(C::THREADS), C::LDS_BYTES, s, d, tiles_m, tiles_n, vec ? 1 : 0, order);
+    auto* kernel = d.k_align ? gemm_line_kernel<BM, BN, WGM, WGN, BK, NS, WINDOW> : d.K % BK ? gemm_line_kernel<BM, BN, WGM, WGN, BK, NS, 1> : gemm_line_kernel<BM, BN, WGM, WGN, BK, NS, 0>;
+    hipLaunchKernelGGL(kernel, grid, dim3(C::THREADS), C::LDS_BYTES, s, d, tiles_m, tiles_n, vec ? 1 : 0, order);
     return hipGetLastError();
 }
 

@@ -65,3 +65,18 @@ def test_coupling_of_absent_blocks(T, b):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     _blast(T, 64, 40, b, 128, [(1, b * 64 - 1)], 0)
+
+
+@pytest.mark.parametrize("T,q,b,r", [
+    (1300, 344, 8, 264),          # 128 x 128 and 128 x 192 tiles
+    (300, 152, 16, 640),          # one round
+    (500, 344, 16, 640),          # 256 x 128
+    (700, 344, 16, 1024),         # 256 x 256 or 192 x 128
+])
+def test_windows_of_input_blocks(T, q, b, r):
+    """Input blocks read in 64-column chunks of the input row: infinities in the first and the last column of a block, which
+    its neighbours' windows hold too."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    _blast(T, q, 16, b, r, [(0, q), (1, q - 1), (T // 2, (b - 1) * q), (T - 1, b * q - 1), (T - 2, 0)], gu.B.BLAST_THREE_KERNELS)
