@@ -36,7 +36,7 @@ struct MonarchF32Args {
     int tpl;                         // 16-row tiles of one input block's rank indices
     int qt;                          // outputs per workgroup (a multiple of 16)
     int out_step, out_block;         // output j of block k is element k out_block + j out_step of its row
-    int xstr, zstr;                  // LDS row strides in floats: n_in + 4 and w2 + 4, the last four are zeros
+    int xstr, zstr;                  // LDS row strides in floats
 };
 
 // DEEP: two items in flight behind the one in use, in three register buffers; else one item at a time (a wavefront has
@@ -83,23 +83,35 @@ __global__ __launch_bounds__(512) void monarch_f32_kernel(MonarchF32Args a) {
         }
     };
     f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;     // (two chains of dependent MFMAs)
-    auto multiply = [&](const Phase& ph, const Cursor& c, const float* tok, const float* zero, const f32x4 (&w)[4]) {
+    auto multiply = [&](const Phase& ph, const Cursor& c, const float* tok, const f32x4 (&w)[4]) {
+        if (c.k0 + 64 <= ph.K) {                        // uniform: a whole item needs no selects (256 x 256, 8 tokens: 4.2 -> 3.9 us; 1024 x 1024: 16.5 -> 15.5)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < 4; ++u) {
+                const f32x4 x = *(const f32x4*)(tok + c.k0 + u * 16 + kg * 4);
+#pragma unroll
+                for (int e = 0; e < 4; e += 2) {
+                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][e], x[e], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][e + 1], x[e + 1], acc1, 0, 0, 0);
+                }
+            }
+            return;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {                   // past K both operands are zero (an infinity times zero would be NaN)
             const int kk = c.k0 + u * 16 + kg * 4;
             const bool in = kk < ph.K;
-            const f32x4 x = *(const f32x4*)(in ? tok + kk : zero);            // (both operands are zero past K: an infinity times zero would be NaN)
+            const f32x4 x = *(const f32x4*)(tok + (in ? kk : ph.K - 4));
 #pragma unroll
             for (int e = 0; e < 4; e += 2) {
-                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? w[u][e] : 0.f, x[e], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? w[u][e + 1] : 0.f, x[e + 1], acc1, 0, 0, 0);
+                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? w[u][e] : 0.f, in ? x[e] : 0.f, acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? w[u][e + 1] : 0.f, in ? x[e + 1] : 0.f, acc1, 0, 0, 0);
             }
         }
     };
-    // every item of a phase: multiplied with its part of this lane's token (`zero`: the zeros behind it); done(l, first row of the lane, sum) per tile.
-    auto run = [&](const Phase& ph, Cursor c, const float* tok, int tok_block, const float* zero, f32x4 (&w)[4], auto done) {
+    // every item of a phase: multiplied with its part of this lane's token; done(l, first row of the lane, sum) per tile.
+    auto run = [&](const Phase& ph, Cursor c, const float* tok, int tok_block, f32x4 (&w)[4], auto done) {
         auto use = [&](const f32x4 (&v)[4]) {
-            multiply(ph, c, tok + c.l * tok_block, zero, v);
+            multiply(ph, c, tok + c.l * tok_block, v);
             const int l = c.l, sub = c.sub;
             next(ph, c);
             if (c.k0 == 0) {
@@ -139,7 +151,6 @@ __global__ __launch_bounds__(512) void monarch_f32_kernel(MonarchF32Args a) {
     settle(p2, c2);
     f32x4 w1[4], w2[4];
     fetch(p1, c1, w1);
-    if (tid < 2 * FM_TT) *(f32x4*)(tid < FM_TT ? Xs + tid * a.xstr + a.n_in : Zs + (tid - FM_TT) * a.zstr + a.w2) = f32x4{0.f, 0.f, 0.f, 0.f};
     {                                                   // X tile: a wavefront moves whole rows, four loads in flight
         const int pieces = a.n_in >> 2, last = a.T - t0 > FM_TT ? FM_TT - 1 : (int)(a.T - t0) - 1;
         const int row = tid >> 5;                       // 32 lanes per row; all 16 rows at once with 8 wavefronts, 8 with 4
@@ -158,13 +169,13 @@ __global__ __launch_bounds__(512) void monarch_f32_kernel(MonarchF32Args a) {
     }
     fetch(p2, c2, w2);
     __syncthreads();
-    run(p1, c1, Xs + l16 * a.xstr, a.p, Xs + l16 * a.xstr + a.n_in, w1, [&](int l, int row, f32x4 v) {
+    run(p1, c1, Xs + l16 * a.xstr, a.p, w1, [&](int l, int row, f32x4 v) {
         if (row < a.rp) *(f32x4*)(Zs + l16 * a.zstr + l * a.rp + row) = v;
     });
     __syncthreads();                                    // Z'_k is complete
     const bool live = t0 + l16 < a.T;
     float* y = a.Y + (t0 + l16) * a.n_out + (int64_t)k * a.out_block + (int64_t)j0 * a.out_step;
-    run(p2, c2, Zs + l16 * a.zstr, 0, Zs + l16 * a.zstr + a.w2, w2, [&](int, int row, f32x4 v) {
+    run(p2, c2, Zs + l16 * a.zstr, 0, w2, [&](int, int row, f32x4 v) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             if (live && row + e < nj) y[(int64_t)(row + e) * a.out_step] = v[e];
