@@ -152,6 +152,7 @@ hipError_t launch_gemm_skinny_from(int kind, const GemmDesc& d, const SkinnySour
 // the same kernel over tiles of 32 tokens (the weights are streamed once per tile): for products with
 // too few 64 x 64 tiles to fill the chip and a long contraction index
 bool skinny_gemm_tiled_supported(const GemmDesc& d);
+int64_t skinny_workgroups(const GemmDesc& d);   // of that launch
 
 // Monarch (b1 input blocks, b2 output blocks, per-block rank rp; low-rank is b1 = b2 = 1) in one kernel
 // for narrow layers: the intermediate stays on chip. Needs 16 | rp, 32 | n_in/b1, 32 | b1 rp and a token

@@ -1174,7 +1174,7 @@ hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s) {
     // and 1152-wide layers: 2 us less per call in graph replay; with K = 4096 the split parts, which
     // put more workgroups on the stream, are as fast or faster).
     if (d.split_scratch && split_plan(tiles(64, 64), d.K).nsplit > 1 && skinny_gemm_tiled_supported(d)) {
-        const int64_t wgs = ((d.M + 31) / 32) * ((d.N + 15) / 16) * d.G;
+        const int64_t wgs = skinny_workgroups(d);
         const double est_us = (double)((wgs + 255) / 256) * (d.K * 96 / 55e3 + 1.0);
         // ... or under about 9 us when one round of workgroups covers at least half of the chip (4096 x 1024
         // weights at 64 ... 128 tokens: 10 us against 12-13 us; with 32 workgroups the split parts win)
@@ -1192,7 +1192,7 @@ hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s) {
     // 8192 -> 2048: 55.5 -> 17.4 us). Taken when its estimate (rounds of workgroups x the time to
     // stream 96 K bytes at 55 GB/s) is below that walk by a margin (level estimates went to the tiles).
     if (skinny_gemm_tiled_supported(d)) {
-        const int64_t wgs = ((d.M + 31) / 32) * ((d.N + 15) / 16) * d.G;
+        const int64_t wgs = skinny_workgroups(d);
         const double est_us = (double)((wgs + 255) / 256) * (d.K * 96 / 55e3 + 1.0);
         if (est_us < 0.85 * ((d.K + 31) / 32 * 0.17 + 3.0)) return launch_gemm_skinny(d, s);
     }

@@ -40,6 +40,7 @@ struct SkinnyArgs {
     int64_t a_gs, a_rs, b_gs, c_gs, c_rs, b_s, c_s, c_i;
     unsigned b_i;                     // row pitch of B inside a segment (elements)
     int M, n, K;
+    int nall;                         // PACK: columns of all segments
     int a_seg;
     int64_t a_seg_stride;
     int kper;                         // contraction indices per wavefront, a multiple of 32
@@ -188,12 +189,13 @@ __device__ __forceinline__ void source_rows(const SkinnySource& q, int M, int K,
 // MT: 16-token tiles (M <= 16 MT); NW: wavefronts; TAIL: K is no multiple of 32
 // ROWS: every wavefront owns 16 weight rows and the whole contraction index instead of a part of it (computed rows only:
 // the rows serve 16 NW outputs then, and there are no partial sums to add)
-template <int MT, int NW, bool TAIL, int SRC, bool ROWS>
+// PACK: a workgroup's 16 weight rows run across segments shorter than 16
+template <int MT, int NW, bool TAIL, int SRC, bool ROWS, bool PACK>
 __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, SkinnySource src) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     constexpr int XL = SRC == kSrcInput ? MT : 0;        // token rows that come as direct loads, per step
     constexpr int SLOT = (1 + XL) * 1024;                // 16 weight rows and 16 XL token rows of 64 bytes
-    static_assert(SRC == kSrcInput ? !ROWS : MT == 1, "computed rows: a handful of tokens");
+    static_assert(SRC == kSrcInput ? !ROWS : MT == 1 && !PACK, "computed rows: a handful of tokens");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i0 = (ROWS ? blockIdx.x * NW + wave : blockIdx.x) * SK_BN, s = blockIdx.y;
@@ -208,8 +210,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, Skin
     const int kw = ROWS ? 0 : wave * a.kper;
     const unsigned char* B = (const unsigned char*)(a.B + g * a.b_gs + s * a.b_s);
     const unsigned char* A = (const unsigned char*)(a.A + g * a.a_gs + m_base * a.a_rs);
-    const int row = i0 + lrow < a.n ? i0 + lrow : a.n - 1;          // rows past the segment repeat its last one; never stored
-    unsigned woff = (unsigned)row * a.b_i, xoff[MT];
+    const int rows_n = PACK ? a.nall : a.n, row = i0 + lrow < rows_n ? i0 + lrow : rows_n - 1;   // rows past the segment repeat its last one; never stored
+    unsigned woff = PACK ? (unsigned)(row % a.n) * a.b_i + (unsigned)(row / a.n) * (unsigned)a.b_s : (unsigned)row * a.b_i, xoff[MT];
 #pragma unroll
     for (int mt = 0; mt < XL; ++mt) {
         const int m = mt * 16 + lrow, left = a.M - m_base - 1;
@@ -319,17 +321,19 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, Skin
     for (int mt = 0; mt < MT; ++mt)
         *(f32x4*)(part + ((wave * MT + mt) * 16 + l16) * PSTR + 4 * kg) = acc[mt];
     __syncthreads();
+    const int c = tid & 15, ci = i0 + c;                // (64 NW is a multiple of 16: a thread keeps its column)
+    bf16_t* Cc = a.C + g * a.c_gs + (PACK ? (ci / a.n) * a.c_s + (ci % a.n) * a.c_i : s * a.c_s + ci * a.c_i);
     for (int o = tid; o < MT * 256; o += 64 * NW) {
-        const int m = o >> 4, c = o & 15;
-        if (m_base + m >= a.M || i0 + c >= a.n) continue;
+        const int m = o >> 4;
+        if (m_base + m >= a.M || ci >= rows_n) continue;
         float v = part[m * PSTR + c];
 #pragma unroll
         for (int w = 1; w < NW; ++w) v += part[(w * MT * 16 + m) * PSTR + c];
-        a.C[(m_base + m) * a.c_rs + g * a.c_gs + s * a.c_s + (i0 + c) * a.c_i] = float_to_bf16(v);
+        Cc[(m_base + m) * a.c_rs] = float_to_bf16(v);
     }
 }
 
-template <int MT, int NW, int SRC, bool ROWS = false>
+template <int MT, int NW, int SRC, bool ROWS = false, bool PACK = false>
 hipError_t launch_skinny(SkinnyArgs& a, const SkinnySource& src, dim3 grid, hipStream_t s) {
     constexpr int SLOT = (1 + (SRC == kSrcInput ? MT : 0)) * 1024;
     const int nk = (a.K + 31) / 32, per = ROWS ? nk : (nk + NW - 1) / NW;
@@ -340,9 +344,9 @@ hipError_t launch_skinny(SkinnyArgs& a, const SkinnySource& src, dim3 grid, hipS
     if (SRC != kSrcInput) lds += a.M * (a.K * 2 + 16) + a.M * 8 * 4;
     if (lds < sums) lds = sums;
     static LdsLimitOnce lds_limit;
-    if (hipError_t e = lds_limit.set({(const void*)gemm_skinny_kernel<MT, NW, false, SRC, ROWS>, (const void*)gemm_skinny_kernel<MT, NW, true, SRC, ROWS>}, 160 * 1024); e != hipSuccess) return e;
-    if (a.K % 32) hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, true, SRC, ROWS>), grid, dim3(64 * NW), lds, s, a, src);
-    else hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, false, SRC, ROWS>), grid, dim3(64 * NW), lds, s, a, src);
+    if (hipError_t e = lds_limit.set({(const void*)gemm_skinny_kernel<MT, NW, false, SRC, ROWS, PACK>, (const void*)gemm_skinny_kernel<MT, NW, true, SRC, ROWS, PACK>}, 160 * 1024); e != hipSuccess) return e;
+    if (a.K % 32) hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, true, SRC, ROWS, PACK>), grid, dim3(64 * NW), lds, s, a, src);
+    else hipLaunchKernelGGL((gemm_skinny_kernel<MT, NW, false, SRC, ROWS, PACK>), grid, dim3(64 * NW), lds, s, a, src);
     return hipGetLastError();
 }
 
@@ -380,13 +384,34 @@ static SkinnyArgs skinny_args(const GemmDesc& d) {
 // eight wavefronts where each still gets two or more steps: twice the bytes in flight of a workgroup and half its steps
 static bool eight_waves(int K) { return K >= 512; }
 
+// Segments of up to 8 columns leave half and more of a workgroup's 16 weight rows unused: they are packed, at a division per
+// thread, from two workgroups per compute unit on (first Monarch products at 1 / 32 tokens, whole calls, packed against one
+// segment per workgroup: 4096 x 4096, 128 blocks, r' = 1: 5.2 / 8.3 against 14.7 / 19.5 us; 64 blocks, r' = 4: 5.3 / 7.6 against
+// 7.2 / 10.3; 32 blocks, r' = 8: 5.0 / 7.0 against 5.4 / 7.4. Below, and with 12 columns, level or 3 % behind: 2048 x 2048,
+// 16 blocks, r' = 4: 4.6 / 5.6 against 4.5 / 5.4).
+static bool packs(const GemmDesc& d, int n, int nseg, int64_t mtiles) { return n <= SK_BN / 2 && (int64_t)nseg * d.G * mtiles > 512; }
+
+int64_t skinny_workgroups(const GemmDesc& d) {
+    int n = 0, nseg = 0;
+    segments(d, n, nseg);
+    const int64_t mtiles = (d.M + 31) / 32;
+    return packs(d, n, nseg, mtiles) ? (int64_t)((d.N + SK_BN - 1) / SK_BN) * d.G * mtiles : (int64_t)((n + SK_BN - 1) / SK_BN) * nseg * d.G * mtiles;
+}
+
+template <bool PACK>
+static hipError_t launch_input(SkinnyArgs& a, dim3 grid, hipStream_t s) {
+    if (a.M > 16) return launch_skinny<2, 4, kSrcInput, false, PACK>(a, {}, grid, s);
+    return eight_waves(a.K) ? launch_skinny<1, 8, kSrcInput, false, PACK>(a, {}, grid, s) : launch_skinny<1, 4, kSrcInput, false, PACK>(a, {}, grid, s);
+}
+
 hipError_t launch_gemm_skinny(const GemmDesc& d, hipStream_t s) {
     SkinnyArgs a = skinny_args(d);
     const int mt = d.M <= 16 ? 1 : 2;                   // more than 32 tokens: one workgroup per 32-token tile and 16 weight rows
     a.mtiles = (int)((d.M + mt * 16 - 1) / (mt * 16));
-    const dim3 grid((unsigned)((a.n + SK_BN - 1) / SK_BN), (unsigned)(d.b_div ? d.N / d.b_div : 1), (unsigned)(d.G * a.mtiles));
-    if (mt == 2) return launch_skinny<2, 4, kSrcInput>(a, {}, grid, s);
-    return eight_waves(d.K) ? launch_skinny<1, 8, kSrcInput>(a, {}, grid, s) : launch_skinny<1, 4, kSrcInput>(a, {}, grid, s);
+    const int nseg = d.b_div ? d.N / d.b_div : 1;
+    a.nall = d.N;
+    if (packs(d, a.n, nseg, a.mtiles)) return launch_input<true>(a, dim3((unsigned)((d.N + SK_BN - 1) / SK_BN), 1u, (unsigned)(d.G * a.mtiles)), s);
+    return launch_input<false>(a, dim3((unsigned)((a.n + SK_BN - 1) / SK_BN), (unsigned)nseg, (unsigned)(d.G * a.mtiles)), s);
 }
 
 bool skinny_source_supported(const GemmDesc& d) {
