@@ -1106,18 +1106,21 @@ hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s) {
     // Products of several rounds: tiles of 128 x 192, 192 x 128 and 128 x 128 on two stages of 64, two workgroups per compute unit, so that
     // one computes while the other fills its pipeline or writes its tile - the 256-wide tiles' rounds end in a burst of writes from all
     // compute units at once (33 MB at 6.5 TB/s is 5 us a round) - and so that the rounds come in other sizes where the last one of the
-    // large tile would be nearly empty. Chosen by the estimate above, and only where it is 7 % below that of the tile which the rules
-    // below take (of 431 products 75 change, by 15 % in the mean, none more than 2 % slower: 1500 tokens of 512 -> 1536 in 4 blocks
-    // 19.2 -> 15.3 us, 520 tokens of 4096 -> 11008 90.5 -> 55.2, 3500 tokens of 320 -> 320 in 12 blocks 23.5 -> 17.4). Beyond K = 2048 the
-    // matrix units are the bound, and the large tile feeds them with less LDS and L2 traffic: 15 % there. Not beyond eight rounds (level or
-    // slower), nor with rows that straddle cache lines, which smaller tiles fetch more often (344 -> 688 in 8 blocks, 1800 tokens: 17.8 -> 21.5).
-    if (d.M > 128 && d.N > 64 && d.K >= kSmallK && d.K <= 4096 && (d.K % 64 == 0 || d.k_align) && deep_ok(d, 64) && tiles(128, 128) > compute_units()) {
+    // large tile would be nearly empty. Chosen by the estimate above, and only where it is 12 % below that of the tile which the rules
+    // below take, more than its own mean error. Whole calls of 36 layers at 520 ... 8192 tokens, 166 of them with a product the estimate
+    // puts ahead, on four cards: 3.3-4 % faster in the mean, of 664 timings 6 more than 2 % slower, by up to 15 % (8192 -> 2048, 16
+    // blocks, r = 768 at 2048 tokens, on one card); a margin of 7 % gained as much in the mean but was 2-41 % slower on up to 53 of the
+    // 166 on three of the cards (1152 -> 3456, r = 384 at 3500 tokens, low-rank: 1.35). At K = 128 prologue and epilogue are all there is, and the rules
+    // below stay (low-rank 4096 x 4096, r = 128 at 6000 tokens: 7 % margin 1.3 times slower). Beyond K = 2048 the matrix units are the
+    // bound, and the large tile feeds them with less LDS and L2 traffic: 15 % there. Not beyond eight rounds (level or slower), nor with
+    // rows that straddle cache lines, which smaller tiles fetch more often (344 -> 688 in 8 blocks, 1800 tokens: 17.8 -> 21.5 us).
+    if (d.M > 128 && d.N > 64 && d.K > kSmallK && d.K <= 4096 && (d.K % 64 == 0 || d.k_align) && deep_ok(d, 64) && tiles(128, 128) > compute_units()) {
         float now = use_mid ? tile_cost(kCost256x128, d) : tile_cost(kCost128x128, d);
         if (sp.rows) now = tile_cost(kCostWide, sp.first) + tile_cost(kCost128x128, sp.rest);
         else if (sp.cols) now = tile_cost(kCostWide, sp.first) + fminf(tile_cost(kCost256x128, sp.rest), tile_cost(kCost128x128, sp.rest));
         else if (use_big) now = tile_cost(kCostWide, d);
         const TileCost* best = nullptr;
-        float est = (d.K <= 2048 ? 0.93f : 0.85f) * now;
+        float est = (d.K <= 2048 ? 0.88f : 0.85f) * now;
         for (const TileCost* c : {&kCost128x192, &kCost192x128, &kCost128x128}) {
             const int64_t n = tiles(c->bm, c->bn);
             const float e = tile_cost(*c, d);

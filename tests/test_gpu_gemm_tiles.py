@@ -12,13 +12,17 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("T,n_in,n_out", [
-    (4095, 192, 2296), (3073, 128, 3085),             # 192 x 128, two or three steps; columns that end off a 16-byte boundary
-    (4095, 192, 3068),                                # 128 x 192
-    (520, 256, 11000), (1100, 320, 4600),             # 128 x 128, several rounds
+    (4095, 192, 2296), (3334, 192, 2308),             # 192 x 128, three steps
+    (4095, 192, 3068),                                # 256 x 256
+    (3073, 128, 3085),                                # 128 x 128, two steps; columns that end off a 16-byte boundary
+    (520, 256, 11000), (1817, 192, 4108),             # 128 x 128, several rounds
+    (1100, 320, 4600),                                # 256 x 128
     (1999, 1280, 2044), (1999, 1288, 2041),           # one round of 128 x 128 on a full chip: four wavefronts
     (1999, 256, 2044), (1300, 1288, 2041),            # ... and eight
-    (1000, 1280, 2050), (1000, 1416, 2044),           # one round of 128 x 64, in steps of 64 and of 128
-    (300, 1480, 4090), (300, 1000, 4090),             # one round of 64 x 128
+    (1000, 1280, 2042), (300, 1000, 4090),            # one round of 128 x 64, in steps of 64
+    (1000, 1416, 2044), (300, 1480, 4090),            # ... and of 128
+    (1000, 1280, 2050),                               # several rounds of 128 x 64
+    (2529, 264, 389), (2529, 1288, 389),              # one round of 64 x 128, in steps of 64 and of 128
 ])
 def test_dense_tiles(T, n_in, n_out):
     if not torch.cuda.is_available():
@@ -32,9 +36,11 @@ def test_dense_tiles(T, n_in, n_out):
 
 
 @pytest.mark.parametrize("T,b,p,rp,q", [
-    (1409, 4, 64, 32, 1530), (4095, 4, 64, 48, 572),  # second factor on 192 x 128
-    (2047, 4, 64, 32, 1532), (1153, 16, 64, 8, 572),  # 128 x 192
+    (2076, 16, 64, 12, 132), (4111, 4, 64, 48, 388),  # second factor on 192 x 128
+    (1743, 16, 64, 12, 516), (4037, 4, 64, 48, 1028), # 128 x 192
     (1153, 16, 64, 12, 380), (577, 4, 64, 64, 3068),  # 128 x 128, several rounds
+    (1409, 4, 64, 32, 1530), (1153, 16, 64, 8, 572), (2047, 4, 64, 32, 1532),    # ... of two steps
+    (4095, 4, 64, 48, 572),                           # 256 x 256
     (400, 16, 64, 66, 250), (300, 16, 64, 64, 250),   # 128 x 64, one round of four wavefronts and of eight
 ])
 @pytest.mark.parametrize("order", ["interleaved", "blocked"])
