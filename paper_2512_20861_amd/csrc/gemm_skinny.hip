@@ -256,9 +256,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, Skin
     f32x4 acc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto multiply = [&](bf16x8 w, const bf16x8 (&x)[MT], int t) {   // (after the wait for both)
-        if (TAIL) {
-            if (kw + t * 32 + kg * 8 >= a.K) w = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+    auto multiply = [&](bf16x8 w, bf16x8 (&x)[MT], int t) {         // (after the wait for both)
+        if (TAIL && kw + t * 32 + 32 > a.K) {           // uniform; past K both operands are zero (an infinity times zero would be NaN)
+            const bool in = kw + t * 32 + kg * 8 < a.K;
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            w = in ? w : __builtin_bit_cast(bf16x8, zero);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) x[mt] = in ? x[mt] : __builtin_bit_cast(bf16x8, zero);
         }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x[mt], acc[mt], 0, 0, 0);

@@ -60,18 +60,18 @@ def _blast(T, q, p, b, r, bad, flags):
 
 
 @pytest.mark.parametrize("T,b", [(2, 1), (2, 3), (2, 4), (2, 15)])
-def test_coupling_of_absent_blocks(T, b):
+@pytest.mark.parametrize("r", [128, 136])
+def test_coupling_of_absent_blocks(T, b, r):
     """One or two tokens: the coupling takes 16 input blocks in four lanes, whatever their number."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    _blast(T, 64, 40, b, 128, [(1, b * 64 - 1)], 0)
+    _blast(T, 64, 40, b, r, [(1, b * 64 - 1)], 0)
 
 
 @pytest.mark.parametrize("T,q,b,r", [
-    (1300, 344, 8, 264),          # 128 x 128 and 128 x 192 tiles
-    (300, 152, 16, 640),          # one round
-    (500, 344, 16, 640),          # 256 x 128
-    (700, 344, 16, 1024),         # 256 x 256 or 192 x 128
+    (1300, 344, 8, 264), (2700, 136, 16, 264),           # 128 x 128 and 128 x 192 tiles
+    (520, 344, 8, 520), (700, 344, 8, 520),              # one round of 128 x 128, eight wavefronts and four
+    (500, 344, 16, 640), (700, 344, 16, 1024),           # 256 x 128, 256 x 256
 ])
 def test_windows_of_input_blocks(T, q, b, r):
     """Input blocks read in 64-column chunks of the input row: infinities in the first and the last column of a block, which
@@ -80,3 +80,24 @@ def test_windows_of_input_blocks(T, q, b, r):
         pytest.skip("no GPU")
     import gpu_util as gu
     _blast(T, q, 16, b, r, [(0, q), (1, q - 1), (T // 2, (b - 1) * q), (T - 1, b * q - 1), (T - 2, 0)], gu.B.BLAST_THREE_KERNELS)
+
+
+@pytest.mark.parametrize("T", [1, 17, 32])
+@pytest.mark.parametrize("K", [40, 136, 1032])
+def test_partial_last_step_of_the_weight_stream(T, K):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    rng = np.random.default_rng(K)
+    W, X = (torch.from_numpy(rng.uniform(0.5, 1.0, s).astype(np.float32)).bfloat16() for s in ((40, K), (T + 1, K)))
+    X[0, K - 1], X[T // 2, K - 8], W[3, K - 1] = float("inf"), float("nan") if T > 1 else 1.0, float("inf")
+    X = X[:T].contiguous()
+    Y = gu.empty_out(T, 40, "bf16")
+    gu.B.dense_reference_forward(X.cuda(), W.cuda(), Y, 0)
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        ref = X.double().numpy() @ W.double().numpy().T
+    got = gu.to_f64(Y)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+    ok = np.isfinite(ref)
+    assert not ok.any() or np.abs(got[ok] - ref[ok]).max() <= gu.TOL["bf16"] * np.abs(ref[ok]).max()
