@@ -168,7 +168,7 @@ __device__ __forceinline__ void store_a_tile(const unsigned char* Zs, bf16_t* __
 // reads its tile of all blocks before it writes it).
 // The Z tile is read with full-line loads (8 lanes per 128-byte row segment) and transposed on its
 // way into LDS; blocks j and j+1 travel together so that every LDS write is a bf16 pair.
-// TNT tokens per workgroup: 16 or 32.
+// TNT tokens per workgroup: 16 (8-bit Z: 32).
 // Z8: Z holds 8-bit floats (E4M3, written by the stage-1 product of the quantised-intermediate execution),
 // one byte per element in the same [T][b][r] order; they are widened to bf16 (exactly) on their way into LDS.
 template <int TNT, bool Z8>
@@ -512,13 +512,11 @@ static hipError_t launch_coupling_inst(const void* Z, const void* Sp, void* A, i
 
 hipError_t launch_blast_coupling(const void* Z, const void* Sp, void* A, int64_t T, int b, int r, hipStream_t s, bool z_fp8) {
     // A workgroup loads its tile, couples it and stores it, one after the other: several on a compute unit overlap these
-    // phases, so small tiles are faster at every size (r = 1024 at 2048 tokens 25.7 -> 20.7 us, 6.5 TB/s; r = 640 20.6 -> 14.7;
-    // 64-token tiles hold one workgroup per compute unit). Between one and a few rounds of 16-token tiles, 32 tokens are
-    // level or 5 % ahead.
-    const int64_t tiles16 = ((T + 15) / 16) * ((r + TR - 1) / TR);
-    if (z_fp8) return launch_coupling_inst<32, true>(Z, Sp, A, T, b, r, s);
-    if (tiles16 <= 256 || tiles16 >= 600) return launch_coupling_inst<16, false>(Z, Sp, A, T, b, r, s);
-    return launch_coupling_inst<32, false>(Z, Sp, A, T, b, r, s);
+    // phases, so small tiles are faster (r = 1024 at 2048 tokens 25.7 us on 64-token tiles, which hold one workgroup per
+    // compute unit, 20.7 on these, 6.5 TB/s; r = 640 20.6 -> 14.7). Against 32-token tiles, whole calls on six cards:
+    // 4096 x 4096, r = 640 0.99 / 0.97-0.99 / 0.97-0.99 / 1.00-1.02 at 500 / 750 / 1000 / 1250 tokens, r = 1024 0.98-1.00 / 0.95-0.97
+    // at 400 / 700, 2048 x 2048, r = 256 0.98-0.99 at 1500.
+    return z_fp8 ? launch_coupling_inst<32, true>(Z, Sp, A, T, b, r, s) : launch_coupling_inst<16, false>(Z, Sp, A, T, b, r, s);
 }
 
 namespace {

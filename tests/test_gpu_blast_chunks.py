@@ -1,6 +1,6 @@
 """The three-kernel BLAST execution where its plan can go wrong: input blocks that are no whole cache lines (read in
-64-column chunks against the zero-padded copy of the factor), chunks of tokens with the coupling in place, a last chunk of
-a few tokens, both coupling tiles."""
+64-column chunks against the zero-padded copy of the factor) on each tile that takes them, chunks of tokens with the
+coupling in place, a last chunk of a few tokens, the 8-bit intermediate behind such windows."""
 import numpy as np
 import pytest
 
@@ -12,9 +12,14 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("T,q,p,b,r", [
-    (700, 88, 64, 16, 136),       # 64 | 16 q, 64 does not divide q: windows of 2 and 3 chunks, partial tiles in every dimension
-    (1300, 344, 32, 8, 264), (640, 184, 40, 8, 128), (330, 152, 24, 16, 512),
-    (270, 64, 40, 16, 1032),      # coupling on 32-token tiles, a partial last group of rank indices
+    # windows of 64-column chunks: 64 | b q, 64 does not divide q, q >= 128 and 160 and more tiles of 128 x 128
+    (330, 152, 24, 16, 512), (1300, 344, 32, 8, 264),                    # 128 x 128 tiles, two stages
+    (520, 344, 16, 8, 520), (700, 344, 16, 8, 520),                      # ... in one round: eight wavefronts, four on a full chip
+    (1200, 152, 24, 16, 264), (2700, 136, 16, 16, 264),                  # 128 x 128 and 128 x 192, by the estimate
+    (500, 344, 16, 16, 640), (700, 344, 16, 16, 1024),                   # 256 x 128, 256 x 256
+    # blocks read for themselves: short ones, too few tiles
+    (700, 88, 64, 16, 136), (640, 184, 40, 8, 128),
+    (270, 64, 40, 16, 1032),                                             # a partial last group of rank indices
 ])
 def test_against_the_oracle(T, q, p, b, r):
     if not torch.cuda.is_available():
@@ -26,16 +31,17 @@ def test_against_the_oracle(T, q, p, b, r):
     assert gu.rel_err(Y, oracle.blast_forward(X.f64, lay.U.f64, lay.S.f64, lay.V.f64)) <= gu.TOL["bf16"]
 
 
-@pytest.mark.parametrize("T", [3072 + 5, 2 * 3072, 7000])
-def test_chunks_agree_with_one_chunk(T):
-    """More tokens than a chunk holds (1536 to 3072 at b r = 16 K): rows do not depend on each other, so the rows of a
-    call equal those of calls on parts of it that fit one chunk, bit for bit where the products pick the same tiles
+@pytest.mark.parametrize("T,r", [(3072 + 5, 1024), (2 * 3072, 1024), (7000, 1024),      # chunks of 1792, 3072 and 3072 tokens
+                                 (513, 4096), (540, 4096)])                             # of 512: a last one of 1 and of 28 tokens
+def test_chunks_agree_with_one_chunk(T, r):
+    """More tokens than a chunk holds, the coupling in place: rows do not depend on each other, so the rows of a call equal
+    those of calls on parts of it that fit one chunk, bit for bit where the products pick the same tiles
     (they need not: bf16 rounding of two intermediates and the output, 3 * 2^-9 of the largest value)."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import gpu_util as gu
     B = gu.B
-    b, r, q, p = 16, 1024, 64, 16
+    b, q, p = 16, 64, 16
     g = torch.Generator(device="cuda").manual_seed(T)
     rand = lambda *s: torch.randn(s, generator=g, device="cuda")
     U, S, V = ((rand(*s) / r ** 0.5).bfloat16() for s in ((b, p, r), (b, b, r), (b, q, r)))
@@ -48,7 +54,8 @@ def test_chunks_agree_with_one_chunk(T):
         return y
 
     whole = run(X)
-    parts = torch.cat([run(X[i:i + 1000].contiguous()) for i in range(0, T, 1000)])
+    step = 1000 if r == 1024 else 256
+    parts = torch.cat([run(X[i:i + step].contiguous()) for i in range(0, T, step)])
     torch.cuda.synchronize()
     err = (whole.double() - parts.double()).abs().max() / parts.double().abs().max()
     assert torch.isfinite(whole).all() and float(err) <= 3 * 2.0 ** -9
@@ -73,3 +80,15 @@ def test_unaligned_blocks_and_a_last_column_tile():
     Z = [X[:, j * q:(j + 1) * q].float() @ V[j].float() for j in range(b)]
     ref = torch.cat([sum(S[i, j].float() * Z[j] for j in range(b)) @ U[i].float().t().contiguous() for i in range(b)], dim=1)
     assert float((Y.float() - ref).norm() / ref.norm()) <= 1e-2
+
+
+@pytest.mark.parametrize("T,q,b,r", [(700, 344, 16, 1024), (1300, 344, 8, 272)])        # 256 x 256 and 128 x 128 tiles
+def test_windows_with_the_8_bit_intermediate(T, q, b, r):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    from oracle import quant
+    lay = bi.blast_layer(b * q, b * 16, b, r, "bf16", seed=T)
+    X = bi.activations(T, b * q, "bf16", seed=r)
+    Y = gu.to_f64(gu.run_blast(X, lay, gu.B.BLAST_Z_FP8, packed=True))
+    assert gu.rel_err(Y, quant.blast_forward_qz(X.f64, lay.U.f64, lay.S.f64, lay.V.f64)[0]) <= gu.TOL["bf16"]
