@@ -17,6 +17,7 @@ tenth of its time, and hand every other call to it.
 from __future__ import annotations
 
 import ctypes
+import inspect
 import os
 
 import torch
@@ -224,6 +225,8 @@ def _launcher(marshal):
     fn = (_host.launcher(name, call, _check) if _host else None) or call
     fn.marshal = marshal
     fn.__name__, fn.__doc__ = name, marshal.__doc__
+    if fn is not call:
+        fn.__signature__ = inspect.signature(marshal)
     return fn
 
 

@@ -237,6 +237,7 @@ struct Launcher {
     PyObject* failed;                                    // failed(status, name) raises
     const Entry* entry;
     PyObject* names[kMaxParams];                         // interned parameter names
+    PyObject* weakrefs;
     vectorcallfunc vectorcall;
 };
 
@@ -277,6 +278,7 @@ PyObject* launcher_call(PyObject* self_, PyObject* const* args, size_t nargsf, P
 void launcher_dealloc(PyObject* self_) {
     Launcher* self = (Launcher*)self_;
     PyObject_GC_UnTrack(self_);
+    if (self->weakrefs) PyObject_ClearWeakRefs(self_);
     Py_XDECREF(self->dict);
     Py_XDECREF(self->fallback);
     Py_XDECREF(self->failed);
@@ -293,6 +295,12 @@ int launcher_traverse(PyObject* self_, visitproc visit, void* arg) {
 
 PyTypeObject LauncherType = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
+// a copy of a function is the function
+PyObject* launcher_itself(PyObject* self, PyObject*) {
+    Py_INCREF(self);
+    return self;
+}
+PyMethodDef launcher_methods[] = {{"__copy__", launcher_itself, METH_NOARGS, nullptr}, {"__deepcopy__", launcher_itself, METH_O, nullptr}, {}};
 PyGetSetDef launcher_getset[] = {{"__dict__", PyObject_GenericGetDict, PyObject_GenericSetDict, nullptr, nullptr}, {}};
 
 // launcher(name, fallback, failed) -> Launcher, or None for a function without a native form
@@ -305,6 +313,7 @@ PyObject* make_launcher(PyObject*, PyObject* args) {
             Launcher* l = PyObject_GC_New(Launcher, &LauncherType);
             if (!l) return nullptr;
             l->dict = nullptr;
+            l->weakrefs = nullptr;
             l->fallback = fallback;
             l->failed = failed;
             Py_INCREF(fallback);
@@ -407,6 +416,8 @@ PyMODINIT_FUNC PyInit__host(void) {
     LauncherType.tp_traverse = launcher_traverse;
     LauncherType.tp_dictoffset = offsetof(Launcher, dict);
     LauncherType.tp_getset = launcher_getset;
+    LauncherType.tp_methods = launcher_methods;
+    LauncherType.tp_weaklistoffset = offsetof(Launcher, weakrefs);
     LauncherType.tp_vectorcall_offset = offsetof(Launcher, vectorcall);
     LauncherType.tp_call = PyVectorcall_Call;
     if (PyType_Ready(&LauncherType) < 0) return nullptr;
