@@ -20,10 +20,11 @@ def sources():
 
 def _host_command():
     """g++ command line of the binding's extension module: torch's own C++ headers and libraries, and libblr.so beside it."""
+    import shutil
     import sysconfig
     import torch
     t = os.path.dirname(torch.__file__)
-    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    rocm = os.path.dirname(os.path.dirname(os.path.abspath(shutil.which(HIPCC) or HIPCC)))     # (HIPCC may be a bare command name)
     return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1",
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
             "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),

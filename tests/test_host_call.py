@@ -128,6 +128,18 @@ def test_native_checks(name, T):
     assert (out == 7.0).all()                            # nothing was launched
 
 
+def test_build_command_with_a_bare_compiler_name(monkeypatch):
+    import os
+    import shutil
+    from paper_2512_20861_amd import build
+    if not shutil.which("hipcc"):
+        pytest.skip("no hipcc on the path")
+    monkeypatch.setattr(build, "HIPCC", "hipcc")
+    command = build._host_command()
+    dirs = [command[i + 1] for i, a in enumerate(command) if a == "-isystem"]
+    assert all(os.path.isabs(d) for d in dirs) and any(os.path.exists(os.path.join(d, "hip", "hip_runtime.h")) for d in dirs)
+
+
 def test_callables_behave_as_functions_do():
     import copy
     import inspect
