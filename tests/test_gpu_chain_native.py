@@ -83,6 +83,29 @@ def test_copies_and_lifetimes(T):
         assert torch.equal(other.h, want[0])
 
 
+@pytest.mark.parametrize("op,hidden,mlp,params", [
+    # a model's widths: products on eight wavefronts (every first Monarch product, BLAST's down), rows owned by wavefronts
+    # (BLAST's first products of q/k/v and gate/up and its coupling in gate/up)
+    ("monarch", 2048, 8192, dict(nblocks=4, r_square=512, r_mlp=512)), ("blast", 2048, 8192, dict(b=16, r_square=256, r_mlp=512)),
+    # rows owned by wavefronts: 800 and 784 tiles, 50 and 49 a block (a last workgroup of two tiles and of one), ranks that
+    # are no multiple of 16 or of 32, blocks of 40 and 72 columns (a partial last step)
+    ("blast", 640, 1152, dict(b=16, r_square=264, r_mlp=392))])
+@pytest.mark.parametrize("T", [1, 3, 4])
+def test_wide_fused_chain(op, hidden, mlp, params, T):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    from paper_2512_20861_amd.chain import DeviceChain
+    layers = bi.chain_layers(op, n_layers=2 if hidden < 2048 else 1, hidden=hidden, mlp=mlp, params=params, dtype="bf16")
+    x = bi.activations(T, hidden, "bf16")
+    chain = DeviceChain(layers, T, eps=oc.EPS)
+    assert chain._native
+    ref = oc.chain_forward(x.f64, layers, _lin)
+    got = [chain.forward(gu.to_dev(x)).clone() for _ in range(3)]
+    torch.cuda.synchronize()
+    assert gu.rel_err(gu.to_f64(got[0]), ref) <= 2e-2 and all(torch.equal(g, got[0]) for g in got)
+
+
 def _lin(x, f):
     return oracle.monarch_forward(x, f.R.f64, f.L.f64) if hasattr(f, "R") else oracle.blast_forward(x, f.U.f64, f.S.f64, f.V.f64)
 
