@@ -48,6 +48,8 @@ struct SkinnyArgs {
     int mtiles;                       // tiles of 16 MT tokens
 };
 
+__device__ __attribute__((aligned(16))) const unsigned char zero_piece[16] = {0};
+
 __device__ __forceinline__ bf16x8 lds_read_frag(unsigned addr) {   // (reads the compiler can see wait for all direct loads)
     bf16x8 v;
     asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr) : "memory");
@@ -227,13 +229,14 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, Skin
         seg_left = a.a_seg - kw % a.a_seg;
     }
     auto fetch = [&](unsigned char* slot) {
-        unsigned kl = kf + piece * 8;
-        if (TAIL) kl = kl < (unsigned)a.K ? kl : a.K - 8;           // pieces past K re-read the last one, zeroed on use
-        __builtin_amdgcn_global_load_lds(BLR_GPTR(B + (woff + kl) * 2u), BLR_LPTR(slot), 16, 0, 0);
+        const unsigned kl = kf + piece * 8;
+        // pieces past K are zeros in both operands (an infinity times zero would be NaN)
+        auto from = [&](const unsigned char* p) { return TAIL && kl >= (unsigned)a.K ? zero_piece : p; };
+        __builtin_amdgcn_global_load_lds(BLR_GPTR(from(B + (woff + kl) * 2u)), BLR_LPTR(slot), 16, 0, 0);
         const unsigned char* As = A + seg_off * 2;
 #pragma unroll
         for (int mt = 0; mt < XL; ++mt)
-            __builtin_amdgcn_global_load_lds(BLR_GPTR(As + (xoff[mt] + kl) * 2u), BLR_LPTR(slot + (1 + mt) * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(BLR_GPTR(from(As + (xoff[mt] + kl) * 2u)), BLR_LPTR(slot + (1 + mt) * 1024), 16, 0, 0);
         kf += 32;
         seg_left -= 32;
         if (XL && seg_left == 0) {
@@ -250,20 +253,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, Skin
     auto x_frag = [&](int mt, unsigned at, int t) {      // token fragment of step t, whose slot is at
         if constexpr (SRC == kSrcInput) return lds_read_frag(frag + at + (1 + mt) * 1024);
         int k = kw + t * 32 + kg * 8;
-        if (TAIL) k = k < a.K ? k : a.K - 8;
+        if (TAIL) k = k < a.K ? k : a.K;                 // (zeros behind the row)
         return lds_read_frag(row_frag + k * 2);
     };
     f32x4 acc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto multiply = [&](bf16x8 w, bf16x8 (&x)[MT], int t) {         // (after the wait for both)
-        if (TAIL && kw + t * 32 + 32 > a.K) {           // uniform; past K both operands are zero (an infinity times zero would be NaN)
-            const bool in = kw + t * 32 + kg * 8 < a.K;
-            const u32x4 zero = {0u, 0u, 0u, 0u};
-            w = in ? w : __builtin_bit_cast(bf16x8, zero);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) x[mt] = in ? x[mt] : __builtin_bit_cast(bf16x8, zero);
-        }
+    auto multiply = [&](bf16x8 w, const bf16x8 (&x)[MT]) {           // (after the wait for both)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x[mt], acc[mt], 0, 0, 0);
     };
@@ -271,6 +267,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, Skin
     int t = 0;
     for (; t < steps && t < a.slots; ++t) fetch(mine + t * SLOT);
     if constexpr (SRC != kSrcInput) {
+        if (TAIL && tid < a.M) *(u32x4*)(rows + tid * xs + a.K * 2) = u32x4{0u, 0u, 0u, 0u};
         source_rows<SRC, NW>(src, a.M, a.K, g, s, rows, xs, (float*)(rows + a.M * xs));
         __syncthreads();
     }
@@ -286,7 +283,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, Skin
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) asm volatile("" : "+v"(x[mt]));
         fetch(mine + at);
-        multiply(w, x, t);
+        multiply(w, x);
         at = at == (SK_RD - 1) * SLOT ? 0 : at + SLOT;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -302,8 +299,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, Skin
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w0), "+v"(w1) :: "memory");
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) asm volatile("" : "+v"(x0[mt]), "+v"(x1[mt]));
-        multiply(w0, x0, t);
-        if (t + 1 < steps) multiply(w1, x1, t + 1);     // uniform
+        multiply(w0, x0);
+        if (t + 1 < steps) multiply(w1, x1);            // uniform
         t += 2;
         at = at1 == (unsigned)(a.slots - 1) * SLOT ? 0 : at1 + SLOT;
     }
