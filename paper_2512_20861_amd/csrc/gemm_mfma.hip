@@ -1157,12 +1157,15 @@ hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s) {
     // compute unit does (128 x 128 tiles: 512 -> 512, 4 blocks at 2048 tokens 9.2 -> 8.3 us, interleaved 11.3 -> 10.3;
     // 1024 -> 4096 at 1000 tokens 12.4 -> 11.6; 128 x 64: 1024 -> 1024, 4 blocks at 512 tokens 9.0 -> 8.2; 64 x 128: 1488 ->
     // 4096 at 300 tokens 14.4 -> 10.8). With these two in steps of 64 on four stages up to K = 1280, of 128 on three beyond (11.4 -> 10.8).
-    // Not on a nearly full chip where the contraction is long: cards differ in how far they throttle under the matrix units' load, and
-    // eight wavefronts read each operand fragment from LDS 1.5 times as often. With 224 tiles of 128 x 128 and more, four took 0.87-1.00 of
-    // the time on eight cards for BLAST 4096 x 4096, r = 640 at 1000 tokens (38.0 -> 32.9 us, 41.1 -> 38.1, 31.8 -> 31.9), 0.86-1.02 for
-    // low-rank 4096 x 4096, r = 1024 at 1000 tokens, 0.93-1.07 for Monarch 4096 x 4096, 4 blocks. With fewer tiles, and up to K = 256, eight
-    // are ahead on all (1024 x 1024, 4 blocks at 4096 tokens: 17.7 against 18.8 us). The 128 x 64 tile loses only at K >= 1024 in batches
-    // with up to 256 columns (BLAST, r = 1024 at 400 tokens: 35.4 -> 31.4 us on the slowest card, 27.0 -> 27.5 on the fastest).
+    // Not with up to 1024 tokens on a nearly full chip where the contraction is long: cards differ in how far they throttle under the matrix
+    // units' load, and eight wavefronts read each operand fragment from LDS 1.5 times as often. With 224 tiles of 128 x 128 and more, four
+    // took 0.87-1.00 of the time on ten cards for BLAST 4096 x 4096, r = 640 at 1000 tokens (38.0 -> 32.9 us, 41.1 -> 38.1, 31.8 -> 31.9),
+    // 0.86-1.02 for low-rank 4096 x 4096, r = 1024 at 900 ... 1024 tokens, 0.93-1.07 for Monarch 4096 x 4096, 4 blocks. With more tokens
+    // eight are level or ahead (0.97-1.04; 4096 x 4096, 4 blocks, r = 512 at 2048 tokens 32.0 against 32.9 us), up to K = 512 they are where
+    // such products alternate with lighter kernels (16 Monarch layers at 2048 tokens: 0.98-0.99 of the pass; a layer of them alone in a
+    // loop between 0.95 and 1.14), and with fewer tiles on all (1024 x 1024, 4 blocks at 4096 tokens: 17.7 against 18.8 us). The 128 x 64
+    // tile loses only at K >= 1024 in batches with up to 256 columns (BLAST, r = 1024 at 400 tokens: 35.4 -> 31.4 us on the slowest card,
+    // 27.0 -> 27.5 on the fastest).
     auto full = [&](int bm, int bn) { return tiles(bm, bn) * 8 >= compute_units() * 7; };
     const bool long_k = d.K > 1280 && deep_ok(d, 128);
     auto one_round = [&](int bm, int bn) { return d.K >= 256 && deep_ok(d, 128) && tiles(bm, bn) <= 256; };
@@ -1171,7 +1174,7 @@ hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s) {
     // (768 x 768 at 6304 tokens: 19.1 -> 14.4 us; 3072 -> 768: 58.6 -> 40.8 us; 1152 x 1152 at 1024 tokens: 10.9 -> 8.0 us)
     const bool rounds_deep = d.K >= 128 && deep_ok(d, 64);   // (from two steps on: 128 -> 2304 at 32768 tokens 53.7 -> 46.0 us; 192 -> 768 at 6304 tokens 8.4 -> 7.4 us)
     if (d.M > 64 && d.N > 64 && tiles(128, 128) >= kFill)
-        return one_round(128, 128) ? (full(128, 128) && d.K > 256 ? launch_line<128, 128, 2, 2, 64, 4>(d, s) : launch_line<128, 128, 2, 4, 64, 4>(d, s)) : rounds_deep ? launch_line<128, 128, 2, 2, 64, 2>(d, s) : launch_dma<128, 128, 2, 2>(d, s);
+        return one_round(128, 128) ? (full(128, 128) && d.K > 512 && d.M <= 1024 ? launch_line<128, 128, 2, 2, 64, 4>(d, s) : launch_line<128, 128, 2, 4, 64, 4>(d, s)) : rounds_deep ? launch_line<128, 128, 2, 2, 64, 2>(d, s) : launch_dma<128, 128, 2, 2>(d, s);
     if (d.M > 64 && tiles(128, 64) >= kFill)
         return one_round(128, 64) ? (full(128, 64) && d.K >= 1024 && d.N <= 256 ? launch_line<128, 64, 2, 2, 128, 3>(d, s) : long_k ? launch_line<128, 64, 4, 2, 128, 3>(d, s) : launch_line<128, 64, 4, 2, 64, 4>(d, s)) : rounds_deep ? launch_line<128, 64, 2, 2, 64, 2>(d, s) : launch_dma<128, 64, 2, 2>(d, s);
     if (d.N > 64 && tiles(64, 128) >= kFill)

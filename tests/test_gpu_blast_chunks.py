@@ -14,7 +14,7 @@ torch = pytest.importorskip("torch")
 @pytest.mark.parametrize("T,q,p,b,r", [
     # windows of 64-column chunks: 64 | b q, 64 does not divide q, q >= 128 and 160 and more tiles of 128 x 128
     (330, 152, 24, 16, 512), (1300, 344, 32, 8, 264),                    # 128 x 128 tiles, two stages
-    (520, 344, 16, 8, 520), (700, 344, 16, 8, 520),                      # ... in one round: eight wavefronts, four on a full chip
+    (520, 344, 16, 8, 520), (700, 584, 16, 8, 520),                      # ... in one round: eight wavefronts, four on a full chip
     (1200, 152, 24, 16, 264), (2700, 136, 16, 16, 264),                  # 128 x 128 and 128 x 192, by the estimate
     (500, 344, 16, 16, 640), (700, 344, 16, 16, 1024),                   # 256 x 128, 256 x 256
     # blocks read for themselves: short ones, too few tiles

@@ -17,8 +17,8 @@ torch = pytest.importorskip("torch")
     (3073, 128, 3085),                                # 128 x 128, two steps; columns that end off a 16-byte boundary
     (520, 256, 11000), (1817, 192, 4108),             # 128 x 128, several rounds
     (1100, 320, 4600),                                # 256 x 128
-    (1999, 1280, 2044), (1999, 1288, 2041),           # one round of 128 x 128 on a full chip: four wavefronts
-    (1999, 256, 2044), (1300, 1288, 2041),            # ... and eight
+    (1999, 1280, 2044), (1999, 1288, 2041),           # one round of 128 x 128: eight wavefronts
+    (1020, 520, 4090), (1000, 640, 4044),             # ... four: a full chip, up to 1024 tokens
     (1000, 1280, 2042), (300, 1000, 4090),            # one round of 128 x 64, in steps of 64
     (1000, 1416, 2044), (300, 1480, 4090),            # ... and of 128
     (1000, 1280, 2050),                               # several rounds of 128 x 64

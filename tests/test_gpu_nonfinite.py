@@ -70,7 +70,7 @@ def test_coupling_of_absent_blocks(T, b, r):
 
 @pytest.mark.parametrize("T,q,b,r", [
     (1300, 344, 8, 264), (2700, 136, 16, 264),           # 128 x 128 and 128 x 192 tiles
-    (520, 344, 8, 520), (700, 344, 8, 520),              # one round of 128 x 128, eight wavefronts and four
+    (520, 344, 8, 520), (700, 584, 8, 520),              # one round of 128 x 128, eight wavefronts and four
     (500, 344, 16, 640), (700, 344, 16, 1024),           # 256 x 128, 256 x 256
 ])
 def test_windows_of_input_blocks(T, q, b, r):
