@@ -10,7 +10,8 @@
  *
  * With a handful of tokens the glue and BLAST's coupling are computed inside the products that consume them (two launches
  * per linear, eight per layer); with more, every step is a call of blr.h. From its second call on a chain replays its
- * launches as a HIP graph, except on a stream that is being captured.
+ * launches as a HIP graph, except on a stream that is being captured; the second call captures and instantiates the graph
+ * (0.6 ms of host time for 128 launches, once, 1.2 ms for 300).
  *
  * Ownership: the factors and all buffers are the caller's and must outlive the chain; the handle holds host memory and,
  * from the second call on, one HIP graph. Calls on one chain use its buffers: overlapping calls race.
@@ -45,7 +46,8 @@ typedef struct {
     size_t workspace_bytes;
 } blr_chain_buffers;
 
-/* BLR_ERR_INVALID_ARG: sizes or null pointers; BLR_ERR_UNSUPPORTED: no grouped execution of these shapes. */
+/* BLR_ERR_INVALID_ARG: sizes or null pointers; BLR_ERR_UNSUPPORTED: a linear or group of these shapes does not run on
+ * the kernels with an intermediate in the workspace (no grouped execution, or one kernel for the whole layer). */
 blr_status blr_chain_create(const blr_chain_desc* desc, const blr_chain_layer* layers, const blr_chain_buffers* buffers, blr_chain** out);
 /* Runs the chain on the residual stream that h holds, in place. */
 blr_status blr_chain_forward(blr_chain* chain, blr_stream stream);

@@ -215,8 +215,11 @@ bool monarch_takes_fused(int64_t T, int n_in, int n_out, int b1, int b2, int rp,
     return base <= 256 && (b2 >= 16 || T <= 64);
 }
 
-// fp32 layers whose whole call is one round of workgroups of the fp32 single kernel (16 tokens x one output block each);
-// with more, the weights a workgroup streams for its 16 tokens are what the call costs.
+// fp32 layers whose whole call is up to 512 workgroups of the fp32 single kernel (16 tokens x one output block each): one round
+// where two fit a compute unit's LDS, else two; with more, the weights a workgroup streams for its 16 tokens are what the call
+// costs. Against the portable kernels: one round 57 -> 28 us (1024 x 1024, 4 blocks, r' = 64, 1024 tokens), two rounds of one per
+// compute unit 67 -> 51 (2048 tokens), 135 -> 42 (16 blocks, r' = 64, 300 tokens), one block of rank 1024 on 1024 -> 4096 at 4096
+// tokens, whose every workgroup streams all of both factors, 669 -> 582, of rank 256 on 256 -> 1024 at 8192 tokens 114 -> 84.
 bool monarch_takes_f32(int64_t T, int n_in, int n_out, int b1, int b2, int rp, blr_dtype dt, unsigned flags) {
     if (dt != BLR_F32 || (flags & (BLR_FORCE_GENERIC | BLR_ONLY_FIRST_STAGE | BLR_ONLY_LAST_STAGE | BLR_MONARCH_IN_BLOCKED | BLR_MONARCH_TWO_KERNELS))) return false;
     return (T + 15) / 16 * b2 <= 512 && monarch_f32_supported(T, n_in, n_out, b1, b2, rp);

@@ -77,11 +77,6 @@ __device__ inline uint32_t pack2_bf16(float lo, float hi) {
 #define BLR_GPTR(p) ((const void __attribute__((address_space(1)))*)(p))
 #define BLR_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
 
-// value select (a ternary on two uint4 lvalues would select an address and force them into memory)
-__device__ inline uint4 keep_if(bool ok, uint4 v) {
-    return make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
-}
-
 // A batched "NT" product with index maps, general enough for every contraction of the path:
 //   C(g, m, n) = sum_k A(g, m, k) * B(g, n, k),  g < G, m < M, n < N, k < K
 // element addresses (in elements of the storage type):

@@ -483,22 +483,21 @@ struct Window {
         hi = (g + 1) * K - (c1 - 1) * 64;
     }
 };
-// Zeros in place of the 16-byte pieces [from, to) of the BM A rows of a stage that has landed, and a barrier: their
-// product with the zeros of B would be NaN for a neighbour's infinity. In LDS, once per end of a window: a choice of
-// address per lane behind every load cost the 11008 -> 4096 layer 5 % at 8192 tokens. addr(row): the row's LDS address.
-template <class C, int BM, class Addr>
-__device__ __forceinline__ void clear_pieces(int from, int to, Addr addr) {
-    if (from == to) return;                             // uniform
+// Zeros in place of the 16-byte pieces [from, to) of the A rows that this wavefront's direct loads have brought into a
+// stage (landed, and behind the next barrier for the others): their product with the zeros of B would be NaN for a
+// neighbour's infinity. In LDS, once per end of a window: a choice of address per lane behind every load cost the
+// 11008 -> 4096 layer 5 % at 8192 tokens, this 0.6 %. chunk(h): LDS address of what load h filled, lane l at 16 l.
+template <class C, int BM, class Chunk>
+__device__ __forceinline__ void clear_pieces(int wave, int lane, int from, int to, Chunk chunk) {
     const u32x4 zero = {0u, 0u, 0u, 0u};
-    constexpr int SWEEP = C::THREADS / C::PPR;          // rows per sweep; rows a sweep apart are swizzled alike
-    static_assert(BM % SWEEP == 0 && (SWEEP >> C::SH) % C::PPR == 0, "a thread keeps its piece");
-    const int row = threadIdx.x / C::PPR, p = threadIdx.x % C::PPR;
-    const unsigned slot = (unsigned)(p ^ ((row >> C::SH) & (C::PPR - 1))) * 16u;
-    if (p >= from && p < to)
 #pragma unroll
-        for (int r = 0; r < BM; r += SWEEP)             // (a store the compiler can see would wait for all direct loads)
-            asm volatile("ds_write_b128 %0, %1" :: "v"(addr(row + r) + slot), "v"(zero) : "memory");
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    for (int h = 0; h < C::LPW; ++h) {
+        const int row = C::RPL * (C::LPW * wave + h) + lane / C::PPR;
+        const int piece = (lane % C::PPR) ^ ((row >> C::SH) & (C::PPR - 1));
+        if (row < BM && piece >= from && piece < to)    // (a store the compiler can see would wait for all direct loads)
+            asm volatile("ds_write_b128 %0, %1" :: "v"(chunk(h) + lane * 16), "v"(zero) : "memory");
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -597,7 +596,8 @@ __global__ __launch_bounds__(512) void gemm_wide_kernel(GemmDesc d, int tiles_m,
         static_for<C::NI>([&](auto J) { bfr[ks & 1][decltype(J)::value] = lds_read_b128<decltype(J)::value * 32 * C::RB>(fb[st][ks]); });
     };
     auto clear = [&](int stage_off, int from, int to) {
-        clear_pieces<C, BM>(from, to, [&](int row) { return lds0 + stage_off + row * C::RB; });
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        clear_pieces<C, BM>(wave, lane, from, to, [&](int h) { return lds0 + stage_off + (C::LPW * wave + h) * 1024; });
     };
     // step kt, on stage ST
     auto step = [&](auto ST, int kt) {
@@ -626,8 +626,8 @@ __global__ __launch_bounds__(512) void gemm_wide_kernel(GemmDesc d, int tiles_m,
                 }
                 if constexpr (ks == C::KS - 1 && q == C::MI * C::NI / 2 - 1) {
                     // every wavefront is past its last read of this stage; the other stage has landed (own loads: vmcnt; the others': barrier)
-                    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
                     if (EDGE == 2 && kt == nk - 2) clear((1 - st) * C::STAGE, win.hi >> 3, C::PPR);
+                    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
                     read_frags(std::integral_constant<int, 1 - st>{}, std::integral_constant<int, 0>{});
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -637,8 +637,8 @@ __global__ __launch_bounds__(512) void gemm_wide_kernel(GemmDesc d, int tiles_m,
 
     static_for<C::LPW>([&](auto H) { issue(0, H); });
     advance();
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     if (EDGE == 2) clear(0, 0, win.lo >> 3);
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     read_frags(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
 #pragma unroll 1
     for (int kt = 0; kt + 1 < nk; kt += 2) {            // (stages alternate: two steps per trip keep them compile-time constants)
@@ -750,7 +750,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_line_kernel(GemmDesc d, i
         static_for<C::NI>([&](auto J) { bfr[ks & 1][decltype(J)::value] = lds_read_b128<decltype(J)::value * 32 * C::RB * NS + st * 1024>(fb[ks]); });
     };
     auto clear = [&](int st, int from, int to) __attribute__((always_inline)) {
-        clear_pieces<C, BM>(from, to, [&](int row) { return lds0 + st * 1024 + (row / C::RPL) * (NS * 1024) + (row % C::RPL) * C::RB; });
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(C::LPW * (NS - 2)) : "memory");
+        clear_pieces<C, BM>(wave, lane, from, to, [&](int h) { return lds0 + ((C::LPW * wave + h) * NS + st) * 1024; });
     };
     // step kt, on stage ST: fetches the step NS - 1 ahead into the stage that was computed on one step ago
     auto step = [&](auto ST, int kt) __attribute__((always_inline)) {
@@ -779,8 +780,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_line_kernel(GemmDesc d, i
                 }
                 if constexpr (ks == C::KS - 1 && q == HALF - 1) {
                     // every wavefront is past its last read of this stage; the next stage has landed (own loads: vmcnt; the others': barrier)
-                    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(C::LPW * (NS - 2)) : "memory");
                     if (EDGE == 2 && kt == nk - 2) clear((st + 1) % NS, win.hi >> 3, C::PPR);
+                    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(C::LPW * (NS - 2)) : "memory");
                     read_frags(std::integral_constant<int, (st + 1) % NS>{}, std::integral_constant<int, 0>{});
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -792,8 +793,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_line_kernel(GemmDesc d, i
         static_for<C::LPW>([&](auto H) { issue(S, H); });
         advance();
     });
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(C::LPW * (NS - 2)) : "memory");
     if (EDGE == 2) clear(0, 0, win.lo >> 3);
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(C::LPW * (NS - 2)) : "memory");
     read_frags(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
     int kt = 0;
 #pragma unroll 1
@@ -1148,15 +1149,14 @@ hipError_t launch_gemm_mfma(const GemmDesc& d, hipStream_t s) {
     // ahead of 200 by 10-30 % wherever the two differ (e.g. 11008 -> 4096 at 640 tokens: 144 -> 98 us,
     // 160 tiles of 128 x 128 in one round instead of 320 of 128 x 64 in two) and 128 behind both
     constexpr int64_t kFill = 160;
-    // Calls that are a single round of workgroups (at most one per compute unit) take deep steps of 128
-    // (64 for the 128 x 128 tile) contraction indices per barrier: every workgroup is alone on its compute
-    // unit, so nothing else hides the fixed cost of a step. Measured on the 4096- and 11008-wide layers at
-    // 256 ... 2048 tokens: 5-25 % faster for one round; with more workgroups than compute units the
-    // 32-deep steps, whose smaller LDS footprint lets two or three workgroups share a compute unit, stay.
-    // Eight wavefronts then, of 64 x 32 or 32 x 32 each: two on a SIMD cover each other's waits where nothing else on the
+    // Calls that are a single round of workgroups (at most one per compute unit) take deep steps on three or four
+    // stages: every workgroup is alone on its compute unit, so nothing else hides the fixed cost of a step (5-25 %
+    // on the 4096- and 11008-wide layers at 256 ... 2048 tokens against steps of 32). Steps of 64 on four stages, and for
+    // the two smaller tiles of 128 on three beyond K = 1280 (11.4 -> 10.8 us); the 64 x 64 tile in steps of 128 on four.
+    // On eight wavefronts, of 64 x 32 or 32 x 32 each: two on a SIMD cover each other's waits where nothing else on the
     // compute unit does (128 x 128 tiles: 512 -> 512, 4 blocks at 2048 tokens 9.2 -> 8.3 us, interleaved 11.3 -> 10.3;
-    // 1024 -> 4096 at 1000 tokens 12.4 -> 11.6; 128 x 64: 1024 -> 1024, 4 blocks at 512 tokens 9.0 -> 8.2; 64 x 128: 1488 ->
-    // 4096 at 300 tokens 14.4 -> 10.8). With these two in steps of 64 on four stages up to K = 1280, of 128 on three beyond (11.4 -> 10.8).
+    // 1024 -> 4096 at 1000 tokens 12.4 -> 11.6; 128 x 64: 1024 -> 1024, 4 blocks at 512 tokens 9.0 -> 8.2, 1488 -> 4096
+    // at 300 tokens 14.4 -> 10.8).
     // Not with up to 1024 tokens on a nearly full chip where the contraction is long: cards differ in how far they throttle under the matrix
     // units' load, and eight wavefronts read each operand fragment from LDS 1.5 times as often. With 224 tiles of 128 x 128 and more, four
     // took 0.87-1.00 of the time on ten cards for BLAST 4096 x 4096, r = 640 at 1000 tokens (38.0 -> 32.9 us, 41.1 -> 38.1, 31.8 -> 31.9),

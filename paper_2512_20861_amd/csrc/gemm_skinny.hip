@@ -7,7 +7,7 @@
 // between them (split-K inside the workgroup, summed through LDS in wavefront order, so results do not depend on
 // timing). Many small workgroups (N/16 per batch entry) put every compute unit to work on the stream.
 //
-// What bounds it: a launch (2.0 us for an empty kernel in a graph) plus one memory latency, and the instructions
+// What bounds it: a launch (1.6 us for an empty kernel in a graph) plus one memory latency, and the instructions
 // themselves: code that runs once per launch is fetched at the latency of the L2. So the loops are rolled, the operands
 // go to LDS with direct loads (no registers, hence no unrolling, to hold what is in flight), and the index maps are
 // grid dimensions instead of divisions. Monarch 4096 x 4096, 4 blocks, r = 1024, both products with weights from the
@@ -419,7 +419,10 @@ bool skinny_source_supported(const GemmDesc& d) {
     return d.M >= 1 && d.M <= kSourceTokens && mfma_gemm_supported(d) && shape_ok(d, 1) && d.K <= 4096;      // (rows of 8 tokens: 64 KB of LDS behind the weights)
 }
 
-// From this many 16-row tiles on a wavefront owns a tile: there are workgroups enough, and the source is computed a quarter as often.
+// From this many 16-row tiles on a wavefront owns a tile: there are workgroups enough (three a compute unit before), and the source
+// is computed a quarter as often. A layer of the BLAST chain of 2048 / 8192, 16 blocks, at 1 / 4 tokens, with the limit at 384, 768 (its
+// q/k/v) and 1024 (its gate/up): 39.2 / 48.3, 37.8 / 47.6 and 37.8 / 47.7 us, 41.4 / 54.0 without this form; between 512 and 768, where
+// nothing of these chains has tiles, the limit is not resolved.
 constexpr int64_t kRowsTiles = 768;
 
 template <int SRC>

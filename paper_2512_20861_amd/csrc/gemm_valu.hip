@@ -1,6 +1,6 @@
 // Portable scalar-ALU kernels: correct for every shape and stride, fp32 accumulation.
-// They are the whole fp32 path and the fallback of the bf16 path where the MFMA kernels'
-// alignment contract does not hold.
+// They are the fp32 path of everything but Monarch layers of a round or two of workgroups
+// (monarch_f32.hip), and the fallback of the bf16 path where the MFMA kernels' alignment contract does not hold.
 #include "blr_common.h"
 
 namespace blr {
