@@ -94,11 +94,11 @@ int64_t blast_chunk_tokens(int64_t T, int b, int r, int64_t most) {
 }
 // The fused stage 1 + coupling kernel runs one workgroup per compute unit on 128-token x 64-rank tiles. What it saves, the
 // round trip of Z, grows with b r per token; what it pays, a stage 1 on tiles of half the arithmetic intensity of the
-// GEMM's, grows with n_in r. Input blocks longer than 256 columns always lose to three kernels (11008 -> 4096, r = 1024 at
-// 2048 / 8192 tokens 124 / 502 against 101 / 402 us; 8192 -> 2048, r = 768: 83 / 291 against 75 / 247). Up to 256 the fused
-// kernel is ahead or level while its rounds of workgroups are full (r = 1024, 4096 x 4096 at 4096 tokens 147 against 164;
-// 2048 -> 8192, r = 512 at 8192 tokens 170 against 188) and behind with a last round half empty (r = 640 at 4096 / 8192
-// tokens, 1.25 / 2.5 rounds: 115 / 214 against 100 / 199); with too few tiles it leaves too much of the chip idle.
+// GEMM's, grows with n_in r. Input blocks longer than 256 columns lose to three kernels (graph replays on one card: 11008 ->
+// 4096, r = 1024 at 2048 / 8192 tokens 121 / 504 against 100 / 400 us; 8192 -> 2048, r = 768: 81 / 291 against 69 / 232). Up to 256
+// the fused kernel is ahead while its rounds of workgroups are full (r = 1024, 4096 x 4096 at 4096 tokens 145 against 170;
+// 2048 -> 8192, r = 512 at 8192 tokens 168 against 184) and behind with a last round half empty (r = 640 at 4096 / 8192
+// tokens, 1.25 / 2.5 rounds: 113 / 214 against 98 / 196); with too few tiles it leaves too much of the chip idle.
 bool fused_pays(int64_t T, int n_in, int b, int r) {
     const int q = n_in / b;
     const int64_t tiles = blast_fused_tiles(T, r), rounds = (tiles + 255) / 256;
