@@ -92,17 +92,31 @@ int64_t blast_chunk_tokens(int64_t T, int b, int r, int64_t most) {
     }
     return best;
 }
-// The fused stage 1 + coupling kernel runs one workgroup per compute unit on 128-token x 64-rank tiles. What it saves, the
-// round trip of Z, grows with b r per token; what it pays, a stage 1 on tiles of half the arithmetic intensity of the
-// GEMM's, grows with n_in r. Input blocks longer than 256 columns lose to three kernels (graph replays on one card: 11008 ->
-// 4096, r = 1024 at 2048 / 8192 tokens 121 / 504 against 100 / 400 us; 8192 -> 2048, r = 768: 81 / 291 against 69 / 232). Up to 256
-// the fused kernel is ahead while its rounds of workgroups are full (r = 1024, 4096 x 4096 at 4096 tokens 145 against 170;
-// 2048 -> 8192, r = 512 at 8192 tokens 168 against 184) and behind with a last round half empty (r = 640 at 4096 / 8192
-// tokens, 1.25 / 2.5 rounds: 113 / 214 against 98 / 196); with too few tiles it leaves too much of the chip idle.
+// The fused stage 1 + coupling kernel runs one workgroup per compute unit on tiles of 64 ranks and 128 tokens (64 up to 128
+// tiles). What it saves, the round trip of Z, grows with b r per token; what it pays, a stage 1 on tiles of half the
+// arithmetic intensity of the GEMM's and a last round that is partly empty, grows with n_in r: a workgroup walks n_in
+// indices. Graph replays on one card, fused against three kernels in us:
+//   short inputs, whatever the rounds: 768 -> 2304, b = 6, r = 192 at 12608 / 24576 tokens (1.16 / 2.25 rounds) 62 / 102
+//     against 69 / 117; b = 3, r = 128 at 6304 (0.39) 24.6 against 31.0; 1152 wide, b = 9, r = 640 at 20000 (6.1) 202 / 250;
+//   n_in = 2048: ahead from 0.7 of the rounds on (2048 -> 8192, b = 16, r = 512 at 6304 / 10000 tokens 144 / 217 against
+//     158 / 241), behind at 0.62 with r = 256 (90 / 85);
+//   longer inputs: only with full rounds (r = 1024, 4096 x 4096 at 4096 tokens 145 / 170; r = 640 at 4096 / 8192 tokens, 1.25 /
+//     2.5 rounds: 113 / 214 against 98 / 196); with too few tiles it leaves too much of the chip idle.
+// Input blocks longer than 256 columns lose to three kernels where the stage-1 GEMM fills its 256-wide tiles or the input is long
+// (11008 -> 4096, r = 1024 at 2048 / 8192 tokens 121 / 504 against 100 / 400; 8192 -> 2048, r = 256 at 8192 105 / 94). With ranks
+// up to 256 and a shorter input the fused kernel is ahead: 3072 -> 768, r = 192, b = 6 at 32768 tokens 138 / 153, r = 128, b = 3
+// at 6304 24.6 / 29.9, 2048 -> 2048, b = 4, r = 256 at 24576 118 / 144; 4608 -> 1152, b = 9, r = 256 at 8192 / 24576 56 / 176
+// against 66 / 198, but 92 / 78 at 10000 (1.23 rounds).
 bool fused_pays(int64_t T, int n_in, int b, int r) {
     const int q = n_in / b;
-    const int64_t tiles = blast_fused_tiles(T, r), rounds = (tiles + 255) / 256;
-    return q <= 256 && tiles >= (q <= 128 ? 80 : 120) && (rounds == 1 || tiles * 10 >= rounds * 256 * 9);
+    const int64_t tiles = blast_fused_tiles(T, r), wgs = tiles <= 128 ? 2 * tiles : tiles;
+    const int64_t slots = (wgs + 255) / 256 * 256;
+    if (q > 256) {
+        if (r > 256) return false;
+        return n_in <= 3072 ? wgs * 4 > slots * 3 : n_in <= 4608 && tiles >= 224 && wgs * 10 >= slots * 9;
+    }
+    if (n_in <= 1280) return tiles >= 80;
+    return tiles >= (q <= 128 ? 80 : 120) && (slots == 256 || wgs * 10 >= slots * (n_in <= 2048 ? 7 : 9));
 }
 // Up to this many tokens the coupling runs as one thread per 8 outputs; from there on the MFMA coupling kernel on its
 // 16-token tiles is ahead (BLAST 4096 x 4096, r = 640: 13.6 against 14.4 us at 33 tokens, 16.5 against 15.9 at 64,

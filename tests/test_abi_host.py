@@ -361,3 +361,20 @@ def test_python_wrappers_reject_mismatched_tensors(monkeypatch):
         B.lowrank_forward.marshal(bf(T, n), bf(r, n + 8), bf(48, r), bf(T, 48), 0, ws)
     with pytest.raises(ValueError):
         B.dense_reference_forward.marshal(bf(T, n), bf(n, n + 8), bf(T, n))
+
+
+@pytest.mark.parametrize("T,n_in,b,r,fused", [
+    (12608, 768, 6, 192, True), (24576, 768, 6, 192, True), (6304, 768, 3, 128, True), (2048, 1152, 9, 256, False),  # short inputs: any round
+    (10000, 2048, 16, 512, True), (16384, 2048, 16, 256, True), (10000, 2048, 16, 256, False),                       # 0.7 of the rounds
+    (4096, 4096, 16, 1024, True), (8192, 4096, 16, 640, False), (10000, 4096, 16, 256, False),                       # full rounds
+    (32768, 3072, 6, 192, True), (24576, 3072, 6, 192, False), (6304, 3072, 3, 128, True), (10000, 3072, 3, 128, False),
+    (8192, 4608, 9, 256, True), (10000, 4608, 9, 256, False),                                                        # long blocks
+    (8192, 4096, 8, 512, False), (8192, 11008, 16, 1024, False), (8192, 8192, 16, 256, False),
+])
+def test_blast_execution_by_size(T, n_in, b, r, fused):
+    """Which of the two large-batch executions a call takes, told by its workspace: the fused stage 1 + coupling keeps A only,
+    the three kernels Z beside it (or both of a chunk in two parts)."""
+    flags = (B.BLAST_FUSED_STAGE12, B.BLAST_THREE_KERNELS)
+    sizes = [B.blast_workspace_bytes(T, n_in, 64 * b, b, r, B.BF16, B.BLAST_PACKED | f) for f in flags]
+    assert sizes[0] != sizes[1]
+    assert B.blast_workspace_bytes(T, n_in, 64 * b, b, r, B.BF16, B.BLAST_PACKED) == sizes[0 if fused else 1]

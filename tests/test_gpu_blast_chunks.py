@@ -92,3 +92,26 @@ def test_windows_with_the_8_bit_intermediate(T, q, b, r):
     X = bi.activations(T, b * q, "bf16", seed=r)
     Y = gu.to_f64(gu.run_blast(X, lay, gu.B.BLAST_Z_FP8, packed=True))
     assert gu.rel_err(Y, quant.blast_forward_qz(X.f64, lay.U.f64, lay.S.f64, lay.V.f64)[0]) <= gu.TOL["bf16"]
+
+
+@pytest.mark.parametrize("T,n_in,n_out,b,r", [
+    (6145, 768, 96, 3, 128), (8193, 768, 96, 3, 128),                    # 64-token tiles, 128-token tiles; a last tile of one token
+    (6200, 3072, 48, 6, 72),                                             # blocks of 512: two groups of rank indices, the last of 8
+    (32641, 1536, 24, 3, 8),                                             # one group, the last tile of one token
+])
+def test_fused_stage12_with_few_blocks(T, n_in, n_out, b, r):
+    """The rule's fused execution on few, long blocks, all tokens against the three kernels (each rounds two intermediates and
+    the output to bf16: 6 * 2^-9 of the largest value between them) and the first and last rows against the oracle."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    B = gu.B
+    lay = bi.blast_layer(n_in, n_out, b, r, "bf16", seed=T)
+    X = bi.activations(T, n_in, "bf16", seed=r)
+    sizes = [B.blast_workspace_bytes(T, n_in, n_out, b, r, B.BF16, B.BLAST_PACKED | f) for f in (0, B.BLAST_FUSED_STAGE12)]
+    assert sizes[0] == sizes[1]
+    Y = gu.to_f64(gu.run_blast(X, lay, 0, packed=True))
+    three = gu.to_f64(gu.run_blast(X, lay, B.BLAST_THREE_KERNELS, packed=True))
+    assert abs(Y - three).max() <= 6 * 2.0 ** -9 * abs(three).max()
+    rows = np.r_[0:64, T - 65:T]
+    assert gu.rel_err(Y[rows], oracle.blast_forward(X.f64[rows], lay.U.f64, lay.S.f64, lay.V.f64)) <= gu.TOL["bf16"]
