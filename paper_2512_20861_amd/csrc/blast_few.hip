@@ -4,10 +4,10 @@
 //   Z[t][j][rho] = sum_c X[t][j q + c] Vt[j][rho][c]          (rounded to bf16, on chip)
 //   A[t][i][rho] = sum_j S[i][j][rho] Z[t][j][rho]
 //
-// The coupling reduces over the input blocks j, so a workgroup owns 8 (or 4) rank indices of ALL blocks: a tile of 16 weight rows
-// is 8 rank indices of two neighbouring blocks (or 4 of four). Up to 8 tokens the other operand is 8 tokens of one block and 8 of the other
-// (half of the product is meant), up to 16 it is 16 tokens of either (two MFMAs per step). The wavefronts take a pair of
-// blocks each, or, with few blocks, a part of a pair's contraction index. Z goes through LDS once as [rho][t][j], where every rank index is one 16x16x16 MFMA against its 16x16
+// The coupling reduces over the input blocks j, so a workgroup owns some rank indices of ALL blocks: a tile of 16 weight rows is
+// 16 / JW rank indices of JW neighbouring blocks, 2, 4, 8 or 16 of them. The other operand is 16 / JW tokens of each of these blocks (one JW-th of
+// the product is meant); with two blocks, up to 16 tokens of either (two MFMAs per step). The wavefronts take a tile of
+// blocks each, or, with few tiles, a part of a tile's contraction index. Z goes through LDS once as [rho][t][j], where every rank index is one 16x16x16 MFMA against its 16x16
 // coupling tile, and a lane then holds all 8 rank indices of four (token, output block): 16-byte stores.
 //
 // What bounds it: a launch, one memory latency and the fetch of instructions that run once, as in the kernel for the product
@@ -180,7 +180,9 @@ __global__ __launch_bounds__(512) void blast_few_kernel(FewArgs a, SkinnySource 
         if (l16 < a.T && i < a.b) {
             bf16_t* p = a.A + ((int64_t)l16 * a.b + i) * a.r + rho0;
             if constexpr (RANKS == 8) *(u32x4*)p = u32x4{pack2_bf16(d[0][e], d[1][e]), pack2_bf16(d[2][e], d[3][e]), pack2_bf16(d[4][e], d[5][e]), pack2_bf16(d[6][e], d[7][e])};
-            else *(uint2*)p = make_uint2(pack2_bf16(d[0][e], d[1][e]), pack2_bf16(d[2][e], d[3][e]));
+            else if constexpr (RANKS == 4) *(uint2*)p = make_uint2(pack2_bf16(d[0][e], d[1][e]), pack2_bf16(d[2][e], d[3][e]));
+            else if constexpr (RANKS == 2) *(unsigned*)p = pack2_bf16(d[0][e], d[1][e]);
+            else *p = float_to_bf16(d[0][e]);
         }
     }
 }
@@ -217,20 +219,29 @@ FewArgs few_args(int jw, const void* X, const void* Vt, const void* Sp, void* A,
 
 template <int JW, int XT, int SRC>
 hipError_t launch_few(const FewArgs& a, const SkinnySource& src, hipStream_t s) {
-    return a.splits > 1 ? launch_few<JW, XT, SRC, true>(a, src, s) : launch_few<JW, XT, SRC, false>(a, src, s);
+    if constexpr (JW > 2) return launch_few<JW, XT, SRC, true>(a, src, s);   // (at most four tiles of blocks, and wide_tile's q: there are always parts)
+    else return a.splits > 1 ? launch_few<JW, XT, SRC, true>(a, src, s) : launch_few<JW, XT, SRC, false>(a, src, s);
 }
 
-// Long blocks at a handful of tokens: four blocks to a tile, twice the workgroups of half the weights each. Whole calls on graph
-// replays, against two blocks, at 1 / 4 tokens: 8192 -> 2048, r = 768, 16 blocks 6.9 / 7.2 against 7.4 / 7.6 us, 3072 -> 768,
-// b = 3, r = 128 5.7 / 5.6 against 6.0 / 6.2; down of the 16-layer chain of 2048 / 8192, its weights cold, 5.8 against 7.3 at one
-// token. With blocks of 128 (2048 x 2048) 5.4 / 5.6 against 5.2 / 5.3, of 256 level.
-bool four_blocks(int64_t T, int q) { return T <= 4 && q >= 512; }
+// How many blocks to a tile: more of them are more workgroups, r JW / 16, of fewer weights each, for fewer tokens. The most that the
+// tokens leave and that stay one round, one workgroup to a compute unit (their LDS). Whole calls on graph replays with 2 / 4 / 8 / 16 blocks
+// to a tile, 16 input blocks unless said: 1 token 8192 -> 768, r = 32 7.05 / 6.63 / 5.94 / 5.75 us, 8192 -> 2048, r = 384 7.44 / 6.98 / 6.37 /
+// 6.43 (384 workgroups), 4096 x 4096, r = 256 6.23 / 6.16 / 5.87 / 5.78, r = 1024 6.92 / 6.94 / 6.87 / 7.63 (1024); 2 tokens 8192 -> 2048,
+// r = 192 7.20 / 6.81 / 6.17; 4 tokens 3072 -> 768, 3 blocks, r = 128 6.62 / 6.15. With more than 8 blocks two to a tile need no sum of
+// parts, and short ones are as fast that way: 4 tokens of 2048 x 2048, blocks of 128, r = 256 5.85 / 6.08, blocks of 256 level;
+// 2 tokens, blocks of 128, r = 512 6.53 / 6.78 / 6.59.
+bool wide_tile(int jw, int64_t T, int q, int b, int r) {
+    return T * jw <= 16 && b > jw / 2 && (int64_t)r * jw <= 16 * 256 && q > 32 && (b <= 8 || q * jw >= 2048);
+}
 
 }  // namespace
 
 hipError_t launch_blast_few(const void* X, const void* Vt, const void* Sp, void* A, int64_t T, int n_in, int b, int r, hipStream_t s) {
     if (T > kBlastFewTokens) return hipErrorInvalidValue;
-    if (four_blocks(T, n_in / b)) return launch_few<4, 1, kSrcInput>(few_args(4, X, Vt, Sp, A, T, n_in, b, r), {}, s);
+    const int q = n_in / b;
+    if (wide_tile(16, T, q, b, r)) return launch_few<16, 1, kSrcInput>(few_args(16, X, Vt, Sp, A, T, n_in, b, r), {}, s);
+    if (wide_tile(8, T, q, b, r)) return launch_few<8, 1, kSrcInput>(few_args(8, X, Vt, Sp, A, T, n_in, b, r), {}, s);
+    if (wide_tile(4, T, q, b, r)) return launch_few<4, 1, kSrcInput>(few_args(4, X, Vt, Sp, A, T, n_in, b, r), {}, s);
     const FewArgs a = few_args(2, X, Vt, Sp, A, T, n_in, b, r);
     return T <= 8 ? launch_few<2, 1, kSrcInput>(a, {}, s) : launch_few<2, 2, kSrcInput>(a, {}, s);
 }

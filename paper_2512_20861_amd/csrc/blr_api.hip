@@ -124,11 +124,19 @@ bool fused_pays(int64_t T, int n_in, int b, int r) {
 constexpr int64_t kSmallCouplingTokens = 48;
 
 // Few tokens: stage 1 and the coupling in one launch instead of two or, up to 48 tokens, the coupling as one thread per 8 outputs.
-// Every workgroup of 8 rank indices reads all of X. Whole calls as graph replays, one card, against stage 1 and coupling apart, at
-// 1 / 8 / 16 tokens: 4096 x 4096, r = 640 6.5 / 6.8 / 7.7 against 7.8 / 8.2 / 9.0 us; 8192 -> 2048, r = 768 7.4 / 7.8 / 9.5
-// against 8.7 / 9.1 / 10.1; 1152 -> 4608, b = 9, r = 256 5.4 / 5.5 / 5.9 against 8.9 / 9.4 / 9.6; with the longest input,
-// 11008 -> 4096, r = 1024, 9.7 / 13.1 / 18.1 against 10.7 / 12.1 / 14.0, behind from 4 tokens on.
-bool blast_few_pays(int64_t T, int n_in) { return T <= (n_in <= 8192 ? kBlastFewTokens : 2); }
+// Every workgroup reads all of X and 16 n_in weights (few of them to a workgroup up to 4 tokens: blast_few.hip). Whole calls as graph replays, one card,
+// against stage 1 and coupling apart, at 1 / 8 / 16 tokens: 4096 x 4096, r = 640 6.5 / 6.8 / 7.7 against 7.8 / 8.2 / 9.0 us; 1152 ->
+// 4608, b = 9, r = 256 5.4 / 5.5 / 5.9 against 8.9 / 9.4 / 9.6; with the longest input, 11008 -> 4096, r = 1024, 9.7 / 13.1 /
+// 18.1 against 10.7 / 12.1 / 14.0, behind from 4 tokens on.
+// Beyond 8 tokens a workgroup has 8 rank indices and n_in columns of up to 16 tokens to read whatever the rank, and stage 1 by itself shrinks
+// with the rank: long inputs in 16 blocks need one to fill the chip with (16 tokens: 6144 wide, r = 32 / 128 / 256 7.39 / 7.51 / 7.64 against 7.17 /
+// 7.48 / 7.76; 8192 wide, r = 128 / 256 / 512 8.07 / 8.20 / 8.86 against 7.54 / 7.83 / 8.88); in 2 ... 8 blocks it is ahead from r = 64 on (8192 wide,
+// 4 / 8 blocks, r = 64 8.37 / 8.38 against 8.67 / 9.61); with a single block half of every tile is absent (r = 256: 4096 wide 8.42 against 9.05, 6144 level, 8192
+// 11.06 against 10.69).
+bool blast_few_pays(int64_t T, int n_in, int b, int r) {
+    if (T <= 8) return T <= 2 || n_in <= 8192;
+    return T <= kBlastFewTokens && (n_in <= 4096 || (n_in <= 8192 && b > 1 && (b <= 8 || 8 * (int64_t)r >= n_in - 4096)));
+}
 
 // The single kernel for few, wide blocks: forced by its flag, else where it was measured ahead of the three kernels.
 bool blast_narrow_possible(int64_t T, int n_in, int n_out, int b, int r, unsigned flags) {
@@ -427,7 +435,7 @@ static blr_status blast_run(const void* X, const void* U, const void* S, const v
         return last ? run_stage3(0, T, true) : BLR_OK;
     }
     // Few tokens: stage 1 and the coupling in one launch
-    if (!(flags & (BLR_BLAST_THREE_KERNELS | BLR_BLAST_Z_FP8)) && blast_few_pays(T, n_in)) {
+    if (!(flags & (BLR_BLAST_THREE_KERNELS | BLR_BLAST_Z_FP8)) && blast_few_pays(T, n_in, b, r)) {
         if (first) {
             blr_status st = from_hip(launch_blast_few(X, Vt, Sp, Aws, T, n_in, b, r, s));
             if (st != BLR_OK) return st;

@@ -30,6 +30,30 @@ def test_against_the_oracle(T, b, q, p, r):
     assert gu.rel_err(gu.to_f64(Y), gu.to_f64(three)) <= gu.TOL["bf16"]
 
 
+@pytest.mark.parametrize("T", [1, 2, 3, 4])
+@pytest.mark.parametrize("b,q,p,r", [
+    (16, 136, 16, 256), (16, 264, 16, 512),             # 16 blocks to a tile at one token, 8 up to two; r that leaves one round with 8
+    (15, 520, 8, 104), (9, 264, 8, 104),                # absent blocks in the only tile and in the last of two, each width
+    (6, 264, 8, 24), (5, 40, 80, 152),                  # 8 up to two tokens, 4 up to four; two steps, a partial one
+    (3, 1032, 8, 1032)])                                # a round and two rank indices over: two blocks to a tile
+def test_blocks_to_a_tile(T, b, q, p, r):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    B = gu.B
+    lay = bi.blast_layer(b * q, b * p, b, r, "bf16")
+    X = bi.activations(T, b * q, "bf16", seed=T)
+    Y = gu.run_blast(X, lay, packed=True)
+    assert gu.rel_err(gu.to_f64(Y), oracle.blast_forward(X.f64, lay.U.f64, lay.S.f64, lay.V.f64)) <= gu.TOL["bf16"]
+    # a token's infinities stay its own: the tile multiplies it with the other tokens' blocks too
+    U, S, V = (gu.to_dev(t) for t in (lay.U, lay.S, lay.V))
+    packed, x = B.blast_pack(U, S, V, b * q, b * p, b, r), gu.to_dev(X).clone()
+    x[T - 1, q - 1] = x[T - 1, (b - 1) * q] = float("inf")
+    Z = B.blast_forward(x, U, None, packed, gu.empty_out(T, b * p, "bf16"), b, r, B.BLAST_PACKED)
+    torch.cuda.synchronize()
+    assert torch.equal(Z[:T - 1], Y[:T - 1]) and not bool(torch.isfinite(Z[T - 1]).any())
+
+
 @pytest.mark.parametrize("op,params", [("monarch", dict(nblocks=4, r_square=64, r_mlp=1056)), ("blast", dict(b=4, r_square=136, r_mlp=264))])
 @pytest.mark.parametrize("T", [3, 16, 17, 32, 33])
 def test_combined_groups(op, params, T):
