@@ -48,7 +48,8 @@ Linear linear_of(const blr_chain_desc& d, int which) {  // 0: q, k, v; 1: o; 2: 
 }
 
 // ---- every step a call of the public entry points ----------------------------------------------------
-blr_status run_linear(const blr_chain& c, const Linear& l, const blr_chain_factors& f, const void* X, void* Y, hipStream_t s) {
+// gathered: X of a Monarch o or down lies block by block already
+blr_status run_linear(const blr_chain& c, const Linear& l, const blr_chain_factors& f, const void* X, void* Y, hipStream_t s, bool gathered = false) {
     const blr_chain_desc& d = c.d;
     void* ws = c.buf.workspace;
     const size_t wsb = c.buf.workspace_bytes;
@@ -56,7 +57,7 @@ blr_status run_linear(const blr_chain& c, const Linear& l, const blr_chain_facto
         if (l.members > 1) return blr_blast_group_forward(X, f.second, f.first, Y, d.T, l.n_in, l.n_out, d.b, l.r, l.members, BLR_BF16, 0, ws, wsb, s);
         return blr_blast_forward(X, f.second, nullptr, f.first, Y, d.T, l.n_in, l.n_out, d.b, l.r, BLR_BF16, BLR_BLAST_PACKED, ws, wsb, s);
     }
-    if (l.in_blocked) return blr_monarch_forward(X, f.first, f.second, Y, d.T, l.n_in, l.n_out, d.b, l.r, BLR_BF16, BLR_MONARCH_IN_BLOCKED, ws, wsb, s);
+    if (l.in_blocked) return blr_monarch_forward(X, f.first, f.second, Y, d.T, l.n_in, l.n_out, d.b, l.r, BLR_BF16, gathered ? 0 : BLR_MONARCH_IN_BLOCKED, ws, wsb, s);
     return blr_monarch_rect_forward(X, f.first, f.second, Y, d.T, l.n_in, l.members * l.n_out, d.b, l.members * d.b, l.r / d.b, BLR_BF16,
                                     BLR_MONARCH_OUT_BLOCKED, ws, wsb, s);
 }
@@ -84,13 +85,26 @@ bool norm_inside(const blr_chain& c, int which, const blr_chain_factors& f) {
 
 // A group and the elementwise step behind it: 3 members, their scaled sum; 2, SiLU(first) * second. One launch for the last product
 // and the step where the group runs that way (up to 32 tokens gemm_skinny_kernel, from 65 on the tiles), else a call each.
-struct Group { bool tail; GroupTail t; };
+//
+// gathered: an input block of a Monarch o or down is b runs of n_in / b^2 elements of the blocked order, and the matrix kernels read
+// runs of whole steps of 32. Where they are none, the combined result leaves in the order in which the next linear's re-ordered
+// factor counts, an input block in one piece. A layer of 768 / 3072 in 4 blocks (runs of 48) at 1 / 4 / 16 / 32 tokens 44.5 / 49.1 / 50.9 /
+// 57.6 us with the runs (first products on the portable kernel), 25.6 / 29.1 / 30.2 / 33.3 in one piece; of 2048 / 8192 in 16 blocks (runs of 8)
+// 47.6 / 54.4 / 58.8 / 70.6 and 34.2 / 38.6 / 43.1 / 52.3, at 1000 tokens 212 and 159.
+struct Group { bool tail, gathered; GroupTail t; };
 Group group_of(const blr_chain& c, int which, const blr_chain_factors& f, void* out) {
     const Linear l = linear_of(c.d, which);
     Group g{};
     g.tail = group_tail(c.d.blast, f.second, c.d.T, l.n_in, l.n_out, c.d.b, l.r, l.members, c.buf.workspace, &g.t);
-    g.t.product.C = out;
-    g.tail = g.tail && gemm_combine_supported(g.t.product, l.members);
+    GemmDesc& p = g.t.product;
+    p.C = out;
+    const int run = l.n_out / c.d.b / c.d.b;
+    if (!c.d.blast && run % 32) {
+        p.c_gs = p.c_div = run; p.c_hi = l.n_out / c.d.b; p.c_lo = 1;
+        g.gathered = true;
+    }
+    g.tail = g.tail && gemm_combine_supported(p, l.members);
+    g.gathered = g.gathered && g.tail;
     return g;
 }
 blr_status run_group(const blr_chain& c, int which, const blr_chain_factors& f, const SkinnySource* norm, void* wide, void* out, hipStream_t s) {
@@ -123,7 +137,8 @@ blr_status run_pass(const blr_chain& c, hipStream_t s) {
     const blr_chain_desc& d = c.d;
     const blr_chain_buffers& b = c.buf;
     const blr_chain_layer& L0 = c.layers[0];
-    const bool inside = group_of(c, 0, L0.qkv, b.a).tail && group_of(c, 2, L0.gate_up, b.m).tail && norm_inside(c, 0, L0.qkv) && norm_inside(c, 2, L0.gate_up);
+    const Group qkv = group_of(c, 0, L0.qkv, b.a), gate_up = group_of(c, 2, L0.gate_up, b.m);     // (every layer's: the same sizes, and all factors are aligned)
+    const bool inside = qkv.tail && gate_up.tail && norm_inside(c, 0, L0.qkv) && norm_inside(c, 2, L0.gate_up);
     blr_status st = BLR_OK;
     auto step = [&](auto&& f) { if (st == BLR_OK) st = f(); };
     // inside: the residual stream moves between two buffers, the workgroups of a product all read the old one, one of them writes the new one
@@ -138,10 +153,10 @@ blr_status run_pass(const blr_chain& c, hipStream_t s) {
         const bool last = i + 1 == d.layers;
         const SkinnySource n1 = i ? norm(b.h2, b.dn, b.h) : norm(b.h, nullptr, nullptr), n2 = norm(b.h, b.o, b.h2);
         step([&] { return run_group(c, 0, L.qkv, inside ? &n1 : nullptr, b.qkv, b.a, s); });
-        step([&] { return run_linear(c, linear_of(d, 1), L.o, b.a, b.o, s); });
+        step([&] { return run_linear(c, linear_of(d, 1), L.o, b.a, b.o, s, qkv.gathered); });
         if (!inside) step([&] { return blr_residual_add_rmsnorm(b.h, b.o, b.n, d.T, d.hidden, d.eps, BLR_BF16, s); });
         step([&] { return run_group(c, 2, L.gate_up, inside ? &n2 : nullptr, b.gu, b.m, s); });
-        step([&] { return run_linear(c, linear_of(d, 3), L.down, b.m, b.dn, s); });
+        step([&] { return run_linear(c, linear_of(d, 3), L.down, b.m, b.dn, s, gate_up.gathered); });
         if (!inside) step([&] { return blr_residual_add_rmsnorm(b.h, b.dn, last ? nullptr : b.n, d.T, d.hidden, d.eps, BLR_BF16, s); });
     }
     if (inside) step([&] { return from_hip(launch_add(b.h2, b.dn, b.h, d.T * d.hidden, s)); });

@@ -44,6 +44,7 @@ struct SkinnyArgs {
     int slots;                        // steps a wavefront's part of LDS holds (<= SK_RD)
     int mtiles;                       // tiles of 16 MT tokens
     int64_t a_ms, b_ms;               // MEM: distance of the members' operands
+    int c_seg;                        // MEM: columns in runs of so many, c_s apart (0: one run)
     float scale;
 };
 
@@ -193,7 +194,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_skinny_kernel(SkinnyArgs a, Skin
         *(f32x4*)(part + ((wave * MT + mt) * 16 + l16) * PSTR + 4 * kg) = acc[mt];
     __syncthreads();
     const int c = tid & 15, ci = i0 + c;                // (64 NW is a multiple of 16: a thread keeps its column)
-    bf16_t* Cc = a.C + g * a.c_gs + (PACK ? (ci / a.n) * a.c_s + (ci % a.n) * a.c_i : s * a.c_s + ci * a.c_i);
+    bf16_t* Cc = a.C + g * a.c_gs + (PACK ? (ci / a.n) * a.c_s + (ci % a.n) * a.c_i : MEM > 1 && a.c_seg ? (ci / a.c_seg) * a.c_s + ci % a.c_seg : s * a.c_s + ci * a.c_i);
     for (int o = tid; o < MT * 256; o += 64 * NW) {
         const int m = o >> 4;
         if (m_base + m >= a.M || ci >= rows_n) continue;
@@ -293,12 +294,15 @@ hipError_t launch_gemm_skinny(const GemmDesc& d, hipStream_t s) {
 }
 
 bool gemm_combine_supported(const GemmDesc& d, int members) {
-    return d.M > 32 ? gemm_members_supported(d, members) : d.b_div == 0 && skinny_gemm_supported(d) && mfma_gemm_supported(d);
+    if (d.M > 32) return gemm_members_supported(d, members);
+    return d.b_div == 0 && (d.c_div == 1 || d.c_lo == 1) && d.G <= 65535 && mfma_gemm_supported(d);
 }
 hipError_t launch_gemm_combine(const GemmDesc& d, int members, const Combine& c, hipStream_t s) {
     if (d.M > 32) return launch_gemm_members(d, members, c, s);
     SkinnyArgs a = skinny_args(d);
+    a.n = d.N;
     a.a_ms = c.a_ms; a.b_ms = c.b_ms; a.scale = c.scale;
+    if (d.c_div > 1) { a.c_seg = d.c_div; a.c_s = d.c_hi; }
     const dim3 grid((unsigned)((a.n + SK_BN - 1) / SK_BN), 1u, (unsigned)d.G);
     if (members == 3) return a.M > 16 ? launch_skinny<2, 12, kSrcInput, false, false, 3>(a, {}, grid, s) : launch_skinny<1, 12, kSrcInput, false, false, 3>(a, {}, grid, s);
     return a.M > 16 ? launch_skinny<2, 8, kSrcInput, false, false, 2>(a, {}, grid, s) : launch_skinny<1, 8, kSrcInput, false, false, 2>(a, {}, grid, s);

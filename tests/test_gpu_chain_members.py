@@ -39,3 +39,26 @@ def test_members_on_tiles(op, hidden, mlp, params, T):
     ref = oc.chain_forward(x.f64[rows], layers, _lin)
     sel = torch.from_numpy(rows).cuda()
     assert gu.rel_err(gu.to_f64(got[0][sel]), ref) <= 2e-2
+
+
+# runs of 48 elements (16-byte stores), of 12 and of 9 (element by element), of 8 and of a single one
+@pytest.mark.parametrize("T", [1, 4, 16, 17, 32, 33, 70, 900])
+@pytest.mark.parametrize("hidden,mlp,params", [
+    (768, 3072, dict(nblocks=4, r_square=256, r_mlp=256)), (768, 1152, dict(nblocks=8, r_square=256, r_mlp=264)),
+    (2048, 4096, dict(nblocks=16, r_square=256, r_mlp=512)), (1152, 576, dict(nblocks=24, r_square=192, r_mlp=192))])
+def test_input_blocks_in_one_piece(hidden, mlp, params, T):
+    """Monarch: o and down whose input blocks are runs that the matrix kernels do not read."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    from paper_2512_20861_amd.chain import DeviceChain
+    layers = bi.chain_layers("monarch", n_layers=2, hidden=hidden, mlp=mlp, params=params, dtype="bf16")
+    x = bi.activations(T, hidden, "bf16", seed=T)
+    chain = DeviceChain(layers, T, eps=oc.EPS)
+    assert chain._native
+    got = [chain.forward(gu.to_dev(x)).clone() for _ in range(3)]
+    torch.cuda.synchronize()
+    assert all(torch.equal(g, got[0]) for g in got)
+    rows = np.unique([t for t in (0, 31, 63, 64, 127, 128, T // 2, T - 3, T - 1) if 0 <= t < T])
+    ref = oc.chain_forward(x.f64[rows], layers, _lin)
+    assert gu.rel_err(gu.to_f64(got[0][torch.from_numpy(rows).cuda()]), ref) <= 2e-2
