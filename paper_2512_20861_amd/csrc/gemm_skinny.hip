@@ -312,10 +312,12 @@ bool skinny_source_supported(const GemmDesc& d) {
     return d.M >= 1 && d.M <= kSourceTokens && mfma_gemm_supported(d) && shape_ok(d, 1) && d.K <= 4096;      // (rows of 8 tokens: 64 KB of LDS behind the weights)
 }
 
-// From this many 16-row tiles on a wavefront owns a tile: there are workgroups enough (three a compute unit before), and the norm
-// is computed a quarter as often. (Measured on first products of a BLAST chain of 2048 / 8192 in an earlier split of its work: a
-// layer 37.8 against 41.4 us at 1 token; between 512 and 768 tiles the limit is not resolved.)
-constexpr int64_t kRowsTiles = 768;
+// From this many 16-row tiles on a wavefront owns a tile: there are workgroups enough, and the norm is computed a quarter as often.
+// A Monarch chain layer at 1 / 2 / 3 tokens, owned against four or eight wavefronts to a tile: 4096 / 8192 in 16 blocks, r = 1024 (3072 and 2048
+// tiles) 52.9 / 56.1 / 59.8 against 55.3 / 60.6 / 65.6 us; 2048 / 8192 in 16 blocks, r = 512 (1536 and 1024) 34.2 / 36.1 / 38.0 against 34.1 / 36.0 /
+// 38.3; in 8 blocks, r = 1024 (the same) 45.1 / 47.1 / 49.1 against 44.6 / 46.7 / 49.1; 4096 / 8192 in 4 blocks, r = 1024 and 1536 (768 each)
+// 63.1 / 66.6 / 70.2 against 61.6 / 64.3 / 67.1.
+constexpr int64_t kRowsTiles = 2048;
 
 hipError_t launch_gemm_skinny_norm(const GemmDesc& d, const SkinnySource& src, hipStream_t s) {
     SkinnyArgs a = skinny_args(d);

@@ -41,11 +41,14 @@ def test_members_on_tiles(op, hidden, mlp, params, T):
     assert gu.rel_err(gu.to_f64(got[0][sel]), ref) <= 2e-2
 
 
-# runs of 48 elements (16-byte stores), of 12 and of 9 (element by element), of 8 and of a single one
-@pytest.mark.parametrize("T", [1, 4, 16, 17, 32, 33, 70, 900])
+# runs of 48 elements (16-byte stores), of 12 (element by element), of 8, of two and one, of three. In the last two the normed first
+# products have 2304 to 3840 tiles: a wavefront owns 16 rows, the last workgroup of an output block has two tiles or one, and with
+# input blocks of 48 the last step is a partial one.
+@pytest.mark.parametrize("T", [1, 3, 4, 16, 17, 32, 33, 70, 900])
 @pytest.mark.parametrize("hidden,mlp,params", [
     (768, 3072, dict(nblocks=4, r_square=256, r_mlp=256)), (768, 1152, dict(nblocks=8, r_square=256, r_mlp=264)),
-    (2048, 4096, dict(nblocks=16, r_square=256, r_mlp=512)), (1152, 576, dict(nblocks=24, r_square=192, r_mlp=192))])
+    (2048, 4096, dict(nblocks=16, r_square=256, r_mlp=512)), (1152, 576, dict(nblocks=24, r_square=576, r_mlp=576)),
+    (768, 768, dict(nblocks=16, r_square=1152, r_mlp=1152))])
 def test_input_blocks_in_one_piece(hidden, mlp, params, T):
     """Monarch: o and down whose input blocks are runs that the matrix kernels do not read."""
     if not torch.cuda.is_available():

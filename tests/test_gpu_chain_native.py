@@ -84,11 +84,9 @@ def test_copies_and_lifetimes(T):
 
 
 @pytest.mark.parametrize("op,hidden,mlp,params", [
-    # a model's widths: products on eight wavefronts (every first Monarch product, BLAST's down), rows owned by wavefronts
-    # (BLAST's first products of q/k/v and gate/up and its coupling in gate/up)
+    # a model's widths: first products of a Monarch chain on eight wavefronts, of a BLAST chain with their coupling
     ("monarch", 2048, 8192, dict(nblocks=4, r_square=512, r_mlp=512)), ("blast", 2048, 8192, dict(b=16, r_square=256, r_mlp=512)),
-    # rows owned by wavefronts: 800 and 784 tiles, 50 and 49 a block (a last workgroup of two tiles and of one), ranks that
-    # are no multiple of 16 or of 32, blocks of 40 and 72 columns (a partial last step)
+    # ranks that are no multiple of 16 or of 32, blocks of 40 and 72 columns (a partial last step)
     ("blast", 640, 1152, dict(b=16, r_square=264, r_mlp=392))])
 @pytest.mark.parametrize("T", [1, 3, 4])
 def test_wide_fused_chain(op, hidden, mlp, params, T):
