@@ -31,14 +31,6 @@ struct FewArgs {
     int slots;                                           // steps of 32 a wavefront's part of LDS holds
 };
 
-__device__ __attribute__((aligned(16))) const unsigned char zero_piece[16] = {0};
-
-__device__ __forceinline__ bf16x8 lds_read_frag(unsigned addr) {   // (reads the compiler can see wait for all direct loads)
-    bf16x8 v;
-    asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr) : "memory");
-    return v;
-}
-
 // JW: input blocks in a tile of 16 weight rows, 16 / JW rank indices each; XT: MFMAs per step, whose 16 XT columns are 16 XT / JW
 // tokens of each of the blocks; SRC: where the tokens' rows come from (skinny_source.h; computed rows: XT = 1); TAIL: a wavefront's part of the contraction index is no whole number of steps; SPLIT: pairs are split
 template <int XT, int SRC>

@@ -48,14 +48,6 @@ struct SkinnyArgs {
     float scale;
 };
 
-__device__ __attribute__((aligned(16))) const unsigned char zero_piece[16] = {0};
-
-__device__ __forceinline__ bf16x8 lds_read_frag(unsigned addr) {   // (reads the compiler can see wait for all direct loads)
-    bf16x8 v;
-    asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr) : "memory");
-    return v;
-}
-
 // MT: 16-token tiles (M <= 16 MT); NW: wavefronts; TAIL: K is no multiple of 32
 // ROWS: every wavefront owns 16 weight rows and the whole contraction index instead of a part of it (computed rows only:
 // the rows serve 16 NW outputs then, and there are no partial sums to add)

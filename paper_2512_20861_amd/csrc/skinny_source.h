@@ -1,5 +1,5 @@
-// The rows a few-token product multiplies, computed by every workgroup from what they are made of (SkinnySource), and the
-// small vector helpers that this takes. Included by the kernels that stream weights past a handful of tokens.
+// What the kernels that stream weights past a handful of tokens share: their fragment reads, and the rows such a product
+// multiplies, computed by every workgroup from what they are made of (SkinnySource).
 #pragma once
 #include "blr_common.h"
 
@@ -9,6 +9,14 @@ namespace {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));   // (arrays of HIP's uint4 struct stay in scratch memory)
+
+__device__ __attribute__((aligned(16))) const unsigned char zero_piece[16] = {0};   // the source of operand pieces past the contraction index
+
+__device__ __forceinline__ bf16x8 lds_read_frag(unsigned addr) {   // (reads the compiler can see wait for all direct loads)
+    bf16x8 v;
+    asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr) : "memory");
+    return v;
+}
 
 __device__ __forceinline__ void unpack8(u32x4 v, float (&f)[8]) {
 #pragma unroll
