@@ -114,6 +114,22 @@ def test_every_row_monarch(T, b, p, rp, q, order):
     agree(call(X), lambda t: call(X[t:t + 128].contiguous()))
 
 
+@pytest.mark.parametrize("b", [16, 17, 24, 48])
+@pytest.mark.parametrize("T,p", [(4096, 256), (4100, 328), (2570, 320)])
+def test_every_row_short_runs(T, b, p):
+    """First products whose columns go out in runs of a few elements: up to 16 batch entries walked, above that one tile to a workgroup."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    B, rp, q = gu.B, max(160 // b, 3), 64
+    gen = torch.Generator(device="cuda").manual_seed(T + b)
+    X, R, L = draw(gen, T, b * p), draw(gen, b, rp * b, p, scale=p ** -0.5), draw(gen, b, q, b * rp, scale=(b * rp) ** -0.5)
+    call = lambda x: B.monarch_rect_forward(x, R, L, gu.empty_out(x.shape[0], b * q, "bf16"), b, b, rp, B.MONARCH_OUT_BLOCKED)
+    Y, rows = call(X), sample(T)
+    check(gu, Y, rows, oracle.monarch_rect_forward(gu.to_f64(X)[rows], gu.to_f64(R), gu.to_f64(L), b, b, oracle.OUT_BLOCKED))
+    agree(Y, lambda t: call(X[t:t + 128].contiguous()))
+
+
 @pytest.mark.parametrize("T,q,r", [(3000, 600, 1024), (2900, 688, 1008), (3100, 576, 1024)])
 def test_every_row_blast(T, q, r):
     if not torch.cuda.is_available():
