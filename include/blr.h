@@ -67,7 +67,8 @@ typedef void* blr_stream;      /* a hipStream_t */
  * the coupling on the matrix cores) followed by the stage-3 GEMM, and (b) three kernels over
  * cache-resident token chunks (the paper's optimisation 5). By default the library picks (a) when
  * the input blocks are short and the call's 128-token x 64-rank tiles fill the chip, (b) otherwise; these flags
- * force one of them (mutually exclusive) so that tests and the benchmark can run both. */
+ * force one of them (mutually exclusive) so that tests and the benchmark can run both. One or two tokens
+ * run stage 1 and the coupling in one launch with either setting of BLR_BLAST_THREE_KERNELS. */
 #define BLR_BLAST_FUSED_STAGE12     0x800u
 #define BLR_BLAST_THREE_KERNELS     0x1000u
 /* flag of blr_blast_forward: force the single-kernel execution for layers of FEW, WIDE blocks (the b = 3, 6, 9

@@ -54,6 +54,18 @@ def test_blocks_to_a_tile(T, b, q, p, r):
     assert torch.equal(Z[:T - 1], Y[:T - 1]) and not bool(torch.isfinite(Z[T - 1]).any())
 
 
+@pytest.mark.parametrize("T", [1, 2])
+@pytest.mark.parametrize("b,q,p,r", [(16, 256, 256, 640), (5, 264, 72, 136)])
+def test_one_or_two_tokens_whichever_execution(T, b, q, p, r):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    lay = bi.blast_layer(b * q, b * p, b, r, "bf16")
+    X = bi.activations(T, b * q, "bf16", seed=T)
+    # (the separate launches add stage 1 up in another order: some of these sums round differently there)
+    assert torch.equal(gu.run_blast(X, lay, gu.B.BLAST_THREE_KERNELS, packed=True), gu.run_blast(X, lay, packed=True))
+
+
 @pytest.mark.parametrize("op,params", [("monarch", dict(nblocks=4, r_square=64, r_mlp=1056)), ("blast", dict(b=4, r_square=136, r_mlp=264))])
 @pytest.mark.parametrize("T", [3, 16, 17, 32, 33])
 def test_combined_groups(op, params, T):
