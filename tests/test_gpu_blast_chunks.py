@@ -17,6 +17,7 @@ torch = pytest.importorskip("torch")
     (520, 344, 16, 8, 520), (700, 584, 16, 8, 520),                      # ... in one round: eight wavefronts, four on a full chip
     (1200, 152, 24, 16, 264), (2700, 136, 16, 16, 264),                  # 128 x 128 and 128 x 192, by the estimate
     (500, 344, 16, 16, 640), (700, 344, 16, 16, 1024),                   # 256 x 128, 256 x 256
+    (300, 344, 16, 16, 1024), (640, 344, 16, 8, 1144), (800, 344, 16, 8, 1016),   # one round of 192 x 128, 128 x 192, 128 x 256
     # blocks read for themselves: short ones, too few tiles
     (700, 88, 64, 16, 136), (640, 184, 40, 8, 128),
     (270, 64, 40, 16, 1032),                                             # a partial last group of rank indices

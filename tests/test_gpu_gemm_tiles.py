@@ -1,5 +1,6 @@
 """Tiles of the bf16 products that the dispatch picks by estimate for several rounds of workgroups (128 x 192, 192 x 128 and
-128 x 128, two workgroups per compute unit) and the eight-wavefront tiles of a single round, each with a ragged last tile
+128 x 128, two workgroups per compute unit) and the eight-wavefront tiles of a single round (by their padded area where
+128 x 128 tiles would be more than one), each with a ragged last tile
 in rows and columns, contiguous and interleaved outputs, odd and even numbers of steps, a partial last step."""
 import numpy as np
 import pytest
@@ -23,6 +24,11 @@ torch = pytest.importorskip("torch")
     (1000, 1416, 2044), (300, 1480, 4090),            # ... and of 128
     (1000, 1280, 2050),                               # several rounds of 128 x 64
     (2529, 264, 389), (2529, 1288, 389),              # one round of 64 x 128, in steps of 64 and of 128
+    (1300, 640, 4092), (640, 512, 8189), (800, 320, 8188),                # one round of 192 x 128, 128 x 192 and 128 x 256
+    (2047, 192, 2300),                                # ... of 128 x 192, three steps
+    (1500, 192, 2299), (1500, 200, 2300), (1300, 192, 1148),              # three steps and a partial fourth on four stages
+    (1100, 1344, 2044),                               # half of the chip on 128 x 128
+    (300, 264, 10500),                                # 128 x 128 in one round, where 256 x 128 would fill the chip
 ])
 def test_dense_tiles(T, n_in, n_out):
     if not torch.cuda.is_available():
@@ -42,6 +48,7 @@ def test_dense_tiles(T, n_in, n_out):
     (1409, 4, 64, 32, 1530), (1153, 16, 64, 8, 572), (2047, 4, 64, 32, 1532),    # ... of two steps
     (4095, 4, 64, 48, 572),                           # 256 x 256
     (400, 16, 64, 66, 250), (300, 16, 64, 64, 250),   # 128 x 64, one round of four wavefronts and of eight
+    (1300, 4, 64, 48, 1020), (633, 16, 64, 12, 508), (780, 4, 64, 64, 2036),     # one round of 192 x 128, 128 x 192 and 128 x 256
 ])
 @pytest.mark.parametrize("order", ["interleaved", "blocked"])
 def test_monarch_tiles(T, b, p, rp, q, order):
