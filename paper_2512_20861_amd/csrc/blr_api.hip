@@ -76,8 +76,17 @@ struct BlastPlan {
 // The three-kernel path (stage-1 GEMM, MFMA coupling, stage-3 GEMM) walks the tokens in chunks whose intermediate (b*r bf16
 // per token; the coupling turns Z into A in place, every workgroup reads its tile of all blocks before it writes it) stays
 // well inside the 256 MB memory-side cache, so that it is produced and consumed without a round trip to HBM. The workspace
-// holds two parts of kChunkBytes: one buffer of both for the 16-bit Z, Z and A side by side for the 8-bit one.
+// holds two parts of kChunkBytes (kChunkBytesWide): one buffer of both for the 16-bit Z, Z and A side by side for the 8-bit one.
 constexpr size_t kChunkBytes = 48u << 20;
+// 64 MiB a part for the 16-bit Z from 24 KiB of it per token on (r = 768 in 16 blocks), as far as a chunk's X and Z stay under 224 MiB
+// together: a chunk more is three launches and their partial rounds, and beyond that X pushes Z out of the cache (11008 -> 4096 at
+// 8192 tokens: r = 1024 in chunks of 2048 / 3072 / 4096 / 8192 tokens, X and Z of 107 / 161 / 214 / 428 MiB, 414 / 396 / 384 / 434 us; r = 512
+// in chunks of 4096 / 8192, 150 / 300 MiB, 202 / 222). Against 48 MiB: 4096 x 4096, r = 1024 at 6304 tokens 215 -> 202, 8192 -> 2048, r = 768 at
+// 5000 140 -> 134, 11008 -> 4096, r = 1024 at 20000 955 -> 939; level where the rounds come out the same, as at 4096 tokens (188), up to
+// which the smaller parts stay. Lower ranks are level (4096 x 4096,
+// r = 640 at 8192 tokens 172 in chunks of 4096 and of 8192) and keep the smaller workspace.
+constexpr size_t kChunkBytesWide = 64u << 20, kWidePerToken = 24u << 10, kWideWithInput = 224u << 20;
+constexpr int64_t kWideTokens = 4096;
 // Tokens per chunk: whole rounds of the 256 x 256 tiles of stage 1 as far as they fit. 11008 -> 4096, r = 1024 at 8192
 // tokens: 472 us in chunks of 1536 tokens (1.5 rounds), 421 in chunks of 2048 (2 rounds).
 int64_t blast_chunk_tokens(int64_t T, int b, int r, int64_t most) {
@@ -178,11 +187,16 @@ BlastPlan blast_plan(int64_t T, int n_in, int n_out, int b, int r, blr_dtype dt,
         else pl.path = BlastPlan::MFMA_THREE;
         if (pl.path == BlastPlan::MFMA_STAGE12) { pl.off_A = off; off += align_up((size_t)T * per_token); }
         if (pl.path == BlastPlan::MFMA_THREE) {
+            const bool z8 = flags & BLR_BLAST_Z_FP8;
             int64_t c = (int64_t)(kChunkBytes / per_token) / 256 * 256;
+            if (!z8 && T > kWideTokens && per_token >= kWidePerToken) {
+                const int64_t wide = (int64_t)std::min(kChunkBytesWide / per_token, kWideWithInput / 2 / (per_token + (size_t)n_in * 2)) / 256 * 256;
+                c = std::max(c, wide);
+            }
             if (c < 256) c = 256;
             const int64_t part = c < T ? c : T;         // tokens of one of the two parts
             pl.off_A = off; off += align_up((size_t)part * per_token);
-            if (flags & BLR_BLAST_Z_FP8) {
+            if (z8) {
                 pl.chunk = part;
                 pl.off_Z = off; off += align_up((size_t)part * per_token / 2);                  // one byte per element of an 8-bit Z
             } else {

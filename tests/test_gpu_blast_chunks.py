@@ -32,8 +32,10 @@ def test_against_the_oracle(T, q, p, b, r):
     assert gu.rel_err(Y, oracle.blast_forward(X.f64, lay.U.f64, lay.S.f64, lay.V.f64)) <= gu.TOL["bf16"]
 
 
-@pytest.mark.parametrize("T,r", [(3072 + 5, 1024), (2 * 3072, 1024), (7000, 1024),      # chunks of 1792, 3072 and 3072 tokens
-                                 (513, 4096), (540, 4096)])                             # of 512: a last one of 1 and of 28 tokens
+@pytest.mark.parametrize("T,r", [(3072 + 5, 1024), (2 * 3072, 1024), (7000, 1024),      # chunks of 1792 and of up to 4096 tokens
+                                 (4096, 1024), (4096 + 5, 1024), (8192 + 5, 768),       # ... on both sides of 4096; 5120
+                                 (513, 4096), (540, 4096),                              # of 512: a last one of 1 and of 28 tokens
+                                 (4097, 4096)])                                         # of 1024: a last one of 1 token
 def test_chunks_agree_with_one_chunk(T, r):
     """More tokens than a chunk holds, the coupling in place: rows do not depend on each other, so the rows of a call equal
     those of calls on parts of it that fit one chunk, bit for bit where the products pick the same tiles
@@ -55,7 +57,7 @@ def test_chunks_agree_with_one_chunk(T, r):
         return y
 
     whole = run(X)
-    step = 1000 if r == 1024 else 256
+    step = 256 if r == 4096 else 1000
     parts = torch.cat([run(X[i:i + step].contiguous()) for i in range(0, T, step)])
     torch.cuda.synchronize()
     err = (whole.double() - parts.double()).abs().max() / parts.double().abs().max()
