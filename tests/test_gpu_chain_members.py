@@ -16,7 +16,7 @@ def _lin(x, f):
 
 
 # tokens: q + k + v on 128 x 128 / 128 x 64 / 64 x 64 tiles or as steps, gate and up on all four, one round and several
-@pytest.mark.parametrize("T", [70, 150, 300, 520, 1100, 2050])
+@pytest.mark.parametrize("T", [70, 150, 300, 490, 520, 1100, 2000, 2050])
 @pytest.mark.parametrize("op,hidden,mlp,params", [
     ("monarch", 2048, 8192, dict(nblocks=4, r_square=512, r_mlp=512)), ("blast", 2048, 8192, dict(b=16, r_square=256, r_mlp=512)),
     # 504 columns a block; a rank that stays with the steps, and one of a single trip

@@ -28,6 +28,8 @@ torch = pytest.importorskip("torch")
     (2047, 192, 2300),                                # ... of 128 x 192, three steps
     (1500, 192, 2299), (1500, 200, 2300), (1300, 192, 1148),              # three steps and a partial fourth on four stages
     (1100, 1344, 2044),                               # half of the chip on 128 x 128
+    # a round on nearly every compute unit: 16 x 16 matrix instructions on 192 x 128, 128 x 192, 128 x 256, 256 x 128 and 128 x 128
+    (300, 512, 16380), (600, 320, 9790), (600, 256, 13050), (2040, 320, 4090), (2001, 328, 2044), (2001, 192, 2044),
     (300, 264, 10500),                                # 128 x 128 in one round, where 256 x 128 would fill the chip
 ])
 def test_dense_tiles(T, n_in, n_out):
