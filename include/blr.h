@@ -205,6 +205,8 @@ blr_status blr_lowrank_forward(const void* X, const void* V, const void* U, void
  * blr_blast_pack for the same (n_in, n_out, b, r), `S` is ignored (may be NULL), `U` is still the
  * canonical tensor (bf16 only). workspace: at least blr_blast_workspace_bytes(...) bytes with the
  * same flags (holds A where a kernel needs it; without BLR_BLAST_PACKED also the per-call re-layout).
+ * Beyond 4096 tokens, where b*r is 12288 and more, those bytes let execution (b) take longer chunks (up to 128
+ * instead of 96 MiB, 3-6 % of the time); a workspace of the size for 4096 tokens is accepted too, as by the groups.
  */
 size_t     blr_blast_workspace_bytes(int64_t T, int n_in, int n_out, int b, int r, blr_dtype dt, unsigned flags);
 blr_status blr_blast_forward(const void* X, const void* U, const void* S, const void* V, void* Y,

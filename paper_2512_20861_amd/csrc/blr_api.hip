@@ -166,7 +166,9 @@ bool blast_takes_narrow(int64_t T, int n_in, int n_out, int b, int r, unsigned f
     return wgs <= 256 || (wgs <= 512 && (int64_t)n_in * r <= 100 * 1024 && blast_narrow_lds_bytes(T, n_in, n_out, b, r) <= 80 * 1024);
 }
 
-BlastPlan blast_plan(int64_t T, int n_in, int n_out, int b, int r, blr_dtype dt, unsigned flags) {
+// The plan of a call in a workspace of that many bytes: the wider chunks are a matter of speed, so that a workspace which is too small
+// for them (one of the size that 4096 tokens ask for is enough) runs the others. Unlimited: the plan whose size the query returns.
+BlastPlan blast_plan(int64_t T, int n_in, int n_out, int b, int r, blr_dtype dt, unsigned flags, size_t workspace_bytes = SIZE_MAX) {
     BlastPlan pl{};
     const int q = n_in / b;
     const bool packed = flags & BLR_BLAST_PACKED;
@@ -188,10 +190,11 @@ BlastPlan blast_plan(int64_t T, int n_in, int n_out, int b, int r, blr_dtype dt,
         if (pl.path == BlastPlan::MFMA_STAGE12) { pl.off_A = off; off += align_up((size_t)T * per_token); }
         if (pl.path == BlastPlan::MFMA_THREE) {
             const bool z8 = flags & BLR_BLAST_Z_FP8;
+            const size_t pack = packed ? 0 : pack_layout(n_in, n_out, b, r).total;
             int64_t c = (int64_t)(kChunkBytes / per_token) / 256 * 256;
             if (!z8 && T > kWideTokens && per_token >= kWidePerToken) {
                 const int64_t wide = (int64_t)std::min(kChunkBytesWide / per_token, kWideWithInput / 2 / (per_token + (size_t)n_in * 2)) / 256 * 256;
-                c = std::max(c, wide);
+                if (wide > c && 2 * align_up((size_t)std::min(wide, T) * per_token) + pack <= workspace_bytes) c = wide;
             }
             if (c < 256) c = 256;
             const int64_t part = c < T ? c : T;         // tokens of one of the two parts
@@ -375,7 +378,7 @@ static blr_status blast_run(const void* X, const void* U, const void* S, const v
                             blr_dtype dt, unsigned flags,
                             void* workspace, size_t workspace_bytes, hipStream_t s) {
     const int r = rm * members;                     // stages 1 and 2 see one layer of rank r
-    const BlastPlan pl = blast_plan(T, n_in, n_out, b, r, dt, flags);
+    const BlastPlan pl = blast_plan(T, n_in, n_out, b, r, dt, flags, workspace_bytes);
     if ((flags & BLR_BLAST_PACKED) && pl.path == BlastPlan::GENERIC) return BLR_ERR_UNSUPPORTED;
     if (pl.total > 0 && (!workspace || workspace_bytes < pl.total)) return BLR_ERR_WORKSPACE;
     const int q = n_in / b, p = n_out / b;
@@ -493,12 +496,16 @@ static blr_status blast_run(const void* X, const void* U, const void* S, const v
 // The groups of a chain up to their last product, whose members a combining launch then takes together
 namespace blr {
 
-bool group_tail(bool blast, const void* second, int64_t T, int n_in, int n_out, int b, int r, int members, void* workspace, GroupTail* t) {
+size_t blast_workspace_least(int64_t T, int n_in, int n_out, int b, int r) {
+    return blast_plan(T, n_in, n_out, b, r, BLR_BF16, BLR_BLAST_PACKED, 0).total;
+}
+
+bool group_tail(bool blast, const void* second, int64_t T, int n_in, int n_out, int b, int r, int members, void* workspace, size_t workspace_bytes, GroupTail* t) {
     const int q = n_out / b;
     GemmDesc d{};
     if (blast) {
         if (!blast_group_ok(T, n_in, n_out, b, r, members, BLR_BF16, 0)) return false;
-        const BlastPlan pl = blast_plan(T, n_in, n_out, b, r * members, BLR_BF16, BLR_BLAST_PACKED);
+        const BlastPlan pl = blast_plan(T, n_in, n_out, b, r * members, BLR_BF16, BLR_BLAST_PACKED, workspace_bytes);
         if (pl.path == BlastPlan::MFMA_THREE && pl.chunk < T) return false;                  // A is never there as a whole
         d.A = (const unsigned char*)workspace + pl.off_A;
         d.a_gs = (int64_t)r * members;

@@ -95,7 +95,7 @@ struct Group { bool tail, gathered; GroupTail t; };
 Group group_of(const blr_chain& c, int which, const blr_chain_factors& f, void* out) {
     const Linear l = linear_of(c.d, which);
     Group g{};
-    g.tail = group_tail(c.d.blast, f.second, c.d.T, l.n_in, l.n_out, c.d.b, l.r, l.members, c.buf.workspace, &g.t);
+    g.tail = group_tail(c.d.blast, f.second, c.d.T, l.n_in, l.n_out, c.d.b, l.r, l.members, c.buf.workspace, c.buf.workspace_bytes, &g.t);
     GemmDesc& p = g.t.product;
     p.C = out;
     const int run = l.n_out / c.d.b / c.d.b;
@@ -204,6 +204,7 @@ blr_status blr_chain_create(const blr_chain_desc* desc, const blr_chain_layer* l
             n = l.members > 1 ? blr_blast_group_workspace_bytes(d.T, l.n_in, l.n_out, d.b, l.r, l.members, BLR_BF16, 0)
                               : blr_blast_workspace_bytes(d.T, l.n_in, l.n_out, d.b, l.r, BLR_BF16, BLR_BLAST_PACKED);
             if (!n || !blr_blast_packed_bytes(l.n_in, l.n_out, d.b, l.r * l.members, BLR_BF16)) return BLR_ERR_UNSUPPORTED;
+            n = blast_workspace_least(d.T, l.n_in, l.n_out, d.b, l.r * l.members);
         } else {
             if (l.r % d.b || (l.n_in / d.b) % d.b) return BLR_ERR_UNSUPPORTED;
             n = l.members > 1 ? blr_monarch_rect_workspace_bytes(d.T, l.n_in, l.members * l.n_out, d.b, l.members * d.b, l.r / d.b, BLR_BF16)

@@ -65,12 +65,54 @@ def test_workspace_sizes():
     # enough 128-token x 64-rank tiles (16 x 10 >= 128): the fused kernel is the default, A for all tokens
     assert B.blast_workspace_bytes(2048, 4096, 4096, 16, 640, B.BF16, B.BLAST_PACKED) == 2048 * 16 * 640 * 2
     assert B.blast_workspace_bytes(2048, 4096, 4096, 16, 640, B.BF16, B.BLAST_PACKED | B.BLAST_THREE_KERNELS) == 2 * 2048 * 16 * 640 * 2
-    # many tokens: the chunk (a multiple of 256 tokens whose Z and A are 48 MiB each at most) bounds the workspace
+    # many tokens: the chunk (a multiple of 256 tokens, in two parts of 48 MiB each at most) bounds the workspace
     chunk = (48 << 20) // (16 * 640 * 2) // 256 * 256
     assert B.blast_workspace_bytes(100000, 4096, 4096, 16, 640, B.BF16, B.BLAST_PACKED | B.BLAST_THREE_KERNELS) == 2 * chunk * 16 * 640 * 2
     # portable path keeps Z and A
     assert B.blast_workspace_bytes(50, 36, 30, 3, 10, B.F32, 0) == 2 * ((50 * 3 * 10 * 4 + 255) // 256 * 256)
     assert B.blast_packed_bytes(768, 768, 32, 96) == 0 and B.blast_packed_bytes(768, 768, 16, 96, B.F32) == 0
+
+
+def _blast_bytes(T, n_in, b, r, flags=0):
+    return B.blast_workspace_bytes(T, n_in, 64 * b, b, r, B.BF16, B.BLAST_PACKED | B.BLAST_THREE_KERNELS | flags)
+
+
+def test_workspace_of_long_blast_calls():
+    """Beyond 4096 tokens, from 24 KiB of Z a token on: two parts of up to 64 MiB and 224 MiB with the input, in whole 256 tokens; else of 48."""
+    part = lambda mib, per_token: (mib << 20) // per_token // 256 * 256
+    at_48, at_64 = 2 * part(48, 32768) * 32768, 2 * part(64, 32768) * 32768
+    assert _blast_bytes(4096, 4096, 16, 1024) == at_48 < at_64 == _blast_bytes(4097, 4096, 16, 1024) == _blast_bytes(10 ** 6, 4096, 16, 1024)
+    per = lambda r: 16 * r * 2                           # 24 KiB at r = 768
+    assert _blast_bytes(8192, 4096, 16, 768) == 2 * part(64, per(768)) * per(768)
+    assert _blast_bytes(8192, 4096, 16, 760) == 2 * part(48, per(760)) * per(760)
+    # a part's X and Z within 112 MiB: 2048 tokens of 11008 columns, 1792 of 15360; never less than the 48 MiB parts (32768 columns)
+    assert _blast_bytes(8192, 11008, 16, 1024) == 2 * 2048 * 32768
+    assert _blast_bytes(8192, 15360, 16, 1024) == 2 * 1792 * 32768 > at_48
+    assert _blast_bytes(8192, 32768, 16, 1024) == at_48
+    # the 8-bit intermediate keeps the 48 MiB part of A, and Z beside it
+    assert _blast_bytes(8192, 4096, 16, 1024, B.BLAST_Z_FP8) == B.blast_workspace_bytes(4096, 4096, 1024, 16, 1024, B.BF16, B.BLAST_PACKED | B.BLAST_Z_FP8) == at_48 // 4 * 3
+    # one token more never needs less
+    sizes = [_blast_bytes(T, 4096, 16, 768) for T in range(3900, 5400, 7)]
+    assert sizes == sorted(sizes)
+
+
+def test_smaller_workspace_of_a_long_blast_chain():
+    """The longer chunks are a matter of speed: a chain takes a workspace of the size that 4096 tokens ask for, and no smaller one."""
+    lib = B.lib()
+
+    def create(nbytes):
+        f, out = B.ChainFactors(FAKE, FAKE), ctypes.c_void_p()
+        st = lib.blr_chain_create(ctypes.byref(B.ChainDesc(1, 1, T, 4096, 8192, 16, 256, 384, 1e-6)), (B.ChainLayer * 1)(B.ChainLayer(f, f, f, f)),
+                                  ctypes.byref(B.ChainBuffers(*([FAKE] * 10), nbytes)), ctypes.byref(out))
+        if st == B.OK:
+            lib.blr_chain_destroy(out)
+        return st
+
+    T = 4200
+    group = lambda T: B.blast_group_workspace_bytes(T, 4096, 4096, 16, 256, 3)          # the largest of the four (384 x 2 is as large)
+    most, least = group(T), group(4096 - 128 * 8)                                       # (4096 tokens themselves run the fused stage 1)
+    assert least == 96 << 20 and most == 120 << 20
+    assert create(most) == B.OK and create(least) == B.OK and create(least - 1) == B.ERR_WORKSPACE
 
 
 def _monarch(T=4, n_in=64, n_out=64, nb=4, r=16, dt=B.BF16, flags=0, X=FAKE, R=FAKE, L=FAKE, Y=FAKE, ws=FAKE, wsb=1 << 20):

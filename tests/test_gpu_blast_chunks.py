@@ -33,7 +33,7 @@ def test_against_the_oracle(T, q, p, b, r):
 
 
 @pytest.mark.parametrize("T,r", [(3072 + 5, 1024), (2 * 3072, 1024), (7000, 1024),      # chunks of 1792 and of up to 4096 tokens
-                                 (4096, 1024), (4096 + 5, 1024), (8192 + 5, 768),       # ... on both sides of 4096; 5120
+                                 (4096, 1024), (4096 + 5, 1024), (8192 + 5, 768),       # ... on both sides of 4096; 4352
                                  (513, 4096), (540, 4096),                              # of 512: a last one of 1 and of 28 tokens
                                  (4097, 4096)])                                         # of 1024: a last one of 1 token
 def test_chunks_agree_with_one_chunk(T, r):
@@ -62,6 +62,38 @@ def test_chunks_agree_with_one_chunk(T, r):
     torch.cuda.synchronize()
     err = (whole.double() - parts.double()).abs().max() / parts.double().abs().max()
     assert torch.isfinite(whole).all() and float(err) <= 3 * 2.0 ** -9
+
+
+@pytest.mark.parametrize("T", [4096 + 5, 8192 + 1])
+@pytest.mark.parametrize("packed", [True, False])
+def test_workspace_of_the_shorter_chunks(T, packed):
+    """The longer chunks beyond 4096 tokens are a matter of speed: a call in a workspace of the size that 4096 tokens ask for runs
+    in shorter ones, inside it (both round two intermediates and the output to bf16: 3 * 2^-9 of the largest value)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    B = gu.B
+    b, q, p, r = 16, 64, 16, 1024
+    flags = B.BLAST_THREE_KERNELS | (B.BLAST_PACKED if packed else 0)
+    most, least = (B.blast_workspace_bytes(t, b * q, b * p, b, r, B.BF16, flags) for t in (T, 4096))
+    assert least < most
+    g = torch.Generator(device="cuda").manual_seed(T)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda")
+    U, S, V = ((rand(*s) / r ** 0.5).bfloat16() for s in ((b, p, r), (b, b, r), (b, q, r)))
+    X = rand(T, b * q).bfloat16()
+    pk = B.blast_pack(U, S, V, b * q, b * p, b, r)
+    buf = torch.full((most,), 0x5A, dtype=torch.uint8, device="cuda")
+    ys = [torch.full((T, b * p), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    for y, size in zip(ys, (least, most)):
+        B.blast_forward(X, U, None if packed else S, pk if packed else V, y, b, r, flags, workspace=buf[:size])
+        if size == least:
+            torch.cuda.synchronize()
+            assert bool((buf[size:] == 0x5A).all())
+    err = (ys[0].double() - ys[1].double()).abs().max() / ys[1].double().abs().max()
+    assert torch.isfinite(ys[0]).all() and float(err) <= 3 * 2.0 ** -9
+    with pytest.raises(B.BlrError) as e:
+        B.blast_forward(X, U, None if packed else S, pk if packed else V, ys[0], b, r, flags, workspace=buf[:least - 256])
+    assert e.value.status == B.ERR_WORKSPACE
 
 
 def test_unaligned_blocks_and_a_last_column_tile():

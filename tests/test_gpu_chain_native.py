@@ -188,3 +188,27 @@ def test_replaced_parts_are_used(op, T):
     for _ in range(3):
         with pytest.raises(ValueError):
             chain.forward(x)
+
+
+def test_smaller_workspace_of_a_long_blast_chain():
+    """A chain in a workspace of the size of 4096 tokens' chunks: q + k + v and gate * up are then no longer combined in one piece,
+    nothing behind it is written, and the result is that of the longer chunks up to the rounding of the 20 stored values in between."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util as gu
+    from paper_2512_20861_amd.chain import DeviceChain
+    T = 4200
+    layers = bi.chain_layers("blast", n_layers=1, hidden=4096, mlp=8192, params=dict(b=16, r_square=256, r_mlp=384), dtype="bf16")
+    x = gu.to_dev(bi.activations(T, 4096, "bf16"))
+    chain = DeviceChain(layers, T, eps=oc.EPS)
+    assert chain._native and chain.ws.numel() == 120 << 20
+    want = chain.forward(x).clone()
+    whole = chain.ws
+    whole.fill_(0x5A)
+    chain.ws = whole[:96 << 20]
+    for _ in range(4):                                   # step by step, then the new handle's launches and its graph
+        chain.h.fill_(float("nan"))
+        got = chain.forward(x)
+        torch.cuda.synchronize()
+        assert torch.isfinite(got).all() and gu.rel_err(gu.to_f64(got), gu.to_f64(want)) <= 2e-2
+    assert chain._native and bool((whole[96 << 20:] == 0x5A).all())
