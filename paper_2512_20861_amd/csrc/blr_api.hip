@@ -3,6 +3,7 @@
 #include "../../include/blr_measure.h"
 #include "blr_common.h"
 #include <algorithm>
+#include <cstring>
 #include <mutex>
 
 using namespace blr;
@@ -775,6 +776,30 @@ blr_status blr_dense_reference_forward(const void* X, const void* W, void* Y,
     d.C = Y; d.c_rs = n_out; d.c_gs = 0; d.c_div = 1; d.c_hi = 1; d.c_lo = 0;
     d.M = T; d.N = n_out; d.K = n_in; d.G = 1;
     return run_gemm(d, dt, !(flags & BLR_FORCE_GENERIC), (hipStream_t)stream);
+}
+
+blr_status blr_product_tiles(int64_t M, int N, int K, int G, int run, unsigned form, int members, char* names, size_t size) {
+    if (M <= 0 || N <= 0 || K <= 0 || G <= 0 || run < 0 || (run && N % run) || members < 1 || members > 3 || !names || !size ||
+        (form & ~(BLR_PRODUCT_INTERLEAVED | BLR_PRODUCT_WINDOWS | BLR_PRODUCT_8_BIT))) return BLR_ERR_INVALID_ARG;
+    GemmDesc d{};
+    void* operand = (void*)(uintptr_t)256;              // (aligned, and never looked at)
+    d.A = operand; d.a_gs = K; d.a_rs = (int64_t)members * G * K;
+    d.B = operand; d.b_gs = (int64_t)N * K; d.b_rs = K; d.b_ks = 1;
+    d.C = operand; d.c_rs = (int64_t)G * N; d.c_gs = N; d.c_div = 1; d.c_hi = 1;
+    if (run) { d.b_div = run; d.b_mul = N / run; d.c_gs = run; d.c_div = run; d.c_hi = (int64_t)G * run; d.c_lo = 1; }
+    if (form & BLR_PRODUCT_INTERLEAVED) { d.c_gs = 1; d.c_hi = G; }
+    d.M = M; d.N = N; d.K = K; d.G = G;
+    d.c_fp8 = form & BLR_PRODUCT_8_BIT ? 1 : 0;
+    d.k_align = form & BLR_PRODUCT_WINDOWS && gemm_whole_line_tiles(d) ? 1 : 0;
+    try {                                               // (no exception leaves a C entry)
+        std::string text;
+        if (gemm_tile_names(d, members, &text) != hipSuccess) return BLR_ERR_UNSUPPORTED;
+        if (text.size() + 1 > size) return BLR_ERR_WORKSPACE;
+        std::memcpy(names, text.c_str(), text.size() + 1);
+    } catch (const std::exception&) {
+        return BLR_ERR_INVALID_ARG;
+    }
+    return BLR_OK;
 }
 
 }  // extern "C"

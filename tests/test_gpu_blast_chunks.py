@@ -11,17 +11,32 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("T,q,p,b,r", [
-    # windows of 64-column chunks: 64 | b q, 64 does not divide q, q >= 128 and 160 and more tiles of 128 x 128
-    (330, 152, 24, 16, 512), (1300, 344, 32, 8, 264),                    # 128 x 128 tiles, two stages
-    (520, 344, 16, 8, 520), (700, 584, 16, 8, 520),                      # ... in one round: eight wavefronts, four on a full chip
-    (1200, 152, 24, 16, 264), (2700, 136, 16, 16, 264),                  # 128 x 128 and 128 x 192, by the estimate
-    (500, 344, 16, 16, 640), (700, 344, 16, 16, 1024),                   # 256 x 128, 256 x 256
-    (300, 344, 16, 16, 1024), (640, 344, 16, 8, 1144), (800, 344, 16, 8, 1016),   # one round of 192 x 128, 128 x 192, 128 x 256
-    # blocks read for themselves: short ones, too few tiles
-    (700, 88, 64, 16, 136), (640, 184, 40, 8, 128),
-    (270, 64, 40, 16, 1032),                                             # a partial last group of rank indices
-])
+# kernel of the first stage -> sizes (T, q, p, b, r) it is chosen for; test_tile_rules.py checks that it still is. Windows of 64-column
+# chunks: 64 | b q, 64 does not divide q, q >= 128 and 160 and more tiles of 128 x 128
+STAGE1 = {
+    "128x128 w4 k64x2 i32 windows": [(330, 152, 24, 16, 512), (1200, 152, 24, 16, 264)],
+    "192x128 w4 k64x2 i32 windows": [(1329, 136, 16, 8, 656)],
+    "128x192 w4 k64x2 i32 windows": [(2700, 136, 16, 16, 264)],
+    "128x128 w8 k64x4 i32 windows": [(520, 344, 16, 8, 520)],
+    "128x128 w8 k64x4 i16 windows": [(521, 208, 16, 16, 264)],
+    "128x128 w4 k64x4 i32 windows": [(700, 584, 16, 8, 520)],
+    "192x128 w8 k64x3 i32 windows": [(1300, 344, 32, 8, 264)],
+    "192x128 w8 k64x3 i16 windows": [(300, 344, 16, 16, 1024)],
+    "128x192 w8 k64x3 i32 windows": [(1052, 200, 16, 16, 136)],
+    "128x192 w8 k64x3 i16 windows": [(640, 344, 16, 8, 1144)],
+    "128x256 w8 k64x3 i32 windows": [(800, 344, 16, 8, 1016)],
+    "128x256 w8 k64x3 i16 windows": [(513, 200, 16, 8, 1336)],
+    "256x128 w8 k64x3 i32 windows": [(500, 344, 16, 16, 640)],
+    "256x128 w8 k64x3 i16 windows": [(267, 152, 16, 16, 912)],
+    "256x256 w8 k64x2 i32 windows": [(700, 344, 16, 16, 1024)],
+    # blocks read for themselves: short ones, too few tiles; a partial last group of rank indices
+    "128x128 w4 k32x4 i32 partial": [(700, 88, 64, 16, 136)],
+    "64x64 w4 k64x2 i32 partial": [(640, 184, 40, 8, 128)],
+    "128x128 w4 k32x4 i32": [(270, 64, 40, 16, 1032)],
+}
+
+
+@pytest.mark.parametrize("T,q,p,b,r", [row for sizes in STAGE1.values() for row in sizes])
 def test_against_the_oracle(T, q, p, b, r):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

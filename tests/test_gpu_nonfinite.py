@@ -68,11 +68,27 @@ def test_coupling_of_absent_blocks(T, b, r):
     _blast(T, 64, 40, b, r, [(1, b * 64 - 1)], 0)
 
 
-@pytest.mark.parametrize("T,q,b,r", [
-    (1300, 344, 8, 264), (2700, 136, 16, 264),           # 128 x 128 and 128 x 192 tiles
-    (520, 344, 8, 520), (700, 584, 8, 520),              # one round of 128 x 128, eight wavefronts and four
-    (500, 344, 16, 640), (700, 344, 16, 1024),           # 256 x 128, 256 x 256
-])
+# kernel of the first stage -> sizes (T, q, b, r) it is chosen for; test_tile_rules.py checks that it still is
+WINDOWS = {
+    "128x128 w4 k64x2 i32 windows": [(330, 152, 16, 512)],
+    "192x128 w4 k64x2 i32 windows": [(1329, 136, 8, 656)],
+    "128x192 w4 k64x2 i32 windows": [(2700, 136, 16, 264)],
+    "128x128 w8 k64x4 i32 windows": [(520, 344, 8, 520)],
+    "128x128 w8 k64x4 i16 windows": [(521, 208, 16, 264)],
+    "128x128 w4 k64x4 i32 windows": [(700, 584, 8, 520)],
+    "192x128 w8 k64x3 i32 windows": [(1300, 344, 8, 264)],
+    "192x128 w8 k64x3 i16 windows": [(300, 344, 16, 1024)],
+    "128x192 w8 k64x3 i32 windows": [(1052, 200, 16, 136)],
+    "128x192 w8 k64x3 i16 windows": [(640, 344, 8, 1144)],
+    "128x256 w8 k64x3 i32 windows": [(800, 344, 8, 1016)],
+    "128x256 w8 k64x3 i16 windows": [(513, 200, 8, 1336)],
+    "256x128 w8 k64x3 i32 windows": [(500, 344, 16, 640)],
+    "256x128 w8 k64x3 i16 windows": [(267, 152, 16, 912)],
+    "256x256 w8 k64x2 i32 windows": [(700, 344, 16, 1024)],
+}
+
+
+@pytest.mark.parametrize("T,q,b,r", [row for sizes in WINDOWS.values() for row in sizes])
 def test_windows_of_input_blocks(T, q, b, r):
     """Input blocks read in 64-column chunks of the input row: infinities in the first and the last column of a block, which
     its neighbours' windows hold too."""
