@@ -80,12 +80,13 @@ struct BlastPlan {
 // holds two parts of kChunkBytes (kChunkBytesWide): one buffer of both for the 16-bit Z, Z and A side by side for the 8-bit one.
 constexpr size_t kChunkBytes = 48u << 20;
 // 64 MiB a part for the 16-bit Z from 24 KiB of it per token on (r = 768 in 16 blocks), as far as a chunk's X and Z stay under 224 MiB
-// together: a chunk more is three launches and their partial rounds, and beyond that X pushes Z out of the cache (11008 -> 4096 at
-// 8192 tokens: r = 1024 in chunks of 2048 / 3072 / 4096 / 8192 tokens, X and Z of 107 / 161 / 214 / 428 MiB, 414 / 396 / 384 / 434 us; r = 512
-// in chunks of 4096 / 8192, 150 / 300 MiB, 202 / 222). Against 48 MiB: 4096 x 4096, r = 1024 at 6304 tokens 215 -> 202, 8192 -> 2048, r = 768 at
-// 5000 140 -> 134, 11008 -> 4096, r = 1024 at 20000 955 -> 939; level where the rounds come out the same, as at 4096 tokens (188), up to
-// which the smaller parts stay. Lower ranks are level (4096 x 4096,
-// r = 640 at 8192 tokens 172 in chunks of 4096 and of 8192) and keep the smaller workspace.
+// together (never less than the 48 MiB parts): a chunk more is three launches and their partial rounds, and beyond that X pushes Z out of the
+// cache (11008 -> 4096 at 8192 tokens: r = 1024 in chunks of 2048 / 3072 / 4096 / 8192 tokens, X and Z of 107 / 161 / 214 / 428 MiB, 414 /
+// 396 / 384 / 434 us; r = 512 in chunks of 4096 / 8192, 150 / 300 MiB, 202 / 222). Parts of 48 against 64 MiB on two cards: 4096 x 4096,
+// r = 1024 at 6304 tokens 212-215 -> 200, r = 768 at 5000 134-136 -> 120, 8192 -> 2048, r = 768 at 5000 141 -> 126, 11008 -> 4096 at 8192
+// r = 896 353-357 -> 337-343 and r = 1024 385 -> 378-384, at 20000 936-940 -> 907-929; level (0.99-1.01) where the rounds come out the same, as
+// at 4097 tokens, up to where the smaller parts stay; behind for 4096 x 4096, r = 2048 in 8 blocks at 8192 (398-405 -> 404-410). Lower ranks
+// are level (4096 x 4096, r = 640 at 8192 tokens 172 in chunks of 4096 and of 8192) and keep the smaller workspace.
 constexpr size_t kChunkBytesWide = 64u << 20, kWidePerToken = 24u << 10, kWideWithInput = 224u << 20;
 constexpr int64_t kWideTokens = 4096;
 // Tokens per chunk: whole rounds of the 256 x 256 tiles of stage 1 as far as they fit. 11008 -> 4096, r = 1024 at 8192
@@ -105,18 +106,19 @@ int64_t blast_chunk_tokens(int64_t T, int b, int r, int64_t most) {
 // The fused stage 1 + coupling kernel runs one workgroup per compute unit on tiles of 64 ranks and 128 tokens (64 up to 128
 // tiles). What it saves, the round trip of Z, grows with b r per token; what it pays, a stage 1 on tiles of half the
 // arithmetic intensity of the GEMM's and a last round that is partly empty, grows with n_in r: a workgroup walks n_in
-// indices. Graph replays on one card, fused against three kernels in us:
-//   short inputs, whatever the rounds: 768 -> 2304, b = 6, r = 192 at 12608 / 24576 tokens (1.16 / 2.25 rounds) 62 / 102
-//     against 69 / 117; b = 3, r = 128 at 6304 (0.39) 24.6 against 31.0; 1152 wide, b = 9, r = 640 at 20000 (6.1) 202 / 250;
-//   n_in = 2048: ahead from 0.7 of the rounds on (2048 -> 8192, b = 16, r = 512 at 6304 / 10000 tokens 144 / 217 against
-//     158 / 241), behind at 0.62 with r = 256 (90 / 85);
-//   longer inputs: only with full rounds (r = 1024, 4096 x 4096 at 4096 tokens 145 / 170; r = 640 at 4096 / 8192 tokens, 1.25 /
-//     2.5 rounds: 113 / 214 against 98 / 196); with too few tiles it leaves too much of the chip idle.
+// indices. Graph replays on two cards, fused against three kernels in us:
+//   short inputs, whatever the rounds: 768 -> 2304, b = 6, r = 192 at 12608 / 24576 tokens (1.16 / 2.25 rounds) 59 / 94
+//     against 65 / 108; b = 3, r = 128 at 6304 (0.39) 26.0 against 32.1; 1152 wide, b = 9, r = 640 at 20000 (6.1) 200 / 236;
+//   n_in = 2048: ahead or level from 0.7 of the rounds on (2048 -> 8192, b = 16, r = 512 at 6304 / 10000 tokens 128 / 210 against
+//     144 / 210), behind at 0.62 with r = 256 (90 / 85);
+//   longer inputs: only with full rounds, and no longer there: since stage 1 walks its tiles the three kernels are ahead (4096 x 4096,
+//     r = 1024 at 2048 / 4096 / 8192 tokens 72 / 153 / 312 against 68 / 135 / 261, r = 640 at 2048 61 / 56), which the limits below do
+//     not know yet; r = 640 at 4096 / 8192 tokens, 1.25 / 2.5 rounds: 111 / 208 against 85 / 171.
 // Input blocks longer than 256 columns lose to three kernels where the stage-1 GEMM fills its 256-wide tiles or the input is long
-// (11008 -> 4096, r = 1024 at 2048 / 8192 tokens 121 / 504 against 100 / 400; 8192 -> 2048, r = 256 at 8192 105 / 94). With ranks
-// up to 256 and a shorter input the fused kernel is ahead: 3072 -> 768, r = 192, b = 6 at 32768 tokens 138 / 153, r = 128, b = 3
-// at 6304 24.6 / 29.9, 2048 -> 2048, b = 4, r = 256 at 24576 118 / 144; 4608 -> 1152, b = 9, r = 256 at 8192 / 24576 56 / 176
-// against 66 / 198, but 92 / 78 at 10000 (1.23 rounds).
+// (11008 -> 4096, r = 1024 at 2048 / 8192 tokens 116 / 502 against 92 / 380; 8192 -> 2048, r = 256 at 8192 100 / 88). With ranks
+// up to 256 and a shorter input the fused kernel is ahead: 3072 -> 768, r = 192, b = 6 at 32768 tokens 133 / 147, r = 128, b = 3
+// at 6304 25.8 / 28.1, 2048 -> 2048, b = 4, r = 256 at 24576 104 / 124; 4608 -> 1152, b = 9, r = 256 at 8192 / 24576 55 / 174
+// against 64 / 185, but 89 / 72 at 10000 (1.23 rounds).
 bool fused_pays(int64_t T, int n_in, int b, int r) {
     const int q = n_in / b;
     const int64_t tiles = blast_fused_tiles(T, r), wgs = tiles <= 128 ? 2 * tiles : tiles;
