@@ -47,11 +47,13 @@ def test_against_the_oracle(T, q, p, b, r):
     assert gu.rel_err(Y, oracle.blast_forward(X.f64, lay.U.f64, lay.S.f64, lay.V.f64)) <= gu.TOL["bf16"]
 
 
-@pytest.mark.parametrize("T,r", [(3072 + 5, 1024), (2 * 3072, 1024), (7000, 1024),      # chunks of 1792 and of up to 4096 tokens
-                                 (4096, 1024), (4096 + 5, 1024), (8192 + 5, 768),       # ... on both sides of 4096; 4352
-                                 (513, 4096), (540, 4096),                              # of 512: a last one of 1 and of 28 tokens
-                                 (4097, 4096)])                                         # of 1024: a last one of 1 token
-def test_chunks_agree_with_one_chunk(T, r):
+@pytest.mark.parametrize("T,r,q", [
+    (3072 + 5, 1024, 64), (2 * 3072, 1024, 64), (7000, 1024, 64),         # chunks of 1792 and of up to 4096 tokens
+    (4096, 1024, 64), (4096 + 5, 1024, 64), (8192 + 5, 768, 64),          # ... on both sides of 4096; 4352
+    (4096 + 5, 1024, 960),                                                # ... of up to 3584, where the input bounds them
+    (513, 4096, 64), (540, 4096, 64),                                     # of 512: a last one of 1 and of 28 tokens
+    (4097, 4096, 64)])                                                    # of 1024: a last one of 1 token
+def test_chunks_agree_with_one_chunk(T, r, q):
     """More tokens than a chunk holds, the coupling in place: rows do not depend on each other, so the rows of a call equal
     those of calls on parts of it that fit one chunk, bit for bit where the products pick the same tiles
     (they need not: bf16 rounding of two intermediates and the output, 3 * 2^-9 of the largest value)."""
@@ -59,7 +61,7 @@ def test_chunks_agree_with_one_chunk(T, r):
         pytest.skip("no GPU")
     import gpu_util as gu
     B = gu.B
-    b, q, p = 16, 64, 16
+    b, p = 16, 16
     g = torch.Generator(device="cuda").manual_seed(T)
     rand = lambda *s: torch.randn(s, generator=g, device="cuda")
     U, S, V = ((rand(*s) / r ** 0.5).bfloat16() for s in ((b, p, r), (b, b, r), (b, q, r)))
