@@ -41,7 +41,8 @@ typedef struct {
 typedef struct { const void* first; const void* second; } blr_chain_factors;
 typedef struct { blr_chain_factors qkv, o, gate_up, down; } blr_chain_layer;
 
-/* Device buffers: h, h2, n, a, o, dn [T][hidden]; qkv [T][3 hidden]; gu [T][2 mlp]; m [T][mlp]; workspace: the largest of the linears. */
+/* Device buffers: h, h2, n, a, o, dn [T][hidden]; qkv [T][3 hidden]; gu [T][2 mlp]; m [T][mlp]; workspace: the largest of the linears (BLAST
+ * beyond 4096 tokens: the smaller sizes that blr_blast_forward accepts will do). */
 typedef struct {
     void *h, *h2, *n, *a, *o, *dn, *qkv, *gu, *m, *workspace;
     size_t workspace_bytes;

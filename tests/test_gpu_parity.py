@@ -219,8 +219,15 @@ def test_dense_parity(T, n_in, n_out, dtype, generic):
 # enough 256 x 256 tiles for the large-tile kernel, whose steps are 64 contraction indices deep: an even and an odd
 # number of steps, a last step with 8 valid indices, ragged token and output counts (a last row of tiles with one row)
 # (the last case: 8 x 43 tiles are one round and a third; the column tiles that fill the round and the remaining
-# 2816 columns go out as two products)
-@pytest.mark.parametrize("T,n_in,n_out", [(2561, 328, 4100), (2600, 456, 4096), (2560, 448, 4096), (2817, 192, 3848), (2048, 256, 11008)])
+# 2816 columns go out as two products). T, n_in, n_out by kernel; test_tile_rules.py checks that it is
+DENSE_LARGE = {
+    "256x256 w8 k64x2 i32 partial": [(2561, 328, 4100), (2600, 456, 4096)],
+    "256x256 w8 k64x2 i32": [(2560, 448, 4096), (2817, 192, 3848)],
+    "256x256 w8 k64x2 i32 + 256x128 w8 k64x3 i32": [(2048, 256, 11008)],
+}
+
+
+@pytest.mark.parametrize("T,n_in,n_out", [row for sizes in DENSE_LARGE.values() for row in sizes])
 def test_dense_large_tile_short_and_partial_steps(T, n_in, n_out):
     gu = _gu()
     W = bi.dense_weight(n_in, n_out, "bf16")
@@ -235,10 +242,24 @@ def test_dense_large_tile_short_and_partial_steps(T, n_in, n_out):
     assert err <= gu.TOL["bf16"]
 
 
-# more workgroups than one round on each of the four small tiles (128x128, 128x64, 64x128, 64x64 by the dispatch
-# rules), which take 64-deep steps on two stages: whole steps and a partial last step, odd and even step counts
-@pytest.mark.parametrize("T,n_out", [(6304, 768), (2800, 768), (64, 40960), (1400, 768)])
-@pytest.mark.parametrize("n_in", [320, 328, 448])
+# more workgroups than one round on each of the four small tiles, which take 64-deep steps on two stages: whole steps and a
+# partial last step, odd and even step counts; and the same sizes where a single round of other tiles is taken instead
+DENSE_SMALL = {
+    "128x128 w4 k64x2 i32": [(10756, 320, 644), (10756, 448, 644)],
+    "128x128 w4 k64x2 i32 partial": [(6304, 328, 768)],
+    "192x128 w8 k64x3 i32": [(6304, 320, 768), (6304, 448, 768)],
+    "128x64 w4 k64x2 i32": [(33000, 320, 64), (33000, 448, 64)],
+    "128x64 w4 k64x2 i32 partial": [(33000, 328, 64)],
+    "128x128 w8 k64x4 i32": [(2800, 320, 768), (2800, 448, 768)],
+    "128x128 w8 k64x4 i32 partial": [(2800, 328, 768)],
+    "64x128 w4 k64x2 i32": [(64, 320, 40960), (64, 448, 40960)],
+    "64x128 w4 k64x2 i32 partial": [(64, 328, 40960)],
+    "64x64 w4 k64x2 i32": [(1400, 320, 768), (1400, 448, 768)],
+    "64x64 w4 k64x2 i32 partial": [(1400, 328, 768)],
+}
+
+
+@pytest.mark.parametrize("T,n_in,n_out", [row for sizes in DENSE_SMALL.values() for row in sizes])
 def test_dense_multi_round_small_tiles(T, n_in, n_out):
     gu = _gu()
     W = bi.dense_weight(n_in, n_out, "bf16")

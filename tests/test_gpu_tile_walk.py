@@ -114,14 +114,28 @@ def test_every_row_monarch(T, b, p, rp, q, order):
     agree(call(X), lambda t: call(X[t:t + 128].contiguous()))
 
 
-@pytest.mark.parametrize("b", [16, 17, 24, 48])
-@pytest.mark.parametrize("T,p", [(4096, 256), (4100, 328), (2570, 320)])
+def short_run(b):
+    return max(160 // b, 3)
+
+
+# kernels -> b, T, p. On the 256 x 256 tile alone, with more tiles than compute units: walked up to 16 batch entries, above that one tile
+# to a workgroup. The others: one round of it, one round and the rows of the next on smaller tiles, and what the estimate takes in its place
+SHORT_RUNS = {
+    "256x256 w8 k64x2 i32 partial": [(16, 7000, 328), (17, 7000, 328), (24, 7000, 328), (24, 4100, 328)],
+    "256x256 w8 k64x2 i32": [(16, 4096, 256), (16, 2570, 320), (17, 2570, 320)],
+    "256x256 w8 k64x2 i32 + 128x128 w4 k64x2 i32": [(17, 4096, 256)],
+    "256x256 w8 k64x2 i32 partial + 128x128 w4 k64x2 i32 partial": [(16, 4100, 328), (17, 4100, 328), (48, 4100, 328), (48, 7000, 328)],
+    "128x192 w4 k64x2 i32": [(24, 4096, 256), (24, 2570, 320), (48, 4096, 256), (48, 2570, 320)],
+}
+
+
+@pytest.mark.parametrize("b,T,p", [row for sizes in SHORT_RUNS.values() for row in sizes])
 def test_every_row_short_runs(T, b, p):
-    """First products whose columns go out in runs of a few elements: up to 16 batch entries walked, above that one tile to a workgroup."""
+    """First products whose columns go out in runs of a few elements, b the number of batch entries."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import gpu_util as gu
-    B, rp, q = gu.B, max(160 // b, 3), 64
+    B, rp, q = gu.B, short_run(b), 64
     gen = torch.Generator(device="cuda").manual_seed(T + b)
     X, R, L = draw(gen, T, b * p), draw(gen, b, rp * b, p, scale=p ** -0.5), draw(gen, b, q, b * rp, scale=(b * rp) ** -0.5)
     call = lambda x: B.monarch_rect_forward(x, R, L, gu.empty_out(x.shape[0], b * q, "bf16"), b, b, rp, B.MONARCH_OUT_BLOCKED)

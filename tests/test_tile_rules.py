@@ -10,6 +10,8 @@ pytest.importorskip("torch")
 import test_gpu_blast_chunks as chunks
 import test_gpu_gemm_tiles as tiles
 import test_gpu_nonfinite as nonfinite
+import test_gpu_parity as parity
+import test_gpu_tile_walk as walk
 from paper_2512_20861_amd import binding as B
 
 INTERLEAVED, WINDOWS, EIGHT_BIT = 1, 2, 4
@@ -31,7 +33,7 @@ def cases(table):
     return [(name, row) for name, sizes in table.items() for row in sizes]
 
 
-@pytest.mark.parametrize("name,row", cases(tiles.DENSE))
+@pytest.mark.parametrize("name,row", cases(tiles.DENSE) + cases(parity.DENSE_LARGE) + cases(parity.DENSE_SMALL))
 def test_dense_rows(name, row):
     T, n_in, n_out = row
     assert kernels(T, n_out, n_in) == name
@@ -48,6 +50,13 @@ def test_monarch_rows(name, row):
 def test_rows_of_input_windows(name, row):
     T, q, b, r = row
     assert kernels(T, r, q, b, form=WINDOWS) == name
+
+
+@pytest.mark.parametrize("name,row", cases(walk.SHORT_RUNS))
+def test_rows_of_short_runs(name, row):
+    b, T, p = row
+    rp = walk.short_run(b)
+    assert kernels(T, b * rp, p, b, run=rp) == name
 
 
 def test_pairs_of_matrix_instructions():
