@@ -15,8 +15,12 @@ def _lin(x, f):
     return oracle.monarch_forward(x, f.R.f64, f.L.f64) if hasattr(f, "R") else oracle.blast_forward(x, f.U.f64, f.S.f64, f.V.f64)
 
 
-# tokens: q + k + v on 128 x 128 / 128 x 64 / 64 x 64 tiles or as steps, gate and up on all four, one round and several
-@pytest.mark.parametrize("T", [70, 150, 300, 490, 520, 1100, 2000, 2050])
+# tokens: q + k + v on 128 x 128 / 128 x 64 / 64 x 64 tiles or as steps, gate and up on all four, one round and several, both matrix
+# instructions
+TOKENS = [70, 150, 300, 490, 520, 1100, 1700, 2000, 2050]
+
+
+@pytest.mark.parametrize("T", TOKENS)
 @pytest.mark.parametrize("op,hidden,mlp,params", [
     ("monarch", 2048, 8192, dict(nblocks=4, r_square=512, r_mlp=512)), ("blast", 2048, 8192, dict(b=16, r_square=256, r_mlp=512)),
     # 504 columns a block; a rank that stays with the steps, and one of a single trip

@@ -21,8 +21,13 @@ def _bits(values):
     return torch.from_numpy(np.asarray(values, dtype=np.float32)).bfloat16().view(torch.int16).numpy().view(np.uint16)
 
 
-# 64 x 64, 128 x 64 and 128 x 128 tiles in one round, 128 x 128 tiles in several; the weight-streaming kernel
-@pytest.mark.parametrize("T", [128, 150, 300, 520, 16])
+# 64 x 64, 128 x 64 and 128 x 128 tiles in one round (a nearly full one on the other matrix instruction), 128 x 128 tiles in several; the
+# weight-streaming kernel
+TILES = {"2 of 64x64 w4 k64x4 i32": 128, "2 of 128x64 w8 k64x4 i32": 150, "2 of 128x128 w8 k64x4 i32": 300, "2 of 128x128 w8 k64x4 i16": 490,
+         "2 of 128x128 w4 k64x2 i32": 520, "": 16}
+
+
+@pytest.mark.parametrize("T", list(TILES.values()))
 def test_every_gate(T):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

@@ -8,9 +8,11 @@ import pytest
 
 pytest.importorskip("torch")
 import test_gpu_blast_chunks as chunks
+import test_gpu_chain_members as chain_members
 import test_gpu_gemm_tiles as tiles
 import test_gpu_nonfinite as nonfinite
 import test_gpu_parity as parity
+import test_gpu_silu_gate as gate
 import test_gpu_tile_walk as walk
 from paper_2512_20861_amd import binding as B
 
@@ -57,6 +59,15 @@ def test_rows_of_short_runs(name, row):
     b, T, p = row
     rp = walk.short_run(b)
     assert kernels(T, b * rp, p, b, run=rp) == name
+
+
+def test_combined_members():
+    for name, T in gate.TILES.items():
+        assert kernels(T, gate.MLP // gate.NB, gate.R, gate.NB, members=2) == name
+    forms = ["64x64 w4 k64x4 i32", "128x64 w8 k64x4 i32", "128x128 w8 k64x4 i32", "128x128 w8 k64x4 i16", "128x128 w4 k64x2 i32"]
+    for members, products in ((3, ((512, 512, 4), (128, 256, 16))), (2, ((2048, 512, 4), (512, 512, 16), (504, 256, 15)))):
+        for N, K, G in products:                         # of the chains of 2048 / 8192 and 1920 / 7560
+            assert {f"{members} of {form}" for form in forms} <= {kernels(T, N, K, G, members=members) for T in chain_members.TOKENS}
 
 
 def test_pairs_of_matrix_instructions():
